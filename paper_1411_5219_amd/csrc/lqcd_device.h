@@ -168,10 +168,17 @@ __device__ __forceinline__ T bload(rsrc_t r, uint32_t voff, uint32_t soff)
 using u32x4 = __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t;
 using u32x2 = __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t;
 
+// 16-byte stores carry the plane offset in the per-lane offset: a store of more
+// than 64 bits reads its data registers for some cycles after it issues, and
+// the compiler keeps a following instruction from overwriting them only when
+// the scalar offset is zero.  With an SGPR there it allowed an overwrite in
+// the very next instruction, and on gfx950 single lanes then stored the new
+// value (seen as wrong halves in one word of an FP16 field copy).
 template <int AUX = 0, class T>
 __device__ __forceinline__ void bstore(rsrc_t r, uint32_t voff, uint32_t soff, const T& v)
 {
-    if constexpr (sizeof(T) == 16) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff, soff, AUX);
+    if constexpr (sizeof(T) == 16)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff + soff, 0, AUX);
     else if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, voff, soff, AUX);
     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, voff, soff, AUX);
 }
