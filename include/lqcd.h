@@ -189,33 +189,25 @@ typedef struct {
  * several stacked right-hand sides, nrhs > 1; LQCD_KERNEL_STAG: the
  * staggered hop, which ignores rhs_tile and rhs_group; LQCD_KERNEL_BLAS: the
  * site-local kernels) at one storage precision:
- *   block   work-items per block (64, 128, 192 or 256; with order = 1 the
- *           requested size, the block then holds whole x-rows)
+ *   block   work-items per block (64, 128, 192 or 256); hop kernels: the sites
+ *           that are neighbours in the block order, in chunks of 64
  *   swizzle 1: block indices are remapped so that each of the 8 XCDs works
  *           on a contiguous range of blocks
  *   order   hop kernels only.  0: blocks walk the sites in memory order;
- *           1: a block covers whole x-rows at one (z, t) and blocks run
- *           t fastest, then z, so neighbour spinors are reused from the
- *           XCD's L2 cache; k in 2..64: the same row blocks in z-slabs of
+ *           1: a block covers chunks of one xy plane at one (z, t) and blocks
+ *           run t fastest, then z, so neighbour spinors are reused from the
+ *           XCD's L2 cache; k in 2..64: the same blocks in z-slabs of
  *           T planes (T the largest divisor of Lz not above k), z fastest
  *           within a slab, then t, then the slab, which brings the z
  *           neighbours closer in the block order.
- *   rhs_tile Dslash only: right-hand sides one work-item applies each link
- *           to (1, 2 or 4; FP64 at most 2), so links are loaded once per tile.
- *   rhs_group Dslash only: 0, or G in 2..16: with several right-hand-side
- *           tiles, G tiles run back to back on each spatial block, so the
- *           links loaded for the first are re-read from L2 by the others.
- *   ygroup  hop kernels with order = 1: 0 or 1 (none), or G in 2..64: G
- *           neighbouring chunks of x-rows along y run right after t (then z),
- *           so the rows a chunk's y-hops read beyond its edge come from L2;
- *           the largest divisor of the chunk count not above G is used.
- *   rhs_lanes Dslash with rhs_tile = 1 only: 0 or 1 (none), or 2, 4, 8, 16:
- *           the right-hand sides of a site run in that many adjacent lanes of
- *           one wavefront (the next power of two of nrhs, at most this), whose
- *           link loads are one request: each link comes from memory once per
- *           hop for all of them.  Needs order = 1 (blocks of whole x-rows of
- *           sites, block = the site budget times the lanes); where no row
- *           tile fits, the launch uses tiles in registers instead.
+ *   rhs_tile (1, 2 or 4), rhs_group (0, or 2..16), rhs_lanes (0, 1, 2, 4, 8 or
+ *           16): checked and kept, without effect: launches on several
+ *           right-hand sides put up to four of them in a block, which share
+ *           its links.
+ *   ygroup  hop kernels with order >= 1: 0 or 1 (none), or G in 2..64: G times
+ *           as many neighbouring blocks of an xy plane run right after t (then
+ *           z), so the rows a block's y-hops read beyond its edge come from L2;
+ *           the largest divisor of the plane's blocks not above that is used.
  * Process-wide; the defaults come from measurements on MI355X. */
 typedef struct {
     int32_t block;
@@ -292,7 +284,7 @@ LQCD_API int lqcd_tune_cache_get(int32_t kernel, int32_t prec, int32_t recon, co
                                  lqcd_launch* cfg, double* us, int32_t* found);
 
 /* Autotuner: time every Dslash launch configuration (block 64..256, XCD
- * remap on/off, memory or row-tile order) on this geometry with HIP events,
+ * remap on/off, memory or plane order) on this geometry with HIP events,
  * `reps` launches each after two warm-up launches, and install the fastest
  * as the process-wide setting for op->prec.  U, in, out are as for
  * dslash_eo_apply with op_kind = LQCD_OP_HOP, out_parity 0, nrhs 1 (in and out
@@ -301,12 +293,10 @@ LQCD_API int lqcd_tune_cache_get(int32_t kernel, int32_t prec, int32_t recon, co
 LQCD_API int lqcd_autotune_dslash(const lqcd_geom* geom, const lqcd_op* op, const void* U, const void* in, void* out,
                                   int32_t reps, void* stream, lqcd_launch* best, double* best_us);
 
-/* For several right-hand sides: with the XCD remap and block order of
- * LQCD_KERNEL_DSLASH_RHS at op->prec kept, times the even-odd hop on nrhs
- * (2..16) stacked parity fields for every block request (128, 192, 256),
- * right-hand-side tile compiled (1, 2, 4; FP64 1, 2) and group (0, 2, 4, 8,
- * 16), and tile 1 across 2, 4, 8, 16 lanes (up to the next power of two of
- * nrhs; with order >= 1), and installs the fastest as LQCD_KERNEL_DSLASH_RHS.
+/* For several right-hand sides: with the rest of LQCD_KERNEL_DSLASH_RHS at
+ * op->prec kept, times the even-odd hop on nrhs (2..16) stacked parity fields
+ * for every block request (128, 192, 256) and installs the fastest as
+ * LQCD_KERNEL_DSLASH_RHS.
  * best_us: mean time of one launch over all nrhs.  Synchronises stream. */
 LQCD_API int lqcd_autotune_dslash_rhs(const lqcd_geom* geom, const lqcd_op* op, const void* U, const void* in,
                                       void* out, int32_t nrhs, int32_t reps, void* stream, lqcd_launch* best,
@@ -397,8 +387,8 @@ LQCD_API int cg_solve_batch(int32_t nsys, const lqcd_geom* geoms, const lqcd_op*
  * CGNR that cg_solve_batch runs on exactly these systems (batched launches,
  * no graph) for each candidate launch shape of the inner hop family
  * (LQCD_KERNEL_DSLASH_RHS at params->inner_prec when params->nrhs > 1: block
- * requests 128, 192, 256 x right-hand-side tile 1 or 2 x tile groups 0..8;
- * LQCD_KERNEL_DSLASH when nrhs = 1: block x memory order / row tiles x XCD
+ * requests 128, 192, 256;
+ * LQCD_KERNEL_DSLASH when nrhs = 1: block x memory order / planes x XCD
  * remap), keeps the fastest in the process-wide table for later solves and
  * returns it in *best with the time of one iteration in *best_us (either may
  * be NULL).  Arguments as for cg_solve_batch (params->persistent must be 0);

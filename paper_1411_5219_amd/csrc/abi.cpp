@@ -133,19 +133,15 @@ SpinCoef coef_real(double v) { return {{v, 0.0}, {v, 0.0}}; }
 
 // Process-wide launch table: [kernel family][precision 64 / 32 / 16].
 std::mutex g_launch_mu;
-// Defaults measured on MI355X at 24^3x8 .. 64^3x16: whole x-rows per block
-// in t-fastest order with the XCD remap for the Dslash; plain 256-wide
-// blocks for the site-local kernels.
-// Several right-hand sides: FP64 and FP32 single right-hand sides per
-// work-item in groups of 4, FP16 tiles of 2 in groups of 4.
+// Defaults measured on MI355X at 24^3x8 .. 64^3x16: t-fastest order of chunks
+// of xy planes with the XCD remap for the Dslash, 256 neighbouring sites of a
+// plane in the order; plain 256-wide blocks for the site-local kernels.
 // The staggered hop (colour vectors of 48 / 24 / 16 bytes) gains less from
-// neighbour reuse: memory order in FP64, row tiles of 192 in FP32 and FP16.
+// neighbour reuse: memory order in FP64, 192 sites of a plane in FP32 and FP16.
 Launch g_launch[4][3] = {{{256, 1, 1, 1, 4}, {256, 1, 1, 1, 4}, {256, 1, 1, 2, 4}},
                          {{256, 0, 0, 1, 0}, {256, 0, 0, 1, 0}, {256, 0, 0, 1, 0}},
                          {{256, 1, 0, 1, 0}, {192, 1, 1, 1, 0}, {192, 1, 1, 1, 0}},
-                         // several right-hand sides (the autotuner for them also tries
-                         // 128- and 192-thread requests; no default beat these across
-                         // 24^3x8, 32^3x8 and 48^3x12 by more than the run-to-run spread)
+                         // several right-hand sides
                          {{256, 1, 1, 1, 4}, {256, 1, 1, 1, 4}, {256, 1, 1, 2, 4}}};
 
 int prec_slot(int prec) { return prec == 64 ? 0 : prec == 32 ? 1 : prec == 16 ? 2 : -1; }
@@ -389,10 +385,12 @@ struct Op {
     hipStream_t s = nullptr;
     RedScratch rs;
     Launch dcfg, bcfg;
+    int form = FORM_BY_SIZE;
 
     void tune()
     {
         dcfg = launch_for(nrhs > 1 ? LQCD_KERNEL_DSLASH_RHS : LQCD_KERNEL_DSLASH, prec, recon, g, nrhs);
+        dcfg.form = form;
         bcfg = launch_for(LQCD_KERNEL_BLAS, prec);
     }
 
@@ -868,6 +866,11 @@ int solver_finish(const Op& o, bool eo, char* bc, char* xc)
     return LQCD_OK;
 }
 
+// HopForm of a system's outer and inner hops (given for the systems of a batch).
+struct BatchForms {
+    int outer, inner;
+};
+
 // One CGNR system: plain FP64 (even-odd or full lattice) or mixed precision
 // with FP64 reliable updates (even-odd).  setup / start / iter / finish
 // enqueue the kernels of each phase, so one system can be driven on its own
@@ -885,7 +888,7 @@ struct CgSystem {
     void *t64 = nullptr, *xl = nullptr, *rl = nullptr, *pl = nullptr, *wl = nullptr, *zl = nullptr, *tl = nullptr;
 
     int init(const Geom& g, const lqcd_op* opi, const void* U, const void* b, void* x, const lqcd_solve_params* prm_,
-             const SolverPlan& plan, hipStream_t s)
+             const SolverPlan& plan, hipStream_t s, BatchForms forms = {FORM_BY_SIZE, FORM_BY_SIZE})
     {
         prm = prm_;
         sp = plan;
@@ -903,6 +906,7 @@ struct CgSystem {
         o.pb = parity_bytes(g, 64);
         o.s = s;
         o.rs = sp.rs;
+        o.form = forms.outer;
         o.tune();
         pb = o.pb;
         fb = 2 * pb;
@@ -923,6 +927,7 @@ struct CgSystem {
             lo.recon = prm->inner_recon;
             lo.U = sp.Ulo;
             lo.pb = parity_bytes(g, lo.prec);
+            lo.form = forms.inner;
             lo.tune();
             xl = sp.lo[0];
             rl = sp.lo[1];
@@ -1252,6 +1257,18 @@ int solve(int method, const lqcd_geom* geom, const lqcd_op* opi, const void* U, 
 
 constexpr size_t kStepTableBytes = 16 * 1024;  // per recorded step: arguments, offsets, finalizes of <= 16 systems
 constexpr int kMaxSteps = 32;
+// Form of the hops of a batch (outer FP64, inner prm->inner_prec): every system
+// of a step runs the same kernel, so the rule of a single launch is applied to
+// the systems together.  The persistent kernel runs tiles.
+BatchForms batch_forms(const std::vector<Geom>& g, const lqcd_op* ops, const lqcd_solve_params* prm)
+{
+    if (prm->persistent) return {FORM_TILE, FORM_TILE};
+    int recon = 18;
+    for (size_t i = 0; i < g.size(); ++i) recon = std::min(recon, (int)ops[i].recon);
+    const int want = FORM_BY_SIZE, n = (int)g.size();
+    return {hop_form(64, recon, prm->eo == 0, g.data(), n, prm->nrhs, want),
+            hop_form(prm->inner_prec, prm->inner_recon, prm->eo == 0, g.data(), n, prm->nrhs, want)};
+}
 static_assert(kMaxSteps <= kMaxPersistSteps, "the persistent program holds every recorded step");
 // Polls of a grid barrier slot before the persistent kernel gives up (each
 // poll sleeps ~30 ns and waits one device-coherent load: a few seconds,
@@ -1265,13 +1282,13 @@ int persist_routine(const std::vector<std::vector<Step>>& steps, size_t k)
     const Step& st = steps[0][k];
     for (const auto& sys : steps) {
         const Step& q = sys[k];
-        if (q.kind == STEP_DSLASH && (q.d.block.x > (unsigned)kPersistThreads || q.d.a.lanes != 1)) return PR_NONE;
+        if (q.kind == STEP_DSLASH && q.d.block.x > (unsigned)kPersistThreads) return PR_NONE;
         if (q.kind == STEP_BLAS && q.b.block.x != (unsigned)kPersistThreads) return PR_NONE;
         if (q.kind == STEP_CONVERT && q.c.block.x != (unsigned)kPersistThreads) return PR_NONE;
     }
     if (st.kind == STEP_DSLASH) {
         const DslashPlan& d = st.d;
-        if (d.kind != PLAN_WILSON || d.nr != 1 || d.lnt || (d.red != RED_NONE && d.red != RED_NORM)) return PR_NONE;
+        if (d.kind != PLAN_WILSON || d.split != 0 || (d.red != RED_NONE && d.red != RED_NORM)) return PR_NONE;
         const bool norm = d.red == RED_NORM;
         if (d.prec == 32 && d.recon == 12)
             return d.dag ? (norm ? PR_HOP32_12_D1_NORM : PR_HOP32_12_D1_NONE)
@@ -1322,7 +1339,7 @@ bool same_kernel(const Step& a, const Step& b)
 {
     if (a.kind != b.kind) return false;
     if (a.kind == STEP_DSLASH)
-        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.nr == b.d.nr &&
+        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split &&
                a.d.lnt == b.d.lnt && a.d.red == b.d.red &&
                a.d.dag == b.d.dag && a.d.a.nrhs == b.d.a.nrhs && a.d.grid.y == b.d.grid.y;
     if (a.kind == STEP_BLAS)
@@ -1491,9 +1508,10 @@ int solve_batch(int nsys, const lqcd_geom* geoms, const lqcd_op* ops, const void
     const int nrhs = prm->nrhs;
     const int chunk = prm->check_every > 0 ? prm->check_every : 8;
 
+    const BatchForms forms = batch_forms(g, ops, prm);
     std::vector<CgSystem> sys(nsys);
     for (int s = 0; s < nsys; ++s) {
-        if ((rc = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st))) return rc;
+        if ((rc = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st, forms))) return rc;
         if ((rc = sys[s].setup())) return rc;
     }
     // record one iteration per system and zip the recordings into batched launches
@@ -1645,13 +1663,9 @@ int autotune_batch(int nsys, const lqcd_geom* geoms, const lqcd_op* ops, const v
         if (nrhs > 1) {
             c.order = orig.order < 1 ? 1 : orig.order;
             c.swizzle = 1;
-            const int tg[7][2] = {{1, 0}, {1, 2}, {1, 4}, {1, 8}, {2, 0}, {2, 2}, {2, 4}};
-            for (const auto& t : tg) {
-                if (dslash_rhs_tile(prec, t[0], nrhs) != t[0] || t[0] * t[1] > 2 * nrhs) continue;
-                c.rhs_tile = t[0];
-                c.rhs_group = t[1];
-                cand.push_back(c);
-            }
+            c.rhs_tile = 1;
+            c.rhs_group = 4;
+            cand.push_back(c);
         } else {
             for (int order : {0, 1})
                 for (int swz : {0, 1}) {
@@ -1673,9 +1687,10 @@ int autotune_batch(int nsys, const lqcd_geom* geoms, const lqcd_op* ops, const v
     int result = LQCD_OK;
     for (const Launch& c : cand) {
         install(c);
+        const BatchForms forms = batch_forms(g, ops, prm);
         std::vector<CgSystem> sys(nsys);
         for (int s = 0; s < nsys && !result; ++s) {
-            if ((result = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st))) break;
+            if ((result = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st, forms))) break;
             result = sys[s].setup();
         }
         std::vector<Recorder> rec(nsys);
@@ -2341,46 +2356,30 @@ int lqcd_autotune_dslash_rhs(const lqcd_geom* geom, const lqcd_op* op, const voi
     float win_ms = 0.f;
     bool have = false;
     int result = LQCD_OK;
-    const int blocks[3] = {128, 192, 256};
-    const int tiles[3] = {1, 2, 4};
-    const int groups[5] = {0, 2, 4, 8, 16};
-    const int lanes[4] = {2, 4, 8, 16};
-    for (int bi = 0; bi < 3 && !result; ++bi) {
-        // tiles 1, 2, 4 in registers with groups, then tile 1 across 2..16 lanes
-        for (int ti = 0; ti < 3 + 4 && !result; ++ti) {
-            const bool across = ti >= 3;
-            const int tile = across ? 1 : tiles[ti];
-            if (!across && dslash_rhs_tile(op->prec, tile, nrhs) != tile) continue;  // not compiled / larger than nrhs
-            if (across && (shape.order < 1 || lanes[ti - 3] > 2 * nrhs)) continue;
-            for (int gi = 0; gi < (across ? 1 : 5) && !result; ++gi) {
-                Launch cfg = shape;
-                cfg.block = blocks[bi];
-                cfg.rhs_tile = tile;
-                cfg.rhs_group = across ? 0 : groups[gi];
-                cfg.rhs_lanes = across ? lanes[ti - 3] : 1;
-                o.dcfg = cfg;
-                auto hop = [&]() {
-                    return o.hop(0, in, out, false, SpinCoef{}, nullptr, coef_real(1.0), nullptr, RED_NONE, FIN_STORE,
-                                 PRED_ALWAYS);
-                };
-                hipError_t e = hipSuccess;
-                for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hop();
-                if (e == hipSuccess) e = hipEventRecord(e0, o.s);
-                for (int i = 0; i < reps && e == hipSuccess; ++i) e = hop();
-                if (e == hipSuccess) e = hipEventRecord(e1, o.s);
-                if (e == hipSuccess) e = hipEventSynchronize(e1);
-                float ms = 0.f;
-                if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-                if (e != hipSuccess) {
-                    result = set_error(LQCD_EHIP, "autotune: %s", hipGetErrorString(e));
-                    break;
-                }
-                if (!have || ms < win_ms) {
-                    have = true;
-                    win_ms = ms;
-                    win = cfg;
-                }
-            }
+    for (int blk : {128, 192, 256}) {
+        Launch cfg = shape;
+        cfg.block = blk;
+        o.dcfg = cfg;
+        auto hop = [&]() {
+            return o.hop(0, in, out, false, SpinCoef{}, nullptr, coef_real(1.0), nullptr, RED_NONE, FIN_STORE,
+                         PRED_ALWAYS);
+        };
+        hipError_t e = hipSuccess;
+        for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hop();
+        if (e == hipSuccess) e = hipEventRecord(e0, o.s);
+        for (int i = 0; i < reps && e == hipSuccess; ++i) e = hop();
+        if (e == hipSuccess) e = hipEventRecord(e1, o.s);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e != hipSuccess) {
+            result = set_error(LQCD_EHIP, "autotune: %s", hipGetErrorString(e));
+            break;
+        }
+        if (!have || ms < win_ms) {
+            have = true;
+            win_ms = ms;
+            win = cfg;
         }
     }
     (void)hipEventDestroy(e0);

@@ -1,0 +1,180 @@
+// The order in which the blocks of a hop launch walk the lattice (plain C++:
+// compiled into the library by hipcc and by a host compiler for its test).
+#pragma once
+
+#include <stdint.h>
+
+#if defined(__HIPCC__)
+#define LQCD_CHUNK_FN __host__ __device__ __forceinline__
+#else
+#define LQCD_CHUNK_FN inline
+#endif
+
+namespace lqcd {
+
+constexpr int kChunk = 64;  // sites of a chunk, one per lane of a wave
+
+// Division of 31-bit numbers by a launch constant: n / d = mulhi(n, m) >> s
+// with m = ceil(2^(31 + l) / d), l = ceil(log2 d), s = l - 1, exact for
+// n < 2^31 (m d - 2^(31 + l) < d <= 2^l); m = 0 stands for d = 1.
+struct FastDiv {
+    uint32_t d, m, s;
+};
+inline FastDiv make_fastdiv(uint32_t d)
+{
+    FastDiv f{d, 0, 0};
+    if (d <= 1) return f;
+    uint32_t l = 0;
+    while ((1ull << l) < d) ++l;
+    f.m = (uint32_t)(((1ull << (31 + l)) + d - 1) / d);
+    f.s = l - 1;
+    return f;
+}
+LQCD_CHUNK_FN uint32_t fdiv(const FastDiv& f, uint32_t n)
+{
+    return f.m ? (uint32_t)(((uint64_t)n * f.m) >> 32) >> f.s : n;
+}
+
+// Block order of a hop launch.  The sites of one parity are cut into layers of
+// `planes` consecutive xy planes and these into chunks of 64 consecutive sites
+// (the last chunk of a layer may be ragged); a block covers nsub consecutive
+// chunks, and the spatial blocks run z within a slab of ztile layers fastest,
+// then t, then `group` neighbouring blocks of the layer, then the slab, then
+// the next group: the t and z neighbours a block reads were loaded by blocks
+// that ran just before it on the same XCD, and with a group the rows just
+// outside its chunks too.  chunks = 0: chunks of the whole parity in memory
+// order.  Full-lattice launches alternate the parities of each spatial block.
+struct ChunkArgs {
+    int chunks;      // chunks per layer (0: memory order)
+    int planes;      // xy planes of a layer
+    int nsub;        // chunks per block
+    int nsp;         // spatial blocks per parity
+    int tile;        // right-hand sides per block
+    int nblk;        // blocks of one right-hand-side tile (tiles run one after the other)
+    FastDiv stride;  // hardware blocks of a tile: nblk, with several tiles rounded up to a multiple of 8
+    FastDiv Lxh, Ly, Lz, Lt, plane, group, slabs, ztile;
+};
+
+// Extents (x, y, z, t), sites per parity and sites per half x-row.
+struct ChunkGrid {
+    int L[4];
+    int Lxh, Vh;
+};
+
+// Plan for blocks of at most maxsub chunks of 64 sites.  order 0: memory
+// order; k >= 1: layers, in z-slabs of the largest divisor of the layers with at most
+// k planes; block and ygroup: the sites of a layer that are neighbours in the order
+// (block requests of work-items, one per site, times ygroup).
+inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int ygroup, int maxsub)
+{
+    ChunkArgs c = {};
+    const int plane = g.Lxh * g.L[1];
+    const int64_t flat = (g.Vh + kChunk - 1) / kChunk;
+    // One plane per layer where its last chunk leaves at most a twentieth of
+    // the lanes idle, else the fewest planes (a divisor of Lz up to 8) that do,
+    // or that leave the fewest idle: 20^3x8 has 200 sites per plane, 78% of four
+    // chunks, but 800 in four planes, 96% of 13 (FP64 Schur complement on four
+    // right-hand sides 66.7 us with one plane, 59.9 with four).
+    auto chunks_of = [&](int n) { return (plane * n + kChunk - 1) / kChunk; };
+    c.planes = 1;
+    for (int n = 1; n <= 8 && n <= g.L[2]; ++n) {
+        if (g.L[2] % n) continue;
+        const int64_t idle = (int64_t)chunks_of(n) * kChunk - (int64_t)plane * n;
+        const int64_t best = (int64_t)chunks_of(c.planes) * kChunk - (int64_t)plane * c.planes;
+        if (20 * best <= (int64_t)chunks_of(c.planes) * kChunk) break;
+        if (idle * chunks_of(c.planes) < best * chunks_of(n)) c.planes = n;
+    }
+    const int per = chunks_of(c.planes), layers = g.L[2] / c.planes;
+    // chunks of layers unless memory order is asked for; a lattice so wide and
+    // flat that its ragged layers would take more slots than the caller's
+    // partials hold (one per x-row or per 64 sites) runs in memory order too
+    const int64_t rows = (int64_t)g.L[1] * g.L[2] * g.L[3];
+    c.chunks = order == 0 || (int64_t)per * layers * g.L[3] > (rows > flat ? rows : flat) ? 0 : per;
+    c.nsub = 1;
+    int group = 1, ztile = 1;
+    if (c.chunks) {
+        // most chunks per block that fill every wave, or else waste at most a fifth of a layer's
+        for (int n = 2; n <= maxsub; ++n)
+            if (c.chunks % n == 0) c.nsub = n;
+        for (int n = 2; n <= maxsub && c.nsub == 1; ++n)
+            if (5 * c.chunks >= 4 * ((c.chunks + n - 1) / n) * n) c.nsub = n;
+        const int blocks = (c.chunks + c.nsub - 1) / c.nsub;
+        const int want = (block / kChunk + c.nsub - 1) / c.nsub * (ygroup > 1 ? ygroup : 1);
+        // a layer of several planes is one group: its z neighbours are its own
+        // chunks; a plane a little larger than the request is too
+        if (c.planes > 1 || 2 * blocks <= 3 * want) group = blocks;
+        else
+            for (int d = 1; d <= want; ++d)
+                if (blocks % d == 0) group = d;
+        for (int d = 1; d <= layers && d * c.planes <= order; ++d)
+            if (layers % d == 0) ztile = d;
+        c.nsp = blocks * layers * g.L[3];
+    } else {
+        c.nsub = maxsub;
+        c.nsp = (int)((flat + maxsub - 1) / maxsub);
+    }
+    c.Lxh = make_fastdiv((uint32_t)g.Lxh);
+    c.Ly = make_fastdiv((uint32_t)g.L[1]);
+    c.Lz = make_fastdiv((uint32_t)g.L[2]);
+    c.Lt = make_fastdiv((uint32_t)g.L[3]);
+    c.plane = make_fastdiv((uint32_t)plane);
+    c.group = make_fastdiv((uint32_t)group);
+    c.slabs = make_fastdiv((uint32_t)(layers / ztile));
+    c.ztile = make_fastdiv((uint32_t)ztile);
+    return c;
+}
+
+struct SitePos {
+    int h;            // parity-local index of the output site
+    int xh, x, y, z, t;
+    bool valid;       // false for lanes past the end, which repeat the last site
+    bool some;        // some lane of the wave is valid (uniform)
+};
+
+// Site of lane `lane` of parity p in chunk `sub` of spatial block b.
+// Divisions are by launch constants (FastDiv), and t is uniform over the
+// wave unless the chunks run in memory order, and so is z with one plane per
+// layer.
+LQCD_CHUNK_FN SitePos chunk_site(const ChunkArgs& c, int Lxh, int Ly, int Lz, int Vh, uint32_t b, int sub, int p,
+                                 int lane)
+{
+    SitePos s;
+    if (c.chunks == 0) {
+        const int first = ((int)b * c.nsub + sub) * kChunk;
+        s.some = first < Vh;
+        s.valid = first + lane < Vh;
+        s.h = first + lane < Vh ? first + lane : Vh - 1;
+        const uint32_t r = fdiv(c.Lxh, (uint32_t)s.h);
+        s.xh = s.h - (int)r * Lxh;
+        const uint32_t q = fdiv(c.Ly, r);
+        s.y = (int)r - (int)q * Ly;
+        s.t = (int)fdiv(c.Lz, q);
+        s.z = (int)q - s.t * Lz;
+    } else {
+        uint32_t q = fdiv(c.ztile, b);
+        const int zl = (int)(b - q * c.ztile.d);
+        b = fdiv(c.Lt, q);
+        s.t = (int)(q - b * c.Lt.d);
+        q = fdiv(c.group, b);
+        const int gi = (int)(b - q * c.group.d);
+        b = fdiv(c.slabs, q);
+        s.z = ((int)((q - b * c.slabs.d) * c.ztile.d) + zl) * c.planes;
+        const int plane = Lxh * Ly, sites = plane * c.planes;
+        const int first = (((int)(b * c.group.d) + gi) * c.nsub + sub) * kChunk;
+        s.some = first < sites;
+        s.valid = first + lane < sites;
+        int i = first + lane < sites ? first + lane : sites - 1;
+        s.h = i + plane * (s.z + Lz * s.t);
+        if (c.planes > 1) {
+            const int dz = (int)fdiv(c.plane, (uint32_t)i);
+            s.z += dz;
+            i -= dz * plane;
+        }
+        s.y = (int)fdiv(c.Lxh, (uint32_t)i);
+        s.xh = i - s.y * Lxh;
+    }
+    s.x = 2 * s.xh + ((s.y + s.z + s.t + p) & 1);
+    return s;
+}
+
+}  // namespace lqcd

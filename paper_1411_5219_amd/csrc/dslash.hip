@@ -6,16 +6,25 @@
 
 namespace lqcd {
 
-hipError_t launch_dslash_64(int recon, int nr, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
-                            hipStream_t s);
-hipError_t launch_dslash_32(int recon, int nr, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
-                            hipStream_t s);
-hipError_t launch_dslash_16(int recon, int nr, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
-                            hipStream_t s);
+// Right-hand sides of a block (the kernel's bound).  Their spinors share the
+// XCD's L2: 32^3x8 FP32/12 Schur on 12 right-hand sides 207 us with 4 per
+// block, 218 with 3, 245 with 2; 8 per block read more from beyond L2 (296).
+constexpr int kMaxTile = 4;
+
+hipError_t launch_dslash_64(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
+                            dim3 block, hipStream_t s);
+hipError_t launch_dslash_32(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
+                            dim3 block, hipStream_t s);
+hipError_t launch_dslash_16(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
+                            dim3 block, hipStream_t s);
 
 hipError_t launch_stag_64(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 hipError_t launch_stag_32(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 hipError_t launch_stag_16(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
+
+hipError_t launch_rhs_64(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_rhs_32(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_rhs_16(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 
 static hipError_t launch_dslash_prec(const DslashPlan& p, const DslashLaunch& L, dim3 grid, hipStream_t s)
 {
@@ -25,136 +34,117 @@ static hipError_t launch_dslash_prec(const DslashPlan& p, const DslashLaunch& L,
         if (p.prec == 16) return launch_stag_16(p.recon, p.red, p.lnt, L, grid, p.block, s);
         return hipErrorInvalidValue;
     }
-    if (p.prec == 64) return launch_dslash_64(p.recon, p.nr, p.lnt, p.dag, p.red, L, grid, p.block, s);
-    if (p.prec == 32) return launch_dslash_32(p.recon, p.nr, p.lnt, p.dag, p.red, L, grid, p.block, s);
-    if (p.prec == 16) return launch_dslash_16(p.recon, p.nr, p.lnt, p.dag, p.red, L, grid, p.block, s);
+    if (p.split == 0) {
+        if (p.prec == 64) return launch_rhs_64(p.recon, p.dag, p.red, L, grid, p.block, s);
+        if (p.prec == 32) return launch_rhs_32(p.recon, p.dag, p.red, L, grid, p.block, s);
+        if (p.prec == 16) return launch_rhs_16(p.recon, p.dag, p.red, L, grid, p.block, s);
+        return hipErrorInvalidValue;
+    }
+    if (p.prec == 64) return launch_dslash_64(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
+    if (p.prec == 32) return launch_dslash_32(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
+    if (p.prec == 16) return launch_dslash_16(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
     return hipErrorInvalidValue;
 }
 
-int dslash_rhs_tile(int prec, int want, int nrhs)
+static ChunkGrid chunk_grid(const Geom& g) { return ChunkGrid{{g.L[0], g.L[1], g.L[2], g.L[3]}, g.Lxh, g.Vh}; }
+
+// Block order and grid of a launch whose blocks cover at most maxsub chunks
+// of 64 sites each, for `tile` right-hand sides per block.
+static void plan_chunks(const Launch& cfg, int maxsub, int tile, int nrhs, DslashPlan* p)
 {
-    int nr = want < 1 ? 1 : want;
-    if (prec == 64 && nr > 2) nr = 2;
-    if (nr > 4) nr = 4;
-    if (nr == 3) nr = 2;
-    while (nr > 1 && nr > nrhs) nr >>= 1;
-    return nr;
+    DslashArgs& a = p->a;
+    a.swizzle = cfg.swizzle;
+    a.nrhs = nrhs;
+    a.ch = plan_chunk_order(chunk_grid(a.g), cfg.order, cfg.block, cfg.ygroup, maxsub);
+    a.ch.tile = tile;
+    p->slots = a.ch.nsp * (a.full ? 2 : 1);
+    a.ch.nblk = p->slots;
+    const int ntiles = (nrhs + tile - 1) / tile;
+    const unsigned stride = ntiles > 1 ? (p->slots + 7) / 8 * 8 : p->slots;
+    a.ch.stride = make_fastdiv(stride);
+    p->grid = dim3(stride * (unsigned)ntiles);
+    a.gx = (int)p->grid.x;
+}
+
+static hipError_t finish_plan(int red, DslashPlan* p)
+{
+    if (red != RED_NONE && p->slots > p->a.r.capacity) return hipErrorInvalidValue;  // partials too small
+    p->nfin = red == RED_NONE ? 0 : red == RED_NORM ? 1 : red == RED_DOT_AUX ? 2 : 3;
+    return hipSuccess;
+}
+
+static bool storage_built(int prec, int recon)
+{
+    return (prec == 64 && (recon == 18 || recon == 12)) || (prec == 32 && (recon == 18 || recon == 12)) ||
+           (prec == 16 && recon == 12);
+}
+
+// Which waves serve a launch's sites and right-hand sides, for the n systems
+// of a batch together.
+// One right-hand side: a pair of waves per chunk (see dslash_block) except
+// where one wave per chunk fills every wave slot of the chip, two per SIMD at
+// its register count, planes split evenly into blocks of such waves, and each
+// link is read once and whole: there FP64/18, which streams at the memory's
+// rate either way, loses by the second wave's indices and the exchange
+// (48^3x12 186 us with one wave, 193 with two; 32^3x8, exactly full, 36.5 and
+// 38.2; 24^3x8, half full, 20.2 and 18.5; 40^3x6, uneven, 66 and 59; FP64/12
+// 48^3x8 103 and 99).
+// Several: a tile of them per block (hop_rhs.h) once the pairs of all of them
+// would no longer run at once, three waves per SIMD; below that the pairs are
+// faster, each on its own right-hand side (Schur complement, FP32/12: 8^3x4
+// with four 9.8 us against 13.3, 16^3x8 with four 15.0 against 16.8, with
+// twelve 33.1 against 29.7; FP64/18 20^3x8 with two 35.3 against 46.5), and
+// with two or three in FP16 storage, whose tiles wait for LDS (48^3x12 with
+// two 135 against 147, 28^3x8 with three 34.0 against 36.4, with four 41.0
+// against 40.6).
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want)
+{
+    if (want != FORM_BY_SIZE) return want;
+    int64_t chunks = 0;
+    bool even = true;
+    for (int i = 0; i < n; ++i) {
+        const ChunkArgs c = plan_chunk_order(chunk_grid(g[i]), 1, 256, 1, 4);
+        chunks += (g[i].Vh + kChunk - 1) / kChunk;
+        even = even && c.planes == 1 && c.nsub > 1 && c.chunks % c.nsub == 0;
+    }
+    if (nrhs > 1) return 2 * chunks * nrhs <= 3 * kSimds || (prec == 16 && nrhs <= 3) ? FORM_PAIR : FORM_TILE;
+    return prec == 64 && recon == 18 && !full && even && chunks >= 2 * kSimds ? FORM_WAVE : FORM_PAIR;
 }
 
 hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
                        DslashPlan* out)
 {
-    if (!((prec == 64 && (recon == 18 || recon == 12)) || (prec == 32 && (recon == 18 || recon == 12)) ||
-          (prec == 16 && recon == 12)))
-        return hipErrorInvalidValue;
+    if (!storage_built(prec, recon)) return hipErrorInvalidValue;
     DslashPlan& p = *out;
     p.kind = PLAN_WILSON;
     p.prec = prec;
     p.recon = recon;
     p.dag = dagger;
     p.red = red;
-    DslashArgs& a = p.a;
-    a = args;
-    a.swizzle = cfg.swizzle;
-    a.nrhs = nrhs;
-    // right-hand sides across lanes: L = the next power of two of nrhs, at
-    // most the request and 16; every field's lane offsets must fit 31 bits
-    int L = 1;
-    if (nrhs > 1 && cfg.rhs_lanes > 1 && cfg.rhs_tile == 1) {
-        while (L < nrhs && 2 * L <= cfg.rhs_lanes && L < 16) L *= 2;
-        int64_t st = a.st_in;
-        for (int64_t v : {a.st_out, a.st_site, a.st_add, a.st_aux}) st = v > st ? v : st;
-        if ((int64_t)L * st >= ((int64_t)1 << 31)) L = 1;
-    }
-    int blk = cfg.block;
-    unsigned nbh = (unsigned)((a.g.Vh + blk - 1) / blk);
-    a.rows = 0;
-    a.nyc = 0;
-    a.ztile = 1;
-    a.ygroup = 1;
-    const int Lxh = a.g.Lxh, Ly = a.g.L[1];
-    if (L > 1) {
-        // whole x-rows per block only (the block order and the partials
-        // count of the row tiles): the largest divisor R of Ly with R rows
-        // within the site budget cfg.block / L (at least one row) and
-        // R * Lxh * L lanes within the block limit, where 3/4 of the lanes
-        // are busy; otherwise tiles in registers (L = 1)
-        const int tmax = hop_lane_block_limit(prec);
-        const int sites = cfg.block / L;
-        int R = 0;
-        if (cfg.order >= 1)
-            for (int d = 1; d <= Ly; ++d)
-                if (Ly % d == 0 && (d * Lxh <= sites || d == 1) && d * Lxh * L <= tmax) R = d;
-        const int B = (R * Lxh * L + 63) / 64 * 64;
-        if (R > 0 && B <= tmax && 4 * R * Lxh * L >= 3 * B) {
-            a.rows = R;
-            a.nyc = (Ly + R - 1) / R;
-            for (int d = 1; d <= a.g.L[2] && d <= cfg.order; ++d)
-                if (a.g.L[2] % d == 0) a.ztile = d;
-            if (a.ztile == 1)
-                for (int d = 1; d <= a.nyc && d <= cfg.ygroup; ++d)
-                    if (a.nyc % d == 0) a.ygroup = d;
-            blk = R * Lxh;
-            nbh = (unsigned)a.nyc * a.g.L[2] * a.g.L[3];
-        } else {
-            L = 1;
-        }
-    }
-    a.lanes = L;
-    a.lanes_log2 = 0;
-    while ((1 << a.lanes_log2) < L) ++a.lanes_log2;
-    if (L == 1 && cfg.order >= 1 && Lxh <= 256) {
-        // R whole x-rows per block: the largest divisor of Ly with R*Lxh at
-        // most the requested block size (at least one row); the block is
-        // rounded up to whole wavefronts.
-        int R = 1;
-        for (int d = 1; d <= Ly; ++d)
-            if (Ly % d == 0 && d * Lxh <= cfg.block) R = d;
-        int B = (R * Lxh + 63) / 64 * 64;
-        if (B > 256) {  // one row per block: keep the block within the kernel's bound
-            R = 1;
-            B = (Lxh + 63) / 64 * 64;
-        }
-        // row tiles only where they keep at least 3/4 of the lanes busy
-        if (4 * R * Lxh >= 3 * B) {
-            a.rows = R;
-            a.nyc = (Ly + R - 1) / R;
-            // z-slabs: the largest divisor of Lz not above the requested depth
-            for (int d = 1; d <= a.g.L[2] && d <= cfg.order; ++d)
-                if (a.g.L[2] % d == 0) a.ztile = d;
-            // y-chunk groups (t-fastest order only): the largest divisor of
-            // the chunk count not above the request
-            if (a.ztile == 1)
-                for (int d = 1; d <= a.nyc && d <= cfg.ygroup; ++d)
-                    if (a.nyc % d == 0) a.ygroup = d;
-            blk = B;
-            nbh = (unsigned)a.nyc * a.g.L[2] * a.g.L[3];
-        }
-    }
-    a.bdim = blk;
-    p.nr = L > 1 ? 1 : dslash_rhs_tile(prec, cfg.rhs_tile, nrhs);
-    a.ntiles = (nrhs + p.nr * L - 1) / (p.nr * L);
-    // links are streamed past the caches when no other block of the launch
-    // reads them (one right-hand side per site); with right-hand sides across
-    // lanes the L lanes of a site share one cached load
-    p.lnt = p.nr == 1 && a.ntiles == 1 && L == 1;
-    a.nsp = (int)nbh;
-    // interleave right-hand-side tiles into the block order when there are several
-    a.rhs_group = (L == 1 && cfg.rhs_group > 1 && a.ntiles > 1) ? (cfg.rhs_group < a.ntiles ? cfg.rhs_group : a.ntiles)
-                                                                 : 0;
-    p.block = dim3(L > 1 ? (unsigned)((blk * L + 63) / 64 * 64) : (unsigned)blk);
-    if (a.rhs_group > 0) {
-        const unsigned groups = (unsigned)((a.ntiles + a.rhs_group - 1) / a.rhs_group);
-        p.grid = dim3(nbh * (unsigned)a.rhs_group * groups * (a.full ? 2u : 1u), 1);
+    p.a = args;
+    const int form = hop_form(prec, recon, args.full != 0, &args.g, 1, nrhs, cfg.form);
+    if (form == FORM_TILE) {
+        // Several right-hand sides share a block and the links in its LDS:
+        // as few tiles of at most kMaxTile as there can be, of even sizes
+        const int ntiles = (nrhs + kMaxTile - 1) / kMaxTile, tile = (nrhs + ntiles - 1) / ntiles;
+        Launch c = cfg;
+        // half the group of blocks where a block's spinors are twice as large
+        // or both parities share the L2 (32^3x8, 4 right-hand sides: FP64
+        // Schur 198 us against 204, FP64 full 173 against 203, FP32/18 full 61
+        // against 75; FP32 Schur, 12 right-hand sides, is faster in groups of
+        // 4: 207 us against 213)
+        if (prec == 64 || args.full) c.block = cfg.block / 2;
+        plan_chunks(c, 1, tile, nrhs, &p);
+        p.split = 0;
+        p.lnt = false;
+        p.block = dim3((unsigned)(kChunk * tile));
     } else {
-        p.grid = dim3(nbh * (a.full ? 2u : 1u), (unsigned)a.ntiles);
+        p.lnt = nrhs == 1 && !args.full;
+        p.split = form == FORM_WAVE ? 1 : 2;
+        plan_chunks(cfg, p.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
+        p.block = dim3((unsigned)(kChunk * (p.split == 2 ? 2 : p.a.ch.nsub)));
     }
-    a.gx = (int)p.grid.x;
-    // partials hold one slot per spatial block and parity for each right-hand side
-    p.slots = (int)nbh * (a.full ? 2 : 1);
-    if (red != RED_NONE && p.slots > a.r.capacity) return hipErrorInvalidValue;  // partials too small
-    p.nfin = red == RED_NONE ? 0 : red == RED_NORM ? 1 : red == RED_DOT_AUX ? 2 : 3;
-    return hipSuccess;
+    return finish_plan(red, &p);
 }
 
 hipError_t exec_dslash(const DslashPlan& p, hipStream_t s)
@@ -206,15 +196,20 @@ hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int
                        hipStream_t s)
 {
     if (red != RED_NONE && red != RED_NORM && red != RED_NORM_DS) return hipErrorInvalidValue;
-    Launch c = cfg;
-    c.rhs_tile = 1;   // one right-hand side per work-item, tiles along grid.y
-    c.rhs_group = 0;
-    c.rhs_lanes = 1;
+    if (!storage_built(prec, recon)) return hipErrorInvalidValue;
     DslashPlan p;
-    hipError_t e = plan_dslash(prec, recon, false, red, args, nrhs, c, &p);
-    if (e != hipSuccess) return e;
     p.kind = PLAN_STAG;
-    p.nfin = red == RED_NONE ? 0 : red == RED_NORM ? 1 : 3;
+    p.prec = prec;
+    p.recon = recon;
+    p.dag = false;
+    p.red = red;
+    p.a = args;
+    p.split = 1;
+    p.lnt = nrhs == 1 && !args.full;
+    plan_chunks(cfg, cfg.block / kChunk, 1, nrhs, &p);
+    p.block = dim3((unsigned)(kChunk * p.a.ch.nsub));
+    const hipError_t e = finish_plan(red, &p);
+    if (e != hipSuccess) return e;
     if (Recorder* r = active_recorder()) {
         r->steps.push_back(Step{});
         r->steps.back().kind = STEP_DSLASH;

@@ -1,14 +1,22 @@
 // Even-odd Wilson / twisted-mass Dslash for gfx950 (kernel templates; each
 // storage precision is instantiated in its own translation unit).
 //
-// One work-item per output site of parity p.  For each of the 8 hops it
-// loads the neighbour spinor of parity 1-p, projects it to a 2x3 half
-// spinor with (1 -+ gamma_mu), multiplies by the link (or its adjoint),
-// applies the boundary phase on hops that cross the boundary, and rebuilds
-// the lower spin components from the upper ones.  The site-diagonal
-// twisted-mass terms are fused into the store (out = add + a*site + c*hop)
-// together with FP64 reductions, so a Schur-complement application or a
-// residual never needs a separate vector pass.
+// For each of the 8 hops of an output site of parity p the neighbour spinor
+// of parity 1-p is loaded, projected to a 2x3 half spinor with (1 -+ gamma_mu),
+// multiplied by the link (or its adjoint) and by the boundary phase on hops
+// that cross the boundary, and the lower spin components are rebuilt from the
+// upper ones.  A wave holds 64 sites, one per lane; one or two waves share the
+// hops of its sites.  The site-diagonal twisted-mass terms are fused into the
+// store (out = add + a*site + c*hop) together with FP64 reductions, so a
+// Schur-complement application or a residual never needs a separate vector
+// pass.
+//
+// Bounds: FP64 and FP32 on large lattices by memory (48^3x12 FP64/18 186 us,
+// FP32/12 75.5 us), FP16 storage by memory and VALU issue together (33.9 us;
+// 39.7 with operands converted before use), small lattices by launch and
+// latency.  Both parities in one launch are bound by memory too, with each
+// link read once: 48^3x12 FP64/18 386 -> 330 us against two parities one after
+// the other.
 //
 // In the chiral basis gamma_mu = [[0, B_mu], [B_mu^+, 0]] with
 //   B_x = -i sigma_1, B_y = -i sigma_2, B_z = -i sigma_3, B_t = 1,
@@ -21,6 +29,8 @@
 #include "lqcd_device.h"
 #include "lqcd_fin.h"
 #include "lqcd_kernels.h"
+
+#include <type_traits>
 
 namespace lqcd {
 
@@ -79,187 +89,271 @@ __device__ __forceinline__ void phase_mul(cplx<R> (&w)[2][3], cplx<R> ph)
         for (int a = 0; a < 3; ++a) w[s][a] = ph * w[s][a];
 }
 
-// Operands of one hop for a tile of NR right-hand sides: the link (loaded
-// once for the tile) and the neighbour spinor of each right-hand side.
-template <int PREC, int NR>
-struct HopBuf {
-    Link<typename SpinorIO<PREC>::R> L;
-    Spinor<typename SpinorIO<PREC>::R> p[NR];
+// A launch constant in scalar registers at precision R (converted in vector
+// registers it would stay there across the whole kernel).
+template <class R>
+__device__ __forceinline__ cplx<R> uniform(const double (&v)[2])
+{
+    if constexpr (sizeof(R) == 8) return {v[0], v[1]};
+    else
+        return {__builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)v[0]))),
+                __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, (float)v[1])))};
+}
+
+// ---------------------------------------------------------------------------
+// Operands of one hop as they are loaded.
+//
+// FP64 and FP32 storage: the neighbour spinor and the link as numbers.
+// FP16 storage: the words themselves, 19 registers instead of 42 for the
+// loads in flight, and used as half operands of mixed-precision fused
+// multiply-adds: the projection of the unscaled halves u -+ B l is one
+// instruction per real (it is exact up to one FP32 rounding), the link
+// product takes its matrix elements as halves, and the site's scale is the
+// factor of the accumulation's fused multiply-adds.  The kernel is bound by
+// its VALU issue (a wave instruction takes four cycles of a SIMD): converting
+// and scaling each operand first takes 24 + 12 instructions more per hop.
+
+template <int PREC>
+struct Nbs {
+    using R = typename SpinorIO<PREC>::R;
+    Spinor<R> v;
+    __device__ __forceinline__ void load(const void* in, int64_t S, int site) { SpinorIO<PREC>::load(in, S, site, v); }
+    template <int MU, int SIG>
+    __device__ __forceinline__ void half(cplx<R> (&h)[2][3]) const
+    {
+        project<R, MU, SIG>(v, h);
+    }
+    template <int MU, int SIG>
+    __device__ __forceinline__ void add(Spinor<R>& acc, const cplx<R> (&w)[2][3]) const
+    {
+        accumulate<R, MU, SIG>(acc, w);
+    }
 };
 
-// LNT selects the streaming (non-temporal) cache policy for the link loads,
-// for launches in which no other block reads the same links.  A tile of one
-// right-hand side is active whenever its block runs, so NR = 1 carries no
-// per-hop branch that would keep the loads of consecutive hops apart.
-template <int PREC, int RECON, int NR, bool LNT>
-__device__ __forceinline__ void hop_load(const char* const (&in)[NR], const bool (&act)[NR], const void* U,
-                                         int64_t S, const Nbr& n, HopBuf<PREC, NR>& b, uint32_t xo, int64_t span)
+__device__ __forceinline__ float half_lo(uint32_t w) { return (float)__builtin_bit_cast(_Float16, (unsigned short)w); }
+__device__ __forceinline__ float half_hi(uint32_t w)
 {
-    if constexpr (LNT) LinkIO<PREC, RECON>::template load<>(U, S, n.lblk, n.lsite, b.L);
-    else LinkIO<PREC, RECON>::template load<0>(U, S, n.lblk, n.lsite, b.L);
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        if (NR > 1 && !act[r]) continue;
-        SpinorIO<PREC>::load(in[r], S, n.nb, b.p[r], xo, span);
-    }
+    return (float)__builtin_bit_cast(_Float16, (unsigned short)(w >> 16));
 }
 
-template <int PREC, int MU, bool FWD, int SIG, int NR>
-__device__ __forceinline__ void hop_apply(const HopBuf<PREC, NR>& b, const bool (&act)[NR], bool cross,
-                                          cplx<typename SpinorIO<PREC>::R> ph,
-                                          Spinor<typename SpinorIO<PREC>::R> (&acc)[NR])
-{
-    using R = typename SpinorIO<PREC>::R;
+template <>
+struct Nbs<16> {
+    uint32_t w[12];  // complex component k: real in the low half, imaginary in the high half
+    float scale;
+    __device__ __forceinline__ void load(const void* in, int64_t S, int site)
+    {
+        const rsrc_t r = make_rsrc(in, 52 * S);
+        scale = bload<float>(r, static_cast<uint32_t>(site) * 4u, (uint32_t)(3 * S * 16));
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        if (NR > 1 && !act[r]) continue;
-        cplx<R> h[2][3];
-        project<R, MU, SIG>(b.p[r], h);
-        cplx<R> w[2][3];
-        link_mul<R, !FWD>(b.L, h, w);
-        if (cross) phase_mul(w, FWD ? ph : conj(ph));
-        accumulate<R, MU, SIG>(acc[r], w);
+        for (int k = 0; k < 3; ++k) {
+            const uint4 d = bload<uint4>(r, static_cast<uint32_t>(site) * 16u, (uint32_t)(k * S * 16));
+            w[4 * k] = d.x;
+            w[4 * k + 1] = d.y;
+            w[4 * k + 2] = d.z;
+            w[4 * k + 3] = d.w;
+        }
     }
-}
+    // (u - SIG * B_MU l) / scale
+    template <int MU, int SIG>
+    __device__ __forceinline__ void half(cplx<float> (&h)[2][3]) const
+    {
+        // one: 1 in a scalar register that the compiler does not know, so that u + l stays a fused multiply-add
+        // of halves instead of two conversions and an addition
+        float one = 1.0f;
+        asm("" : "+s"(one));
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const uint32_t u0 = w[c], u1 = w[3 + c], l0 = w[6 + c], l1 = w[9 + c];
+            const uint32_t b0 = MU < 2 ? l1 : l0, b1 = MU < 2 ? l0 : l1;
+            // sign of b in h, and B's factor: -i, (-1 | +1), (-i | +i), 1
+            constexpr float g = SIG > 0 ? -1.f : 1.f;
+            if (MU == 0 || MU == 2) {
+                constexpr float g1 = MU == 0 ? g : -g;
+                h[0][c] = {fmar(half_lo(u0), one, g * half_hi(b0)), fmar(half_hi(u0), one, -g * half_lo(b0))};
+                h[1][c] = {fmar(half_lo(u1), one, g1 * half_hi(b1)), fmar(half_hi(u1), one, -g1 * half_lo(b1))};
+            } else {
+                constexpr float g0 = MU == 1 ? -g : g;
+                h[0][c] = {fmar(half_lo(u0), one, g0 * half_lo(b0)), fmar(half_hi(u0), one, g0 * half_hi(b0))};
+                h[1][c] = {fmar(half_lo(u1), one, g * half_lo(b1)), fmar(half_hi(u1), one, g * half_hi(b1))};
+            }
+        }
+    }
+    // acc += scale * (w ; -SIG * B_MU^+ w)
+    template <int MU, int SIG>
+    __device__ __forceinline__ void add(Spinor<float>& acc, const cplx<float> (&v)[2][3]) const
+    {
+        auto fma2 = [&](cplx<float>& a, cplx<float> b) { a = {fmar(scale, b.x, a.x), fmar(scale, b.y, a.y)}; };
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const cplx<float> w0 = v[0][c], w1 = v[1][c];
+            cplx<float> d0, d1;  // B^+ w
+            if (MU == 0) { d0 = ti(w1); d1 = ti(w0); }
+            else if (MU == 1) { d0 = w1; d1 = -w0; }
+            else if (MU == 2) { d0 = ti(w0); d1 = mti(w1); }
+            else { d0 = w0; d1 = w1; }
+            fma2(acc.s[0][c], w0);
+            fma2(acc.s[1][c], w1);
+            fma2(acc.s[2][c], SIG > 0 ? -d0 : d0);
+            fma2(acc.s[3][c], SIG > 0 ? -d1 : d1);
+        }
+    }
+};
 
-// One hop applied right after its loads (pipeline depth 1).  With one
-// right-hand side the neighbour spinor is loaded and projected to its half
-// spinor before the link is loaded, so the full spinor and the link are not
-// live together; a tile of several right-hand sides loads the link first and
-// then each neighbour spinor in turn.
-template <int PREC, int RECON, int MU, bool FWD, int SIG, int NR, bool LNT>
-__device__ __forceinline__ void hop_fused(const char* const (&in)[NR], const bool (&act)[NR], const void* U,
-                                          int64_t S, const Nbr& n, cplx<typename SpinorIO<PREC>::R> ph,
-                                          Spinor<typename SpinorIO<PREC>::R> (&acc)[NR], uint32_t xo, int64_t span)
-{
+template <int PREC, int RECON>
+struct Lnk {
     using R = typename SpinorIO<PREC>::R;
-    if constexpr (NR == 1) {
-        Spinor<R> p;
-        SpinorIO<PREC>::load(in[0], S, n.nb, p, xo, span);
-        cplx<R> h[2][3];
-        project<R, MU, SIG>(p, h);
-        Link<R> L;
-        if constexpr (LNT) LinkIO<PREC, RECON>::template load<>(U, S, n.lblk, n.lsite, L);
-        else LinkIO<PREC, RECON>::template load<0>(U, S, n.lblk, n.lsite, L);
-        cplx<R> w[2][3];
-        link_mul<R, !FWD>(L, h, w);
-        if (n.cross) phase_mul(w, FWD ? ph : conj(ph));
-        accumulate<R, MU, SIG>(acc[0], w);
-        return;
+    Link<R> u;
+    template <bool LNT>
+    __device__ __forceinline__ void load(const void* U, int64_t S, int blk, int site)
+    {
+        if constexpr (LNT) LinkIO<PREC, RECON>::template load<>(U, S, blk, site, u);
+        else LinkIO<PREC, RECON>::template load<0>(U, S, blk, site, u);
     }
-    Link<R> L;
-    if constexpr (LNT) LinkIO<PREC, RECON>::template load<>(U, S, n.lblk, n.lsite, L);
-    else LinkIO<PREC, RECON>::template load<0>(U, S, n.lblk, n.lsite, L);
+    template <bool ADJ>
+    __device__ __forceinline__ void mul(const cplx<R> (&h)[2][3], cplx<R> (&w)[2][3]) const
+    {
+        link_mul<R, ADJ>(u, h, w);
+    }
+};
+
+template <>
+struct Lnk<16, 12> {
+    uint32_t w[6];  // rows 0 and 1
+    template <bool LNT>
+    __device__ __forceinline__ void load(const void* U, int64_t S, int blk, int site)
+    {
+        const rsrc_t r = make_rsrc(static_cast<const char*>(U) + blk * 24 * S, 24 * S);
+        const uint4 d = bload<uint4, LQCD_LINK16_AUX>(r, static_cast<uint32_t>(site) * 16u, 0u);
+        const uint2 e = bload<uint2, LQCD_LINK16_AUX>(r, static_cast<uint32_t>(site) * 8u, (uint32_t)(16 * S));
+        w[0] = d.x;
+        w[1] = d.y;
+        w[2] = d.z;
+        w[3] = d.w;
+        w[4] = e.x;
+        w[5] = e.y;
+    }
+    __device__ __forceinline__ float lo(int k) const { return half_lo(w[k]); }
+    __device__ __forceinline__ float hi(int k) const { return half_hi(w[k]); }
+    // third row: conj(a b - c d) of row-0 and row-1 entries
+    __device__ __forceinline__ void third(cplx<float> (&t)[3]) const
+    {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        if (NR > 1 && !act[r]) continue;
-        Spinor<R> p;
-        SpinorIO<PREC>::load(in[r], S, n.nb, p, xo, span);
-        cplx<R> h[2][3];
-        project<R, MU, SIG>(p, h);
-        cplx<R> w[2][3];
-        link_mul<R, !FWD>(L, h, w);
-        if (n.cross) phase_mul(w, FWD ? ph : conj(ph));
-        accumulate<R, MU, SIG>(acc[r], w);
+        for (int j = 0; j < 3; ++j) {
+            const int a = (j + 1) % 3, b = 3 + (j + 2) % 3, c = (j + 2) % 3, d = 3 + (j + 1) % 3;
+            float re = fmar(lo(a), lo(b), 0.f), im = fmar(-lo(a), hi(b), 0.f);
+            re = fmar(-hi(a), hi(b), re);
+            im = fmar(-hi(a), lo(b), im);
+            re = fmar(-lo(c), lo(d), re);
+            im = fmar(lo(c), hi(d), im);
+            re = fmar(hi(c), hi(d), re);
+            im = fmar(hi(c), lo(d), im);
+            t[j] = {re, im};
+        }
     }
-}
+    template <bool ADJ>
+    __device__ __forceinline__ void mul(const cplx<float> (&t)[3], const cplx<float> (&h)[2][3],
+                                        cplx<float> (&o)[2][3]) const
+    {
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                float re = 0.f, im = 0.f;
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const int row = ADJ ? k : a, col = ADJ ? a : k;
+                    const float ux = row < 2 ? lo(3 * row + col) : t[col].x;
+                    const float uy = row < 2 ? hi(3 * row + col) : t[col].y;
+                    re = fmar(ux, h[s][k].x, re);
+                    im = fmar(ux, h[s][k].y, im);
+                    re = fmar(ADJ ? uy : -uy, h[s][k].y, re);
+                    im = fmar(ADJ ? -uy : uy, h[s][k].x, im);
+                }
+                o[s][a] = {re, im};
+            }
+    }
+    template <bool ADJ>
+    __device__ __forceinline__ void mul(const cplx<float> (&h)[2][3], cplx<float> (&o)[2][3]) const
+    {
+        cplx<float> t[3];
+        third(t);
+        mul<ADJ>(t, h, o);
+    }
+};
 
 // Per storage precision: waves per SIMD the register allocation must allow
-// (a block of 256 is one wave on each of a compute unit's four SIMDs), and
-// the depth of the software pipeline over the eight hops (the loads of hop
+// and the depth of the software pipeline over the hops (the loads of hop
 // K + depth are issued right after hop K has been applied).  FP64 holds 84
-// registers of operands per hop and already needs about 250 registers for
-// two waves per SIMD with one hop in flight; FP32 and FP16 keep three waves
-// with two hops in flight.
-#ifndef LQCD_DEPTH_64
-#define LQCD_DEPTH_64 1
-#endif
-#ifndef LQCD_DEPTH_32
-#define LQCD_DEPTH_32 2
-#endif
-#ifndef LQCD_DEPTH_16
-#define LQCD_DEPTH_16 2
-#endif
-
-// Tiles of several right-hand sides hold NR accumulators and run at depth 1
-// with the register count the compiler chooses.
-template <int PREC, int NR>
+// registers of operands per hop: two waves per SIMD either way, with one hop
+// in flight where a wave runs all eight (242 registers), with two where it
+// runs four (8^3x4 to 12^3x8: 5.6-7.0 us a hop against 6.8-8.2 with one).
+// FP32 and FP16 keep three waves or more with two hops in flight (three: no
+// faster).
+template <int PREC, int SPLIT>
 struct HopTune {
-    static constexpr int waves = NR > 1 ? 1 : hop_waves(PREC);
-    static constexpr int depth = NR > 1 ? 1 : PREC == 64 ? LQCD_DEPTH_64 : PREC == 32 ? LQCD_DEPTH_32 : LQCD_DEPTH_16;
-    static_assert(depth >= 1 && depth <= 4, "hop pipeline depth 1..4");
-    static_assert(waves >= 1 && waves <= 8, "waves per SIMD 1..8");
+    static constexpr int waves = hop_waves(PREC);
+    static constexpr int depth = PREC == 64 && SPLIT == 1 ? 1 : 2;
 };
 
-// Largest block of a hop launch: 256 work-items, or for the tile-1 launches
-// with cached links (right-hand sides across lanes: up to 16 lanes per site
-// and whole x-rows per block) one block per compute unit at the kernel's
-// waves per SIMD: 8 waves in FP64, 12 in FP32 and FP16.
-template <int PREC, int NR, bool LNT>
-struct HopBlock {
-    static constexpr int max_threads = (NR == 1 && !LNT) ? hop_lane_block_limit(PREC) : 256;
-};
-
-template <int PREC, int RECON, int NR, bool LNT, int SF, int D>
+// Hops K0 .. K1 - 1 of one site added into acc.  At depth 1 the neighbour
+// spinor is loaded and projected before the link is loaded, so the full
+// spinor and the link are not live together.
+template <int PREC, int RECON, bool DAG, bool LNT, int D, int K0, int K1>
 struct HopPipe {
     using R = typename SpinorIO<PREC>::R;
-    const char* const (&in)[NR];
-    const bool (&act)[NR];
-    const void* U;
-    int64_t S;
+    const char* in;
+    const DslashArgs& a;
     const SiteGeo& g;
-    const cplx<R> (&ph)[4];
-    Spinor<R> (&acc)[NR];
-    uint32_t xo;      // per-lane byte offset of the input field (right-hand sides across lanes)
-    int64_t span;     // bytes the input buffer resource covers (0: one field)
-    HopBuf<PREC, NR> buf[D > 1 ? D : 1];
+    Spinor<R>& acc;
+    Nbs<PREC> nb[D];
+    Lnk<PREC, RECON> lk[D];
 
     template <int K>
     __device__ __forceinline__ void load()
     {
-        hop_load<PREC, RECON, NR, LNT>(in, act, U, S, g.template get<K>(), buf[K % D], xo, span);
+        if constexpr (K < K1) {
+            const Nbr n = g.template get<K>();
+            lk[K % D].template load<LNT>(a.U, a.g.S, n.lblk, n.lsite);
+            nb[K % D].load(in, a.g.S, n.nb);
+        }
     }
     template <int K>
     __device__ __forceinline__ void step()
     {
-        constexpr int MU = K >> 1;
-        constexpr bool FWD = (K & 1) == 0;
-        hop_apply<PREC, MU, FWD, FWD ? SF : -SF, NR>(buf[K % D], act, g.template get<K>().cross, ph[MU], acc);
-        if constexpr (K + D < 8) load<K + D>();
-    }
-    template <int K>
-    __device__ __forceinline__ void fused()
-    {
-        constexpr int MU = K >> 1;
-        constexpr bool FWD = (K & 1) == 0;
-        hop_fused<PREC, RECON, MU, FWD, FWD ? SF : -SF, NR, LNT>(in, act, U, S, g.template get<K>(), ph[MU], acc,
-                                                                 xo, span);
+        if constexpr (K < K1) {
+            constexpr int MU = K >> 1;
+            constexpr bool FWD = (K & 1) == 0;
+            constexpr int SIG = FWD != DAG ? 1 : -1;  // projector (1 - SIG gamma)
+            const Nbr n = g.template get<K>();
+            cplx<R> h[2][3], w[2][3];
+            if constexpr (D == 1) nb[0].load(in, a.g.S, n.nb);
+            nb[K % D].template half<MU, SIG>(h);
+            if constexpr (D == 1) lk[0].template load<LNT>(a.U, a.g.S, n.lblk, n.lsite);
+            lk[K % D].template mul<!FWD>(h, w);
+            if (n.cross) {
+                const cplx<R> ph = uniform<R>(a.g.ph[MU]);
+                phase_mul(w, FWD ? ph : conj(ph));
+            }
+            nb[K % D].template add<MU, SIG>(acc, w);
+            if constexpr (D > 1) load<K + D>();
+        }
     }
     __device__ __forceinline__ void run()
     {
-        if constexpr (D == 1) {
-            fused<0>();
-            fused<1>();
-            fused<2>();
-            fused<3>();
-            fused<4>();
-            fused<5>();
-            fused<6>();
-            fused<7>();
-            return;
+        if constexpr (D > 1) {
+            load<K0>();
+            load<K0 + 1>();
+            if constexpr (D > 2) load<K0 + 2>();
+            if constexpr (D > 3) load<K0 + 3>();
         }
-        load<0>();
-        if constexpr (D > 1) load<1>();
-        if constexpr (D > 2) load<2>();
-        if constexpr (D > 3) load<3>();
-        step<0>();
-        step<1>();
-        step<2>();
-        step<3>();
-        step<4>();
-        step<5>();
-        step<6>();
-        step<7>();
+        step<K0>();
+        step<K0 + 1>();
+        step<K0 + 2>();
+        step<K0 + 3>();
+        step<K0 + 4>();
+        step<K0 + 5>();
+        step<K0 + 6>();
+        step<K0 + 7>();
     }
 };
 
@@ -268,227 +362,159 @@ struct RedN {
     static constexpr int N = RED == RED_NONE ? 1 : RED == RED_NORM ? 1 : RED == RED_DOT_AUX ? 2 : 3;
 };
 
-// Block part of the reductions of a right-hand-side tile: NR x N sums per
-// work-item, folded per wavefront and over waves in wave order; thread 0
-// writes partials[rhs][bid][j] for each right-hand side of the tile.
-template <int NR, int N>
-__device__ void block_reduce_tile(double (&v)[NR][N], double* partials, int nb, int rhs0, int nrhs, int bid)
-{
-    __shared__ double sm[NR * N][16];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int nwaves = blockDim.x >> 6;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int j = 0; j < N; ++j) v[r][j] += __shfl_xor(v[r][j], off, 64);
-    if (lane == 0)
-#pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int j = 0; j < N; ++j) sm[r * N + j][wave] = v[r][j];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int r = 0; r < NR; ++r) {
-            if (rhs0 + r >= nrhs) break;
-            double* out = partials + ((int64_t)(rhs0 + r) * nb + bid) * N;
-            for (int j = 0; j < N; ++j) {
-                double s = 0.0;
-                for (int w = 0; w < nwaves; ++w) s += sm[r * N + j][w];
-                out[j] = s;
-            }
-        }
-    }
-}
-
-// Block part of the reductions with right-hand sides across L lanes (L a
-// power of two up to 64; L = 1 is one right-hand side per block): lanes with
-// the same right-hand side (equal lane index mod L) fold their N sums per
-// wavefront, the waves are combined in LDS in wave order, and work-item r < L
-// writes partials[rhs0 + r][bid][j].  Blocks of up to 16 waves.
-template <int N>
-__device__ void block_reduce_lanes(double (&v)[N], double* partials, int nb, int rhs0, int L, int nrhs, int bid)
-{
-    __shared__ double sm[N][16][16];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int nwaves = blockDim.x >> 6;
-    for (int off = 32; off >= L; off >>= 1)
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] += __shfl_xor(v[j], off, 64);
-    if (lane < L)
-#pragma unroll
-        for (int j = 0; j < N; ++j) sm[j][wave][lane] = v[j];
-    __syncthreads();
-    const int r = threadIdx.x;
-    if (r < L && rhs0 + r < nrhs) {
-        double* out = partials + ((int64_t)(rhs0 + r) * nb + bid) * N;
-        for (int j = 0; j < N; ++j) {
-            double s = 0.0;
-            for (int w = 0; w < nwaves; ++w) s += sm[j][w][r];
-            out[j] = s;
-        }
-    }
-}
-
-// The work of one block: block bx of nbx along x and by along y of the
-// launch that serves this set of arguments.
-template <int PREC, int RECON, bool DAG, int RED, int NR, bool LNT>
-__device__ __forceinline__ void dslash_block(const DslashArgs& a, int bx, int nbx, int by)
+// out = add + a * site + c * acc of one right-hand side, with the sums of the reduction.
+template <int PREC, int RED>
+__device__ __forceinline__ void hop_store(const DslashArgs& a, int64_t rr, int64_t poff, int h, bool valid,
+                                          const Spinor<typename SpinorIO<PREC>::R>& acc, double (&tot)[RedN<RED>::N])
 {
     using R = typename SpinorIO<PREC>::R;
     constexpr int N = RedN<RED>::N;
-    // right-hand sides across lanes: the tile-1 launches with cached links
-    constexpr bool kLanes = NR == 1 && !LNT;
-    const int L = kLanes ? a.lanes : 1;
-    const int lr = kLanes ? (int)(threadIdx.x & (unsigned)(L - 1)) : 0;
-    const int tid = kLanes ? (int)(threadIdx.x >> a.lanes_log2) : (int)threadIdx.x;
-    const BlockPos bp = block_pos(a, bx, nbx, by);
-    const int p = bp.p, tile = bp.tile;
-    const int rhs0 = tile * NR * L;  // first right-hand side of the block's tile (uniform)
-    bool act[NR];
-    bool any = false;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const int rr = rhs0 + lr + r;
-        act[r] = tile < a.ntiles && rr < a.nrhs && !pred_skip(a.pred, a.ctl ? a.ctl + rr : nullptr);
-        any = any || act[r];
-    }
-    if (L == 1 && !any) return;  // uniform over the block unless the right-hand sides are across lanes
-    const SitePos sp = site_pos(a, bp.bid, p, tid);
-    const int h = sp.h;
-    const int64_t poff = bp.poff, ioff = bp.ioff;
     const int64_t S = a.g.S;
-    // per-lane offsets and buffer spans of the fields (right-hand side rhs0 + lr)
-    const bool wide = L > 1;
-    const uint32_t xo_in = (uint32_t)(lr * a.st_in), xo_out = (uint32_t)(lr * a.st_out);
-    const uint32_t xo_site = (uint32_t)(lr * a.st_site), xo_add = (uint32_t)(lr * a.st_add);
-    const uint32_t xo_aux = (uint32_t)(lr * a.st_aux);
-    const int64_t sp_in = wide ? L * a.st_in : 0, sp_out = wide ? L * a.st_out : 0;
-    const int64_t sp_site = wide ? L * a.st_site : 0, sp_add = wide ? L * a.st_add : 0;
-    const int64_t sp_aux = wide ? L * a.st_aux : 0;
-
-    double tot[NR][N];
+    const cplx<R> cu = uniform<R>(a.c.up), cl = uniform<R>(a.c.lo);
+    Spinor<R> o, st;
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int j = 0; j < N; ++j) tot[r][j] = 0.0;
-
-    if (sp.valid && any) {
-        const char* in[NR];
+        for (int c = 0; c < 3; ++c) o.s[s][c] = (s < 2 ? cu : cl) * acc.s[s][c];
+    if (a.site) {
+        const cplx<R> au = uniform<R>(a.a.up), al = uniform<R>(a.a.lo);
+        SpinorIO<PREC>::load(static_cast<const char*>(a.site) + rr * a.st_site + poff, S, h, st);
 #pragma unroll
-        for (int r = 0; r < NR; ++r) in[r] = static_cast<const char*>(a.in) + (int64_t)(rhs0 + r) * a.st_in + ioff;
-        constexpr int SF = DAG ? -1 : 1;  // projector sign of forward hops: (1 - SF gamma)
-        Spinor<R> acc[NR];
+        for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int r = 0; r < NR; ++r)
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) acc[r].s[s][c] = {R(0), R(0)};
-
-        const cplx<R> ph[4] = {{R(a.g.ph[0][0]), R(a.g.ph[0][1])},
-                               {R(a.g.ph[1][0]), R(a.g.ph[1][1])},
-                               {R(a.g.ph[2][0]), R(a.g.ph[2][1])},
-                               {R(a.g.ph[3][0]), R(a.g.ph[3][1])}};
-        const SiteGeo geo = site_geo(a.g, sp, p);
-        HopPipe<PREC, RECON, NR, LNT, SF, HopTune<PREC, NR>::depth> pipe{in, act, a.U, S, geo, ph, acc, xo_in, sp_in};
-        pipe.run();
-
-        // epilogue per right-hand side: out = add + a * site + c * acc
-        const cplx<R> cu = {R(a.c.up[0]), R(a.c.up[1])}, cl = {R(a.c.lo[0]), R(a.c.lo[1])};
-#pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            if (NR > 1 && !act[r]) continue;
-            const int64_t rr = rhs0 + r;
-            Spinor<R> o;
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) o.s[s][c] = (s < 2 ? cu : cl) * acc[r].s[s][c];
-            Spinor<R> st;
-            if (a.site) {
-                const cplx<R> au = {R(a.a.up[0]), R(a.a.up[1])}, al = {R(a.a.lo[0]), R(a.a.lo[1])};
-                SpinorIO<PREC>::load(static_cast<const char*>(a.site) + rr * a.st_site + poff, S, h, st, xo_site,
-                                     sp_site);
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) o.s[s][c] = o.s[s][c] + (s < 2 ? au : al) * st.s[s][c];
-            }
-            if (a.add) {
-                Spinor<R> ad;
-                SpinorIO<PREC>::load(static_cast<const char*>(a.add) + rr * a.st_add + poff, S, h, ad, xo_add, sp_add);
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) o.s[s][c] = o.s[s][c] + ad.s[s][c];
-            }
-            if (a.out)
-                SpinorIO<PREC>::template store<LQCD_OUT_AUX>(static_cast<char*>(a.out) + rr * a.st_out + poff, S, h, o,
-                                                             xo_out, sp_out);
-
-            if (RED == RED_NORM || RED == RED_NORM_DS) {
-                double n2 = 0.0;
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) n2 += (double)norm2(o.s[s][c]);
-                tot[r][0] = n2;
-            }
-            if (RED == RED_NORM_DS) {  // <out, site>
-                double re = 0.0, im = 0.0;
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const cplx<R> v = cmulc(o.s[s][c], st.s[s][c]);
-                        re += (double)v.x;
-                        im += (double)v.y;
-                    }
-                tot[r][N - 2] = re;
-                tot[r][N - 1] = im;
-            }
-            if (RED == RED_DOT_AUX) {  // <aux, out>
-                Spinor<R> ax;
-                SpinorIO<PREC>::load(static_cast<const char*>(a.aux) + rr * a.st_aux + poff, S, h, ax, xo_aux, sp_aux);
-                double re = 0.0, im = 0.0;
-#pragma unroll
-                for (int s = 0; s < 4; ++s)
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) {
-                        const cplx<R> v = cmulc(ax.s[s][c], o.s[s][c]);
-                        re += (double)v.x;
-                        im += (double)v.y;
-                    }
-                tot[r][N - 2] = re;
-                tot[r][N - 1] = im;
-            }
-        }
+            for (int c = 0; c < 3; ++c) o.s[s][c] = o.s[s][c] + (s < 2 ? au : al) * st.s[s][c];
     }
-
-    if constexpr (RED != RED_NONE) {
-        if constexpr (kLanes) block_reduce_lanes<N>(tot[0], a.r.partials, bp.nslots, rhs0, L, a.nrhs, bp.pslot);
-        else block_reduce_tile<NR, N>(tot, a.r.partials, bp.nslots, rhs0, a.nrhs, bp.pslot);
+    if (a.add) {
+        Spinor<R> ad;
+        SpinorIO<PREC>::load(static_cast<const char*>(a.add) + rr * a.st_add + poff, S, h, ad);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) o.s[s][c] = o.s[s][c] + ad.s[s][c];
+    }
+    if (!valid) return;
+    if (a.out) SpinorIO<PREC>::template store<LQCD_OUT_AUX>(static_cast<char*>(a.out) + rr * a.st_out + poff, S, h, o);
+    if (RED == RED_NORM || RED == RED_NORM_DS) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) tot[0] += (double)norm2(o.s[s][c]);
+    }
+    if (RED == RED_NORM_DS) {  // <out, site>
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const cplx<R> v = cmulc(o.s[s][c], st.s[s][c]);
+                tot[N - 2] += (double)v.x;
+                tot[N - 1] += (double)v.y;
+            }
+    }
+    if (RED == RED_DOT_AUX) {  // <aux, out>
+        Spinor<R> ax;
+        SpinorIO<PREC>::load(static_cast<const char*>(a.aux) + rr * a.st_aux + poff, S, h, ax);
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const cplx<R> v = cmulc(ax.s[s][c], o.s[s][c]);
+                tot[N - 2] += (double)v.x;
+                tot[N - 1] += (double)v.y;
+            }
     }
 }
 
-template <int PREC, int RECON, bool DAG, int RED, int NR, bool LNT>
-__global__ void __launch_bounds__((HopBlock<PREC, NR, LNT>::max_threads))
-    __attribute__((amdgpu_waves_per_eu(HopTune<PREC, NR>::waves))) k_dslash_eo(const DslashArgs a)
+// The sum wave 1 of a two-wave block leaves for wave 0.
+template <class R, int SPLIT>
+struct SplitLds {
+    cplx<R> v[12][kChunk];
+};
+template <class R>
+struct SplitLds<R, 1> {};
+
+// One right-hand side per block, block bx of the launch.  SPLIT = 1: every wave of the block
+// serves its own chunk of 64 sites.  SPLIT = 2: a block is two waves that
+// share one chunk, wave 0 runs the x and y hops and wave 1 the z and t hops,
+// and wave 0 adds the two sums through LDS and stores.  What the split buys:
+// half the chain of dependent loads per wave and twice the waves, where a
+// lattice does not fill the chip (FP64/18 hop 16^3x8 9.3 -> 6.3 us, 12^3x8
+// 13.9 -> 7.0, 24^3x8 20.2 -> 18.5; FP32/12 20^3x6 8.1 -> 6.3), and a shorter
+// drain at the end of a large launch (48^3x12 FP32/12 77.0 -> 75.5).  The
+// plan chooses (see plan_dslash).
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+__device__ __forceinline__ void dslash_block(const DslashArgs& a, int bx)
 {
-    dslash_block<PREC, RECON, DAG, RED, NR, LNT>(a, blockIdx.x, gridDim.x, blockIdx.y);
+    using R = typename SpinorIO<PREC>::R;
+    constexpr int N = RedN<RED>::N;
+    constexpr int D = HopTune<PREC, SPLIT>::depth;
+    __shared__ SplitLds<R, SPLIT> lds;
+    uint32_t rhs, b;
+    if (!tile_block(a, bx, &rhs, &b) || pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    int p = a.parity;
+    if (a.full) {  // both parities in one launch, adjacent in the block order: the second finds the links in L2
+        p = (int)(b & 1u);
+        b >>= 1;
+    }
+    const int64_t poff = a.full ? p * a.par_bytes : 0, ioff = a.full ? (1 - p) * a.par_bytes : 0;
+    const SitePos s = chunk_site(a.ch, a.g.Lxh, a.g.L[1], a.g.L[2], a.g.Vh, b, SPLIT > 1 ? 0 : wave, p, lane);
+    double tot[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) tot[j] = 0.0;
+    if (SPLIT > 1 || (s.some && wave < a.ch.nsub)) {  // (a batched launch may have more waves than this system's blocks)
+        const SiteGeo geo = site_geo(a.g, s, p);
+        const char* in = static_cast<const char*>(a.in) + (int64_t)rhs * a.st_in + ioff;
+        Spinor<R> acc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc.s[i][c] = {R(0), R(0)};
+        auto hops = [&](auto part) {
+            constexpr int Q = decltype(part)::value;
+            HopPipe<PREC, RECON, DAG, LNT, D, Q * (8 / SPLIT), (Q + 1) * (8 / SPLIT)> pipe{in, a, geo, acc, {}, {}};
+            pipe.run();
+        };
+        if constexpr (SPLIT == 1) hops(std::integral_constant<int, 0>{});
+        else {
+            if (wave == 0) hops(std::integral_constant<int, 0>{});
+            else {
+                hops(std::integral_constant<int, 1>{});
+#pragma unroll
+                for (int k = 0; k < 12; ++k) lds.v[k][lane] = acc.s[k / 3][k % 3];
+            }
+            __syncthreads();
+            if (wave == 0)
+#pragma unroll
+                for (int k = 0; k < 12; ++k) acc.s[k / 3][k % 3] = acc.s[k / 3][k % 3] + lds.v[k][lane];
+        }
+        if (SPLIT == 1 || wave == 0) hop_store<PREC, RED>(a, rhs, poff, s.h, s.valid, acc, tot);
+    }
+    if constexpr (RED != RED_NONE) {
+        const int slot = (int)(rhs * a.ch.nblk) + (int)b + p * (a.full ? a.ch.nsp : 0);
+        if constexpr (SPLIT == 1) block_reduce_store<N>(tot, a.r.partials, slot);
+        else if (wave == 0) {
+            wave_reduce<N>(tot);
+            if (lane == 0)
+#pragma unroll
+                for (int j = 0; j < N; ++j) a.r.partials[(int64_t)slot * N + j] = tot[j];
+        }
+    }
+}
+
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopTune<PREC, SPLIT>::waves)))
+k_dslash_eo(const DslashArgs a)
+{
+    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(a, blockIdx.x);
 }
 
 // Several systems (lattices of different sizes) in one launch: block x of the
 // flattened grid belongs to system s with offs[s] <= x < offs[s + 1]; each
 // system's arguments come from the device table tab.
-template <int PREC, int RECON, bool DAG, int RED, int NR, bool LNT>
-__global__ void __launch_bounds__((HopBlock<PREC, NR, LNT>::max_threads))
-    __attribute__((amdgpu_waves_per_eu(HopTune<PREC, NR>::waves))) k_dslash_eo_batch(const DslashArgs* __restrict__ tab,
-                                                        const int* __restrict__ offs, int nsys)
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopTune<PREC, SPLIT>::waves)))
+k_dslash_eo_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
     const int x = blockIdx.x;
     int s = 0;
@@ -496,52 +522,51 @@ __global__ void __launch_bounds__((HopBlock<PREC, NR, LNT>::max_threads))
     // each system's range starts at a multiple of 8 (XCD remap); blocks past
     // the system's own grid are padding
     const int bx = x - offs[s];
-    if (bx >= tab[s].gx) return;  // (a tile index past ntiles finds no active right-hand side)
-    dslash_block<PREC, RECON, DAG, RED, NR, LNT>(tab[s], bx, tab[s].gx, blockIdx.y);
+    if (bx >= tab[s].gx) return;
+    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(tab[s], bx);
 }
 
-template <int PREC, int RECON, bool DAG, int RED, int NR, bool LNT>
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
 static hipError_t launch_one(const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
     if (L.tab)
-        hipLaunchKernelGGL((k_dslash_eo_batch<PREC, RECON, DAG, RED, NR, LNT>), grid, block, 0, s, L.tab, L.offs, L.nsys);
-    else hipLaunchKernelGGL((k_dslash_eo<PREC, RECON, DAG, RED, NR, LNT>), grid, block, 0, s, *L.a);
+        hipLaunchKernelGGL((k_dslash_eo_batch<PREC, RECON, DAG, RED, LNT, SPLIT>), grid, block, 0, s, L.tab, L.offs,
+                           L.nsys);
+    else hipLaunchKernelGGL((k_dslash_eo<PREC, RECON, DAG, RED, LNT, SPLIT>), grid, block, 0, s, *L.a);
     return hipGetLastError();
 }
 
-template <int PREC, int RECON, bool DAG, int NR, bool LNT>
+template <int PREC, int RECON, bool DAG, bool LNT, int SPLIT>
 static hipError_t launch_red(int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
     switch (red) {
-    case RED_NONE: return launch_one<PREC, RECON, DAG, RED_NONE, NR, LNT>(L, grid, block, s);
-    case RED_NORM: return launch_one<PREC, RECON, DAG, RED_NORM, NR, LNT>(L, grid, block, s);
-    case RED_NORM_DS: return launch_one<PREC, RECON, DAG, RED_NORM_DS, NR, LNT>(L, grid, block, s);
-    case RED_DOT_AUX: return launch_one<PREC, RECON, DAG, RED_DOT_AUX, NR, LNT>(L, grid, block, s);
+    case RED_NONE: return launch_one<PREC, RECON, DAG, RED_NONE, LNT, SPLIT>(L, grid, block, s);
+    case RED_NORM: return launch_one<PREC, RECON, DAG, RED_NORM, LNT, SPLIT>(L, grid, block, s);
+    case RED_NORM_DS: return launch_one<PREC, RECON, DAG, RED_NORM_DS, LNT, SPLIT>(L, grid, block, s);
+    case RED_DOT_AUX: return launch_one<PREC, RECON, DAG, RED_DOT_AUX, LNT, SPLIT>(L, grid, block, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-template <int PREC, int RECON, int NR, bool LNT>
+template <int PREC, int RECON, bool LNT, int SPLIT>
 static hipError_t launch_dag(bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
-    return dag ? launch_red<PREC, RECON, true, NR, LNT>(red, L, grid, block, s)
-               : launch_red<PREC, RECON, false, NR, LNT>(red, L, grid, block, s);
+    return dag ? launch_red<PREC, RECON, true, LNT, SPLIT>(red, L, grid, block, s)
+               : launch_red<PREC, RECON, false, LNT, SPLIT>(red, L, grid, block, s);
 }
 
-// Right-hand-side tiles compiled per storage: 1, 2 and 4 for FP32 and FP16
-// (the multi-RHS inner solves), 1 and 2 for FP64.  Streaming link loads are
-// compiled for the one-tile case only: with several tiles (or a tile of
-// several right-hand sides sharing the loaded link) links stay cached.
+// Streaming link loads for one parity (each link has one reader), cached ones
+// for both parities in one launch (each link has two).  One wave per chunk is
+// built only where it can be the faster split: FP64, one parity.
 template <int PREC, int RECON>
-inline hipError_t launch_tile(int nr, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
-                              hipStream_t s)
+inline hipError_t launch_hop(int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
+                             hipStream_t s)
 {
-    if (nr == 1)
-        return lnt ? launch_dag<PREC, RECON, 1, true>(dag, red, L, grid, block, s)
-                   : launch_dag<PREC, RECON, 1, false>(dag, red, L, grid, block, s);
-    if (nr == 2) return launch_dag<PREC, RECON, 2, false>(dag, red, L, grid, block, s);
-    if constexpr (PREC != 64)
-        if (nr == 4) return launch_dag<PREC, RECON, 4, false>(dag, red, L, grid, block, s);
+    if (split == 2)
+        return lnt ? launch_dag<PREC, RECON, true, 2>(dag, red, L, grid, block, s)
+                   : launch_dag<PREC, RECON, false, 2>(dag, red, L, grid, block, s);
+    if constexpr (PREC == 64)
+        if (split == 1 && lnt) return launch_dag<PREC, RECON, true, 1>(dag, red, L, grid, block, s);
     return hipErrorInvalidValue;
 }
 

@@ -1,0 +1,254 @@
+// Even-odd Wilson / twisted-mass Dslash on several right-hand sides (kernel
+// templates; each storage precision is instantiated in its own translation
+// unit).
+//
+// A block serves 64 output sites for up to four right-hand sides, one per
+// wave.  The waves first share the loading of the eight links of the sites
+// and leave them in LDS with their third row rebuilt; after one barrier each
+// wave runs the eight hops of its right-hand side with the spinors from
+// memory and the links from LDS.
+//
+// Bounds: reads from beyond L2 (each XCD works on an eighth of the lattice and
+// re-reads its surface), and VALU issue in FP16 storage.  Against one
+// right-hand side per work-item with the links re-read through the caches
+// (and for FP16 two of them in registers): a link's third row is rebuilt once
+// for four right-hand sides and the link loads of a hop are one LDS read.
+// 32^3x8 Schur, 12 right-hand sides: FP32/12 241 -> 207 us, FP16/12 186 ->
+// 146, FP64/18 684 -> 565; 24^3x8 FP16/12 hop, 2: 15.2 -> 9.8.  Links are
+// loaded with the normal policy: the next tile finds them in the Infinity
+// Cache (streamed: 223 us instead of 207).
+#pragma once
+
+#include "dslash_impl.h"
+
+namespace lqcd {
+
+constexpr int kRhsTile = 4;  // most right-hand sides per block
+
+// The links of a block's sites, [hop][words of the link][site]: nine entries,
+// or for FP16 storage the halves of rows 0 and 1 and the third row in FP32.
+template <int PREC, int RECON>
+struct RhsLinks {
+    using R = typename SpinorIO<PREC>::R;
+    struct alignas(4 * sizeof(R)) Two {
+        cplx<R> a, b;
+    };
+    Two w[8][4][kChunk];
+    cplx<R> last[8][kChunk];
+    __device__ __forceinline__ void put(int k, int lane, const Lnk<PREC, RECON>& L)
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            w[k][i][lane] = {L.u.u[2 * i / 3][2 * i % 3], L.u.u[(2 * i + 1) / 3][(2 * i + 1) % 3]};
+        last[k][lane] = L.u.u[2][2];
+    }
+    template <bool ADJ>
+    __device__ __forceinline__ void mul(int k, int lane, const cplx<R> (&h)[2][3], cplx<R> (&o)[2][3]) const
+    {
+        Link<R> L;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const Two t = w[k][i][lane];
+            L.u[2 * i / 3][2 * i % 3] = t.a;
+            L.u[(2 * i + 1) / 3][(2 * i + 1) % 3] = t.b;
+        }
+        L.u[2][2] = last[k][lane];
+        link_mul<R, ADJ>(L, h, o);
+    }
+};
+
+template <>
+struct RhsLinks<16, 12> {
+    uint4 w[8][3][kChunk];
+    __device__ __forceinline__ void put(int k, int lane, const Lnk<16, 12>& L)
+    {
+        cplx<float> t[3];
+        L.third(t);
+        w[k][0][lane] = make_uint4(L.w[0], L.w[1], L.w[2], L.w[3]);
+        w[k][1][lane] = make_uint4(L.w[4], L.w[5], __float_as_uint(t[0].x), __float_as_uint(t[0].y));
+        w[k][2][lane] = make_uint4(__float_as_uint(t[1].x), __float_as_uint(t[1].y), __float_as_uint(t[2].x),
+                                   __float_as_uint(t[2].y));
+    }
+    template <bool ADJ>
+    __device__ __forceinline__ void mul(int k, int lane, const cplx<float> (&h)[2][3], cplx<float> (&o)[2][3]) const
+    {
+        const uint4 a = w[k][0][lane], b = w[k][1][lane], c = w[k][2][lane];
+        const Lnk<16, 12> L = {{a.x, a.y, a.z, a.w, b.x, b.y}};
+        const cplx<float> t[3] = {{__uint_as_float(b.z), __uint_as_float(b.w)},
+                                  {__uint_as_float(c.x), __uint_as_float(c.y)},
+                                  {__uint_as_float(c.z), __uint_as_float(c.w)}};
+        L.mul<ADJ>(t, h, o);
+    }
+};
+
+// Neighbour spinors in flight per wave and waves per SIMD.  FP64 issues the
+// next hop's loads after a hop's registers are free again (242 registers at
+// two waves, no spills; ahead of the link product it spills 32).
+template <int PREC>
+struct RhsTune {
+    static constexpr int depth = PREC == 64 ? 1 : 2;
+    static constexpr int waves = PREC == 64 ? 2 : PREC == 32 ? 3 : 4;
+};
+
+template <int PREC, int RECON, bool DAG>
+struct RhsPipe {
+    using R = typename SpinorIO<PREC>::R;
+    static constexpr int D = RhsTune<PREC>::depth;
+    const RhsLinks<PREC, RECON>& lds;
+    const DslashArgs& a;
+    const SiteGeo& g;
+    const char* in;
+    int lane;
+    Nbs<PREC> nb[D];
+    Spinor<R> acc;
+
+    template <int K>
+    __device__ __forceinline__ void load()
+    {
+        if constexpr (K < 8) nb[K % D].load(in, a.g.S, g.template get<K>().nb);
+    }
+    template <int K>
+    __device__ __forceinline__ void step()
+    {
+        constexpr int MU = K >> 1;
+        constexpr bool FWD = (K & 1) == 0;
+        constexpr int SIG = FWD != DAG ? 1 : -1;
+        cplx<R> h[2][3], w[2][3];
+        nb[K % D].template half<MU, SIG>(h);
+        if constexpr (PREC == 32) load<K + D>();
+        lds.template mul<!FWD>(K, lane, h, w);
+        if (g.template get<K>().cross) {
+            const cplx<R> ph = uniform<R>(a.g.ph[MU]);
+            phase_mul(w, FWD ? ph : conj(ph));
+        }
+        nb[K % D].template add<MU, SIG>(acc, w);
+        if constexpr (PREC != 32) load<K + D>();
+        __builtin_amdgcn_sched_barrier(0);  // or the scheduler reads the next hops' links early and spills
+    }
+    __device__ __forceinline__ void first()
+    {
+        load<0>();
+        if constexpr (D > 1) load<1>();
+        if constexpr (D > 2) load<2>();
+    }
+    __device__ __forceinline__ void run()
+    {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acc.s[s][c] = {R(0), R(0)};
+        step<0>();
+        step<1>();
+        step<2>();
+        step<3>();
+        step<4>();
+        step<5>();
+        step<6>();
+        step<7>();
+    }
+};
+
+// Block bx of the launch.
+template <int PREC, int RECON, bool DAG, int RED>
+__device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<PREC, RECON>& lds)
+{
+    constexpr int N = RedN<RED>::N;
+    const int lane = (int)threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = (int)blockDim.x >> 6;
+    uint32_t tile, b;
+    if (!tile_block(a, bx, &tile, &b)) return;
+    const int rhs0 = (int)tile * a.ch.tile, nr = min(a.ch.tile, a.nrhs - rhs0);
+    // right-hand sides of the tile that run
+    const bool on = lane < nr && !pred_skip(a.pred, a.ctl ? a.ctl + rhs0 + min(lane, nr - 1) : nullptr);
+    const uint32_t mask = (uint32_t)__ballot(on);
+    if (!mask) return;  // uniform over the block
+    int p = a.parity;
+    if (a.full) {
+        p = (int)(b & 1u);
+        b >>= 1;
+    }
+    const SitePos s = chunk_site(a.ch, a.g.Lxh, a.g.L[1], a.g.L[2], a.g.Vh, b, 0, p, lane);
+    const SiteGeo geo = site_geo(a.g, s, p);
+    const int64_t S = a.g.S;
+    const int64_t poff = a.full ? p * a.par_bytes : 0, ioff = a.full ? (1 - p) * a.par_bytes : 0;
+    const bool run = (mask >> wave) & 1u;
+    const int64_t rr = rhs0 + wave;
+    RhsPipe<PREC, RECON, DAG> pipe{lds, a, geo, static_cast<const char*>(a.in) + rr * a.st_in + ioff, lane, {}, {}};
+    if (run) pipe.first();
+    for (int k = wave; k < 8; k += nw) {
+        // link of hop k: of this site (forward) or of the neighbour (backward)
+        int l = s.h;
+        if (k == 1) l = geo.get<1>().nb;
+        else if (k == 3) l = geo.get<3>().nb;
+        else if (k == 5) l = geo.get<5>().nb;
+        else if (k == 7) l = geo.get<7>().nb;
+        Lnk<PREC, RECON> L;
+        L.template load<false>(a.U, S, (k & ~1) + ((k & 1) ? 1 - p : p), l);
+        lds.put(k, lane, L);
+    }
+    __syncthreads();
+    if (!run) return;
+    pipe.run();
+    double tot[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) tot[j] = 0.0;
+    hop_store<PREC, RED>(a, rr, poff, s.h, s.valid, pipe.acc, tot);
+    if constexpr (RED != RED_NONE) {
+        wave_reduce<N>(tot);
+        const int64_t nsl = a.ch.nsp * (a.full ? 2 : 1), slot = (int)b + p * (a.full ? a.ch.nsp : 0);
+        if (lane == 0)
+#pragma unroll
+            for (int j = 0; j < N; ++j) a.r.partials[(rr * nsl + slot) * N + j] = tot[j];
+    }
+}
+
+template <int PREC, int RECON, bool DAG, int RED>
+__global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
+k_hop_rhs(const DslashArgs a)
+{
+    __shared__ RhsLinks<PREC, RECON> lds;
+    rhs_block<PREC, RECON, DAG, RED>(a, blockIdx.x, lds);
+}
+
+template <int PREC, int RECON, bool DAG, int RED>
+__global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
+k_hop_rhs_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
+{
+    __shared__ RhsLinks<PREC, RECON> lds;
+    const int x = blockIdx.x;
+    int s = 0;
+    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
+    const int bx = x - offs[s];
+    if (bx >= tab[s].gx) return;  // padding of the system's range
+    rhs_block<PREC, RECON, DAG, RED>(tab[s], bx, lds);
+}
+
+template <int PREC, int RECON, bool DAG, int RED>
+static hipError_t rhs_one(const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
+{
+    if (L.tab) hipLaunchKernelGGL((k_hop_rhs_batch<PREC, RECON, DAG, RED>), grid, block, 0, s, L.tab, L.offs, L.nsys);
+    else hipLaunchKernelGGL((k_hop_rhs<PREC, RECON, DAG, RED>), grid, block, 0, s, *L.a);
+    return hipGetLastError();
+}
+
+template <int PREC, int RECON, bool DAG>
+static hipError_t rhs_red(int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
+{
+    switch (red) {
+    case RED_NONE: return rhs_one<PREC, RECON, DAG, RED_NONE>(L, grid, block, s);
+    case RED_NORM: return rhs_one<PREC, RECON, DAG, RED_NORM>(L, grid, block, s);
+    case RED_NORM_DS: return rhs_one<PREC, RECON, DAG, RED_NORM_DS>(L, grid, block, s);
+    case RED_DOT_AUX: return rhs_one<PREC, RECON, DAG, RED_DOT_AUX>(L, grid, block, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+template <int PREC, int RECON>
+inline hipError_t launch_rhs(bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
+{
+    return dag ? rhs_red<PREC, RECON, true>(red, L, grid, block, s)
+               : rhs_red<PREC, RECON, false>(red, L, grid, block, s);
+}
+
+}  // namespace lqcd

@@ -273,6 +273,13 @@ struct SpinorIO<16> {
         r.x = hi ? (unsigned short)(w >> 16) : (unsigned short)(w & 0xffffu);
         return __half2float(__half(r));
     }
+    // halves of a * inv and b * inv, each rounded once (fma_mixlo / fma_mixhi)
+    __device__ static __forceinline__ uint32_t f2h2(float a, float b, float inv)
+    {
+        using half2v = __attribute__((__vector_size__(2 * sizeof(_Float16)))) _Float16;
+        const half2v v = {(_Float16)__builtin_fmaf(a, inv, 0.f), (_Float16)__builtin_fmaf(b, inv, 0.f)};
+        return __builtin_bit_cast(uint32_t, v);
+    }
     __device__ static __forceinline__ uint32_t f2h2(float a, float b)
     {
         __half_raw ra = __half(__float2half_rn(a));
@@ -315,7 +322,7 @@ struct SpinorIO<16> {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int c = 4 * k + j;
-                w[j] = f2h2(v.s[c / 3][c % 3].x * inv, v.s[c / 3][c % 3].y * inv);
+                w[j] = f2h2(v.s[c / 3][c % 3].x, v.s[c / 3][c % 3].y, inv);
             }
             bstore<AUX>(r, o, (uint32_t)(k * S * 16), make_uint4(w[0], w[1], w[2], w[3]));
         }
@@ -411,7 +418,7 @@ struct ColourIO<16> {
         const float inv = m > 0.f ? 1.0f / m : 0.f;
         uint32_t w[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) w[k] = SpinorIO<16>::f2h2(v.c[k].x * inv, v.c[k].y * inv);
+        for (int k = 0; k < 3; ++k) w[k] = SpinorIO<16>::f2h2(v.c[k].x, v.c[k].y, inv);
         const rsrc_t r = make_rsrc(base, 16 * S);
         bstore<AUX>(r, static_cast<uint32_t>(site) * 16u, 0u, make_uint4(w[0], w[1], w[2], __float_as_uint(m)));
     }

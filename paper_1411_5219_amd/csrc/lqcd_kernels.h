@@ -7,6 +7,7 @@
 
 #include <vector>
 
+#include "chunks.h"
 #include "solver_ctl.h"
 
 namespace lqcd {
@@ -44,6 +45,8 @@ enum Pred {
 // Most values one reduction produces per block (BiCGStab(2)'s Gram step).
 constexpr int kMaxFin = 5;
 
+constexpr int kSimds = 1024;  // 256 compute units of 4 SIMDs
+
 struct RedArgs {
     double* partials;       // [nrhs][nblocks][N]
     int capacity;           // blocks the partials hold per right-hand side (N <= kMaxFin)
@@ -72,77 +75,35 @@ struct DslashArgs {
     RedArgs r;
     Ctl* ctl;               // per right-hand side, or null
     int swizzle;
-    // Block order.  rows = 0: block b covers eo sites [b*B, (b+1)*B) in
-    // memory order.  rows = R > 0: a block covers R whole x-rows at one
-    // (z, t) (a contiguous chunk of sites) and blocks run t fastest, then z,
-    // then the y-chunk, so the t and z neighbours a block reads were loaded
-    // by blocks that ran just before it on the same XCD.  ztile = T > 1
-    // (T divides Lz): z-slabs of T planes, z fastest within a slab, then t,
-    // then the slab, then the y-chunk; a spinor's z and t neighbours are then
-    // at most T blocks away except on slab faces.
-    // ygroup = G > 1 (ztile 1; G divides nyc): G neighbouring y-chunks run
-    // after t and before z (t fastest, then the G chunks, then z, then the
-    // group), so the rows just outside a chunk, which its y-hops read, were
-    // loaded by blocks a few places before it on the same XCD.
-    int rows;
-    int nyc;                // y-chunks of R rows (rows > 0)
-    int ztile;              // z-planes per slab (rows > 0; 1: t fastest)
-    int ygroup;             // y-chunks interleaved after t (rows > 0, ztile 1)
     int nrhs;               // right-hand sides (set by the launcher)
-    // Right-hand-side tiles in the block order.  rhs_group = 0: tile index
-    // is blockIdx.y.  rhs_group = G > 0: grid.y = 1 and the tiles are
-    // interleaved into blockIdx.x, G tiles fastest over the same spatial
-    // block, then the spatial blocks, then the groups of G tiles, so a link
-    // loaded for one tile is re-read from L2 by the next G - 1 blocks.
-    int rhs_group;
-    int ntiles;             // right-hand-side tiles (ceil(nrhs / tile))
-    int nsp;                // spatial blocks per parity (rhs_group > 0)
-    // Right-hand sides across lanes: lanes = L > 1 (a power of two, tile 1):
-    // work-item t of a block serves site t >> lanes_log2 of the block and
-    // right-hand side (tile L + (t & (L - 1))), so the L right-hand sides of
-    // a site sit in adjacent lanes of one wave, their link loads are one
-    // coalesced request, and the link comes from memory once per hop for all
-    // of them.  The right-hand-side offset travels in the per-lane buffer
-    // offset (the buffer base stays uniform).
-    int lanes;
-    int lanes_log2;
-    int bdim;               // site work-items of a block that this argument set uses
     int gx;                 // planned grid.x (batched launches pad each system's range)
+    ChunkArgs ch;
 };
 
 // Waves per SIMD the one-right-hand-side hop kernels are compiled for (their
 // register budget): FP64 holds about 250 registers at two waves, FP32 and FP16
-// keep three.  The tile-1 launches with right-hand sides across lanes take
-// blocks of up to one compute unit's worth of those waves.
-#ifndef LQCD_WAVES_64
-#define LQCD_WAVES_64 2
-#endif
-#ifndef LQCD_WAVES_32
-#define LQCD_WAVES_32 3
-#endif
-#ifndef LQCD_WAVES_16
-#define LQCD_WAVES_16 3
-#endif
-__host__ __device__ constexpr int hop_waves(int prec)
-{
-    return prec == 64 ? LQCD_WAVES_64 : prec == 32 ? LQCD_WAVES_32 : LQCD_WAVES_16;
-}
-__host__ __device__ constexpr int hop_lane_block_limit(int prec) { return 256 * hop_waves(prec); }
+// keep three.
+__host__ __device__ constexpr int hop_waves(int prec) { return prec == 64 ? 2 : 3; }
 
 // Launch configuration picked per kernel (autotuned).
 struct Launch {
     int block = 128;
     int swizzle = 1;
-    int order = 0;     // 0: memory order, 1: t-fastest tiles of whole x-rows, k > 1: z-slabs of k planes (Dslash)
-    int rhs_tile = 4;  // right-hand sides one Dslash work-item handles (links loaded once)
-    int rhs_group = 4; // right-hand-side tiles interleaved per spatial block (0: grid.y)
-    int ygroup = 1;    // y-chunks interleaved after t in the row-tile order (1: none)
-    int rhs_lanes = 1; // right-hand sides across adjacent lanes of a site (1: none; 2..16, tile 1)
+    int order = 0;     // 0: memory order, 1: t-fastest chunks of xy planes, k > 1: z-slabs of k planes (hops)
+    int rhs_tile = 4;  // rhs_tile, rhs_group, rhs_lanes: part of the C ABI's struct; launches on several
+    int rhs_group = 4; // right-hand sides put four of them in a block whatever these say
+    int ygroup = 1;    // blocks of a plane interleaved after t, in units of the block request (1: none)
+    int rhs_lanes = 1;
+    int form = 0;      // HopForm of Wilson hops (set where several launches must run the same kernel)
 };
 
-// Right-hand-side tile the Dslash uses for a request (clamped to the tiles
-// compiled for the precision and to nrhs).
-int dslash_rhs_tile(int prec, int want, int nrhs);
+// How the waves of a Wilson hop share sites and right-hand sides: one wave or
+// a pair of waves per chunk of 64 sites and right-hand side, or a tile of
+// right-hand sides per chunk with its links in LDS.
+enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3 };
+// The form for launches on nrhs right-hand sides of the n lattices g (want if
+// not by size).  FORM_WAVE exists for FP64 on one right-hand side and one parity.
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want);
 
 // Sum N block partials per right-hand side in block order and run the
 // solver's scalar step (Fin) on the totals; one block per right-hand side.
@@ -186,9 +147,10 @@ struct DslashPlan {
     DslashArgs a;
     dim3 grid, block;
     int kind;   // PlanKind
-    int prec, recon, nr, red;
+    int prec, recon, red;
+    int split;  // waves per chunk of sites, 0: several right-hand sides per block
     bool dag;
-    bool lnt;   // streaming link loads (one right-hand-side tile of one)
+    bool lnt;   // streaming link loads (no other block of the launch reads the links)
     int nfin;   // values per finalize (0: no reduction)
     int slots;  // partial slots per right-hand side
 };

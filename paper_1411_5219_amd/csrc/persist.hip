@@ -29,7 +29,7 @@
 // The grid never exceeds the blocks the device keeps resident at once (the
 // launch is cooperative, so the runtime refuses a larger one), which the
 // barrier needs, nor the largest phase (more blocks would only wait).
-#include "dslash_impl.h"
+#include "hop_rhs.h"
 #include "site_ops.h"
 
 namespace lqcd {
@@ -38,13 +38,19 @@ namespace {
 
 // Block routines a phase may run (the ones of the mixed FP32/12-inner,
 // FP64/18-outer CGNR iteration on several right-hand sides).
-__device__ __forceinline__ void run_routine(int routine, const void* tab, int s, int bx, int by)
+// links: LDS of the hops' link tiles, shared by the storages.
+union PersistLds {
+    RhsLinks<64, 18> l64;
+    RhsLinks<32, 12> l32;
+};
+
+__device__ __forceinline__ void run_routine(int routine, const void* tab, int s, int bx, int by, PersistLds& lds)
 {
     switch (routine) {
 #define LQCD_PHOP(ID, P, RC, DG, RD)                                                    \
     case ID: {                                                                          \
         const DslashArgs& a = static_cast<const DslashArgs*>(tab)[s];                   \
-        if (bx < a.gx) dslash_block<P, RC, DG, RD, 1, false>(a, bx, a.gx, by);          \
+        if (bx < a.gx) rhs_block<P, RC, DG, RD>(a, bx, lds.l##P);                       \
         break;                                                                          \
     }
         LQCD_PHOP(PR_HOP32_12_D0_NONE, 32, 12, false, RED_NONE)
@@ -82,14 +88,14 @@ __device__ __forceinline__ void run_routine(int routine, const void* tab, int s,
 }
 
 // The blocks of one step: virtual block v = x + total * y over all systems.
-__device__ void run_step(const PStep& st, int nsys)
+__device__ void run_step(const PStep& st, int nsys, PersistLds& lds)
 {
     const int total = st.total * st.gy;
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int x = v % st.total, y = v / st.total;
         int s = 0;
         while (s + 1 < nsys && x >= st.offs[s + 1]) ++s;
-        run_routine(st.routine, st.tab, s, x - st.offs[s], y);
+        run_routine(st.routine, st.tab, s, x - st.offs[s], y, lds);
         __syncthreads();  // the block reductions' LDS is reused by the next virtual block
     }
 }
@@ -214,6 +220,7 @@ __device__ bool all_done(const PProgram& P)
 __global__ void __launch_bounds__(kPersistThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_batch_persistent(const PProgram* __restrict__ prog)
 {
+    __shared__ PersistLds lds;
     const PProgram& P = *prog;
     unsigned epoch = 0;
     for (int it = 0; it < P.max_iter; ++it) {
@@ -227,7 +234,7 @@ k_batch_persistent(const PProgram* __restrict__ prog)
                 if (!no_update) no_update = !any_active(P, PRED_UPDATE);
                 if (no_update) continue;
             }
-            run_step(st, P.nsys);
+            run_step(st, P.nsys, lds);
             if (!grid_sync(P, ++epoch)) return;
             if (st.nfin) {
                 run_finalize(st, P.nsys, P.nrhs);

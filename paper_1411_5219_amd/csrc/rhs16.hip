@@ -1,0 +1,12 @@
+// FP16-storage instantiations of the Dslash kernels on several right-hand sides.
+#include "hop_rhs.h"
+
+namespace lqcd {
+
+hipError_t launch_rhs_16(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
+{
+    if (recon == 12) return launch_rhs<16, 12>(dag, red, L, grid, block, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace lqcd

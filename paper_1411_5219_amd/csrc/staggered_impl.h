@@ -64,14 +64,21 @@ struct StagRedN {
 };
 
 template <int PREC, int RECON, int RED, bool LNT>
-__device__ __forceinline__ void stag_block(const DslashArgs& a, int bx, int nbx, int by)
+__device__ __forceinline__ void stag_block(const DslashArgs& a, int bx)
 {
     using R = typename ColourIO<PREC>::R;
     constexpr int N = StagRedN<RED>::N;
-    const BlockPos bp = block_pos(a, bx, nbx, by);
-    const int p = bp.p, rhs = bp.tile;
-    if (rhs >= a.nrhs || pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
-    const SitePos sp = site_pos(a, bp.bid, p, (int)threadIdx.x);
+    uint32_t rhs, b;
+    if (!tile_block(a, bx, &rhs, &b)) return;
+    if (pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
+    int p = a.parity;
+    if (a.full) {  // both parities in one launch, adjacent in the block order: the second finds the links in L2
+        p = (int)(b & 1u);
+        b >>= 1;
+    }
+    const int64_t poff = a.full ? p * a.par_bytes : 0, ioff = a.full ? (1 - p) * a.par_bytes : 0;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const SitePos sp = chunk_site(a.ch, a.g.Lxh, a.g.L[1], a.g.L[2], a.g.Vh, b, wave, p, (int)threadIdx.x & 63);
     const int64_t S = a.g.S;
     double tot[N];
 #pragma unroll
@@ -79,7 +86,7 @@ __device__ __forceinline__ void stag_block(const DslashArgs& a, int bx, int nbx,
 
     if (sp.valid) {
         const SiteGeo geo = site_geo(a.g, sp, p);
-        const char* in = static_cast<const char*>(a.in) + (int64_t)rhs * a.st_in + bp.ioff;
+        const char* in = static_cast<const char*>(a.in) + (int64_t)rhs * a.st_in + ioff;
         const cplx<R> ph[4] = {{R(a.g.ph[0][0]), R(a.g.ph[0][1])},
                                {R(a.g.ph[1][0]), R(a.g.ph[1][1])},
                                {R(a.g.ph[2][0]), R(a.g.ph[2][1])},
@@ -107,18 +114,18 @@ __device__ __forceinline__ void stag_block(const DslashArgs& a, int bx, int nbx,
         Colour<R> st;
         if (a.site) {
             const cplx<R> ca = {R(a.a.up[0]), R(a.a.up[1])};
-            ColourIO<PREC>::load(static_cast<const char*>(a.site) + rhs * a.st_site + bp.poff, S, sp.h, st);
+            ColourIO<PREC>::load(static_cast<const char*>(a.site) + rhs * a.st_site + poff, S, sp.h, st);
 #pragma unroll
             for (int c = 0; c < 3; ++c) o.c[c] = o.c[c] + ca * st.c[c];
         }
         if (a.add) {
             Colour<R> ad;
-            ColourIO<PREC>::load(static_cast<const char*>(a.add) + rhs * a.st_add + bp.poff, S, sp.h, ad);
+            ColourIO<PREC>::load(static_cast<const char*>(a.add) + rhs * a.st_add + poff, S, sp.h, ad);
 #pragma unroll
             for (int c = 0; c < 3; ++c) o.c[c] = o.c[c] + ad.c[c];
         }
         if (a.out)
-            ColourIO<PREC>::template store<LQCD_OUT_AUX>(static_cast<char*>(a.out) + rhs * a.st_out + bp.poff, S,
+            ColourIO<PREC>::template store<LQCD_OUT_AUX>(static_cast<char*>(a.out) + rhs * a.st_out + poff, S,
                                                         sp.h, o);
         if (RED == RED_NORM || RED == RED_NORM_DS) {
 #pragma unroll
@@ -133,13 +140,13 @@ __device__ __forceinline__ void stag_block(const DslashArgs& a, int bx, int nbx,
             }
         }
     }
-    if (RED != RED_NONE) block_reduce_store<N>(tot, a.r.partials + ((int64_t)rhs * bp.nslots) * N, bp.pslot);
+    if (RED != RED_NONE) block_reduce_store<N>(tot, a.r.partials + (int64_t)rhs * a.ch.nblk * N, (int)b + p * (a.full ? a.ch.nsp : 0));
 }
 
 template <int PREC, int RECON, int RED, bool LNT>
 __global__ void __launch_bounds__(256) k_stag_eo(const DslashArgs a)
 {
-    stag_block<PREC, RECON, RED, LNT>(a, blockIdx.x, gridDim.x, blockIdx.y);
+    stag_block<PREC, RECON, RED, LNT>(a, blockIdx.x);
 }
 
 template <int PREC, int RECON, int RED, bool LNT>
