@@ -386,6 +386,13 @@ struct Op {
     RedScratch rs;
     Launch dcfg, bcfg;
     int form = FORM_BY_SIZE;
+    // a scalar step its reductions' finalize runs first (see RedArgs)
+    const double* pre_partials = nullptr;
+    int pre_slots = 0, pre_fin = FIN_NONE;
+    // where RED_NORM_LOW puts the result
+    void* low = nullptr;
+    int low_prec = 0;
+    int64_t st_low = 0;
 
     void tune()
     {
@@ -403,8 +410,20 @@ struct Op {
         a.par_bytes = pb;
         a.r.partials = rs.partials;
         a.r.capacity = rs.capacity;
+        a.r.pre_partials = pre_partials;
+        a.r.pre_slots = pre_slots;
+        a.r.pre_fin = pre_fin;
         a.ctl = rs.ctl;
         return a;
+    }
+
+    // Partial sums per right-hand side of ||Mhat x||^2 (full: ||M x||^2), 0: not planned.
+    int norm_slots(bool full) const
+    {
+        DslashArgs a = base();
+        a.full = full;
+        DslashPlan p;
+        return plan_dslash(prec, recon, false, RED_NORM, a, nrhs, dcfg, &p) == hipSuccess ? p.slots : 0;
     }
 
     // out(parity p) = add + a * site + c * H_{p,1-p} in     (dag: H^+)
@@ -474,6 +493,9 @@ struct Op {
         b.add = add;
         b.st_add = st_add >= 0 ? st_add : pb;
         b.aux = aux;
+        b.low = low;
+        b.low_prec = low_prec;
+        b.st_low = st_low;
         b.a = coef_A(kappa, mu, dag, sgn);
         b.c = coef_real(-sgn * kappa * kappa);
         b.r.fin = fin;
@@ -537,6 +559,14 @@ int pinned_ctl(Ctl** out)
 }
 
 enum Method { M_CG = 0, M_BICG = 1 };
+
+// Most bytes of partials the blocks of an iteration's folded scalar steps read
+// together (see CgSystem::can_fold).  Solves folded against launches of their
+// own: 12^3x4 FP64 (0.1 MB) 1.97 ms against 2.31, 24^3x8 FP32 inner 5.31 against
+// 5.80, 20^3x8 FP32 inner with twelve right-hand sides (18 MB) 15.2 against
+// 15.6, 36^3x8 FP64 (38 MB) 21.7 against 22.0, 40^3x8 FP16 inner (72 MB) 10.6
+// against 10.8; 32^3x8 FP32 inner with sixteen (400 MB) 55.0 against 54.4.
+constexpr int64_t kFoldBytes = (int64_t)128 << 20;
 
 // Defaults of the stagnation handling of mixed-precision solves.
 constexpr int kDefaultStagWindow = 500;   // iterations without a reliable update
@@ -884,8 +914,15 @@ struct CgSystem {
     int64_t pb = 0, fb = 0;
     char* bc = nullptr;
     char* xc = nullptr;
-    void *r = nullptr, *p = nullptr, *w = nullptr, *z = nullptr, *t = nullptr, *bhat = nullptr;  // FP64
-    void *t64 = nullptr, *xl = nullptr, *rl = nullptr, *pl = nullptr, *wl = nullptr, *zl = nullptr, *tl = nullptr;
+    void *r = nullptr, *p = nullptr, *w = nullptr, *z = nullptr, *t = nullptr, *bhat = nullptr;
+    void *t64 = nullptr, *xl = nullptr;  // mixed: r, p, w, z, t are the low-precision vectors
+    // The iteration (see plan_iteration): its operator, in the first half (w =
+    // Op p) and the second (z = Op^+ r), and the FP64 residual of an update.
+    Op h1, h2, hu;
+    bool folded = false;
+    Ctl *ctl0 = nullptr, *ctl1 = nullptr, *ctl2 = nullptr;
+    double *part = nullptr, *part_r = nullptr, *part_u = nullptr;
+    int slots = 0, slots_r = 0, slots_u = 0;
 
     int init(const Geom& g, const lqcd_op* opi, const void* U, const void* b, void* x, const lqcd_solve_params* prm_,
              const SolverPlan& plan, hipStream_t s, BatchForms forms = {FORM_BY_SIZE, FORM_BY_SIZE})
@@ -912,8 +949,8 @@ struct CgSystem {
         fb = 2 * pb;
         bc = static_cast<char*>(const_cast<void*>(b));
         xc = static_cast<char*>(x);
-        r = sp.v[0];
         if (!mixed) {
+            r = sp.v[0];
             p = sp.v[1];
             w = sp.v[2];
             z = sp.v[3];
@@ -930,13 +967,78 @@ struct CgSystem {
             lo.form = forms.inner;
             lo.tune();
             xl = sp.lo[0];
-            rl = sp.lo[1];
-            pl = sp.lo[2];
-            wl = sp.lo[3];
-            zl = sp.lo[4];
-            tl = sp.lo[5];
+            r = sp.lo[1];
+            p = sp.lo[2];
+            w = sp.lo[3];
+            z = sp.lo[4];
+            t = sp.lo[5];
         }
+        plan_iteration(can_fold());
         return LQCD_OK;
+    }
+
+    // The operator of the iteration, and its vectors' stride between right-hand sides.
+    const Op& inner() const { return mixed ? lo : o; }
+    // Blocks per right-hand side of a BLAS step on the iteration's vectors.
+    int64_t blas_blocks() const
+    {
+        const int64_t b = inner().bcfg.block;
+        return nsub * ((o.g.Vh + b - 1) / b);
+    }
+    // Whether the iteration's scalar steps run inside the kernels that need
+    // their results (CtlFold) rather than as launches of their own.  Each of
+    // those kernels' blocks then reads all the partials, which pays while that
+    // is little beside a launch.
+    bool can_fold() const
+    {
+        // the two copies of the control blocks live in partials no step uses
+        const int64_t region = sizeof(double) * (int64_t)sp.rs.capacity * nrhs;
+        if (region < (int64_t)sizeof(Ctl) * nrhs) return false;
+        const int64_t n = inner().norm_slots(!eo), b = blas_blocks();
+        const int64_t pre = mixed ? o.norm_slots(false) : b;
+        return n > 0 && (int64_t)sizeof(double) * nrhs * b * (2 * n + pre) <= kFoldBytes;
+    }
+    // Launches of one iteration.  The scalar steps are alpha (from ||w||^2), rr
+    // (||r||^2: convergence, or a reliable update), the update's own test and
+    // beta (||z||^2).  Only beta is needed by what follows z = Op^+ r, so the
+    // plain solve runs rr with beta, and a mixed one the update's test: the two
+    // hops of a last iteration are wasted once per solve, and every iteration
+    // saves a launch of 4.7 us.
+    //   folded: w = Op p | alpha; r -= alpha w | [mixed: rr; x_e += x_low + alpha p | residual |] z = Op^+ r |
+    //           rr or the update's test, beta; x += alpha p, p = z + beta p
+    //   else:   the same with a launch for alpha, [mixed: rr] and (rr or the update's test, beta).
+    // A folded step reads one copy of the control blocks and writes another:
+    // alpha 0 -> 1, [mixed: rr 1 -> 2], beta -> 0.
+    void plan_iteration(bool fold)
+    {
+        folded = fold;
+        const int64_t region = (int64_t)sp.rs.capacity * nrhs;
+        part = sp.rs.partials;
+        part_r = part + region;
+        part_u = part + 2 * region;
+        ctl0 = ctl1 = ctl2 = sp.rs.ctl;
+        if (folded) {
+            ctl1 = reinterpret_cast<Ctl*>(part + 3 * region);
+            ctl2 = mixed ? reinterpret_cast<Ctl*>(part + 4 * region) : ctl1;
+        }
+        slots = inner().norm_slots(!eo);
+        slots_r = (int)blas_blocks();
+        slots_u = mixed ? o.norm_slots(false) : 0;
+        h1 = h2 = inner();
+        h2.rs.ctl = ctl2;
+        if (!folded) {
+            h2.pre_partials = mixed ? part_u : part_r;
+            h2.pre_slots = mixed ? slots_u : slots_r;
+            h2.pre_fin = mixed ? FIN_RU_RR : FIN_CG_RR;
+        }
+        hu = o;
+        hu.rs.ctl = ctl2;
+        hu.rs.partials = part_u;
+        if (mixed) {
+            hu.low = r;
+            hu.low_prec = lo.prec;
+            hu.st_low = lo.pb;
+        }
     }
 
     int setup(bool allow_fallback = false)
@@ -957,49 +1059,23 @@ struct CgSystem {
         lo.prec = 32;
         lo.pb = parity_bytes(o.g, 32);
         lo.tune();
+        plan_iteration(can_fold());
         LQCD_K(launch_convert_gauge(lo.prec, lo.recon, o.g, o.U, o.recon, sp.Ulo, o.s));
         return LQCD_OK;
     }
 
-    // x_e / x as the first operand of a BLAS step (full field stride)
-    hipError_t blas_x(int op, int pred, int fin, void* X, void* Y, void* Z, void* W) const
-    {
-        BlasArgs a = o.blas_base(nsub);
-        a.pred = pred;
-        a.x = X;
-        a.y = Y;
-        a.z = Z;
-        a.w = W;
-        a.st_x = fb;
-        a.r.fin = fin;
-        return launch_blas(64, op, a, nrhs, o.bcfg, o.s);
-    }
     // r = rhs - Op x (rhs = bhat for even-odd, b for the full lattice), FP64
-    hipError_t residual(void* out, int red, int fin, int pred) const
+    hipError_t residual(const Op& op, void* out, int red, int fin, int pred) const
     {
-        if (eo) return o.schur(xc, out, mixed ? t64 : t, false, -1.0, bhat, red, fin, pred, nullptr, fb, pb);
-        return o.full_M(xc, out, false, -1.0, bc, red, fin, pred);
+        if (eo) return op.schur(xc, out, mixed ? t64 : t, false, -1.0, bhat, red, fin, pred, nullptr, fb, pb);
+        return op.full_M(xc, out, false, -1.0, bc, red, fin, pred);
     }
-    hipError_t apply(const void* in, void* out, bool dag, int red, int fin, int pred) const
+    hipError_t apply(const Op& op, const void* in, void* out, bool dag, int red, int fin, int pred) const
     {
-        if (eo) return o.schur(in, out, t, dag, 1.0, nullptr, red, fin, pred);
-        return o.full_M(in, out, dag, 1.0, nullptr, red, fin, pred);
+        if (eo) return op.schur(in, out, t, dag, 1.0, nullptr, red, fin, pred);
+        return op.full_M(in, out, dag, 1.0, nullptr, red, fin, pred);
     }
-    hipError_t to_low(void* dst, const void* src, int pred) const
-    {
-        ConvertArgs c{};
-        c.Vh = o.g.Vh;
-        c.S = o.g.S;
-        c.nsub = 1;
-        c.dst = dst;
-        c.src = const_cast<void*>(src);
-        c.rhs_stride_dst = lo.pb;
-        c.rhs_stride_src = pb;
-        c.pred = pred;
-        c.ctl = sp.rs.ctl;
-        return launch_convert(lo.prec, 64, c, nrhs, o.s);
-    }
-    hipError_t fold(int pred) const  // x_e += x_low ; x_low = 0
+    ConvertArgs fold_args(int pred) const  // x_e += x_low ; x_low = 0
     {
         ConvertArgs c{};
         c.Vh = o.g.Vh;
@@ -1012,45 +1088,80 @@ struct CgSystem {
         c.accumulate = 1;
         c.zero_src = 1;
         c.pred = pred;
-        c.ctl = sp.rs.ctl;
+        c.ctl = ctl0;
+        return c;
+    }
+    hipError_t fold(int pred) const { return launch_convert(64, lo.prec, fold_args(pred), nrhs, o.s); }
+
+    // r -= alpha w ; ||r||^2
+    hipError_t update_r() const
+    {
+        const Op& q = inner();
+        BlasArgs a = q.blas_base(nsub);
+        a.pred = PRED_ACTIVE;
+        a.z = r;
+        a.w = w;
+        a.r.partials = part_r;
+        a.r.fin = mixed && !folded ? FIN_CG_RR : FIN_NONE;
+        if (folded) a.fold = CtlFold{ctl1, part, slots, nullptr, 0, FIN_NONE};
+        return launch_blas(q.prec, BLAS_AXMY_NORM, a, nrhs, q.bcfg, q.s);
+    }
+    // a requested reliable update's x_e += x_low + alpha p ; x_low = 0
+    hipError_t update_x64() const
+    {
+        ConvertArgs c = fold_args(PRED_UPDATE);
+        c.accumulate = 2;
+        c.p = p;
+        c.rhs_stride_p = lo.pb;
+        c.ctl = ctl1;
+        if (folded) c.fold = CtlFold{ctl2, part_r, slots_r, nullptr, 0, FIN_NONE};
         return launch_convert(64, lo.prec, c, nrhs, o.s);
+    }
+    // x += alpha p ; p = z + beta p
+    hipError_t update_xp() const
+    {
+        const Op& q = inner();
+        BlasArgs a = q.blas_base(nsub);
+        a.pred = PRED_ACTIVE;
+        a.x = mixed ? xl : xc;
+        a.y = p;
+        a.z = z;
+        if (!mixed) a.st_x = fb;  // the even half of the caller's field with eo
+        a.ctl = ctl2;
+        if (folded)
+            a.fold = CtlFold{ctl0, part, slots, mixed ? part_u : part_r, mixed ? slots_u : slots_r,
+                             mixed ? FIN_RU_RR : FIN_CG_RR};
+        return launch_blas(q.prec, BLAS_CG_XP, a, nrhs, q.bcfg, q.s);
     }
 
     int start()
     {
         if (!mixed) {
             // r = rhs - Op x ; z = Op^+ r ; zz ; p = z
-            LQCD_K(residual(r, RED_NONE, FIN_STORE, PRED_ACTIVE));
-            LQCD_K(apply(r, z, true, RED_NORM, FIN_CG_ZZ, PRED_ACTIVE));
-            LQCD_K(o.blas(BLAS_COPY, nsub, PRED_ACTIVE, FIN_STORE, z, p));
-            return LQCD_OK;
+            LQCD_K(residual(o, r, RED_NONE, FIN_STORE, PRED_ACTIVE));
+        } else {
+            // r = bhat - Mhat x (in FP64, stored low) ; rr_max ; x_low = 0 ; z = Mhat^+ r ; p = z
+            Op first = hu;
+            first.rs = o.rs;
+            LQCD_K(residual(first, nullptr, RED_NORM_LOW, FIN_RR_INIT, PRED_ACTIVE));
+            LQCD_K(lo.blas(BLAS_ZERO, 1, PRED_ACTIVE, FIN_STORE, nullptr, xl));
         }
-        // r = bhat - Mhat x (FP64) ; rr_max ; r_low ; x_low = 0 ; z = Mhat^+ r_low ; p = z
-        LQCD_K(residual(r, RED_NORM, FIN_RR_INIT, PRED_ACTIVE));
-        LQCD_K(to_low(rl, r, PRED_ACTIVE));
-        LQCD_K(lo.blas(BLAS_ZERO, 1, PRED_ACTIVE, FIN_STORE, nullptr, xl));
-        LQCD_K(lo.schur(rl, zl, tl, true, 1.0, nullptr, RED_NORM, FIN_CG_ZZ, PRED_ACTIVE));
-        LQCD_K(lo.blas(BLAS_COPY, 1, PRED_ACTIVE, FIN_STORE, zl, pl));
+        LQCD_K(apply(inner(), r, z, true, RED_NORM, FIN_CG_ZZ, PRED_ACTIVE));
+        LQCD_K(inner().blas(BLAS_COPY, nsub, PRED_ACTIVE, FIN_STORE, z, p));
         return LQCD_OK;
     }
 
     int iter()
     {
-        if (!mixed) {
-            LQCD_K(apply(p, w, false, RED_NORM, FIN_CG_ALPHA, PRED_ACTIVE));
-            LQCD_K(blas_x(BLAS_CG_XR, PRED_ACTIVE, FIN_CG_RR, xc, p, r, w));
-            LQCD_K(apply(r, z, true, RED_NORM, FIN_CG_BETA, PRED_ACTIVE));
-            LQCD_K(o.blas(BLAS_CG_P, nsub, PRED_ACTIVE, FIN_STORE, nullptr, p, z));
-            return LQCD_OK;
+        LQCD_K(apply(h1, p, w, false, RED_NORM, folded ? FIN_NONE : FIN_CG_ALPHA, PRED_ACTIVE));
+        LQCD_K(update_r());
+        if (mixed) {
+            // reliable update (runs only when the rr step requested it)
+            LQCD_K(update_x64());
+            LQCD_K(residual(hu, nullptr, RED_NORM_LOW, FIN_NONE, PRED_UPDATE));
         }
-        LQCD_K(lo.schur(pl, wl, tl, false, 1.0, nullptr, RED_NORM, FIN_CG_ALPHA, PRED_ACTIVE));
-        LQCD_K(lo.blas(BLAS_CG_XR, 1, PRED_ACTIVE, FIN_CG_RR, xl, pl, rl, wl));
-        // reliable update (runs only when FIN_CG_RR requested it)
-        LQCD_K(fold(PRED_UPDATE));
-        LQCD_K(residual(r, RED_NORM, FIN_RU_RR, PRED_UPDATE));
-        LQCD_K(to_low(rl, r, PRED_UPDATE));
-        LQCD_K(lo.schur(rl, zl, tl, true, 1.0, nullptr, RED_NORM, FIN_CG_BETA, PRED_ACTIVE));
-        LQCD_K(lo.blas(BLAS_CG_P, 1, PRED_ACTIVE, FIN_STORE, nullptr, pl, zl));
+        LQCD_K(apply(h2, r, z, true, RED_NORM, folded ? FIN_NONE : FIN_CG_BETA, PRED_ACTIVE));
+        LQCD_K(update_xp());
         return LQCD_OK;
     }
 
@@ -1288,24 +1399,36 @@ int persist_routine(const std::vector<std::vector<Step>>& steps, size_t k)
     }
     if (st.kind == STEP_DSLASH) {
         const DslashPlan& d = st.d;
-        if (d.kind != PLAN_WILSON || d.split != 0 || (d.red != RED_NONE && d.red != RED_NORM)) return PR_NONE;
-        const bool norm = d.red == RED_NORM;
+        if (d.kind != PLAN_WILSON || d.split != 0 || (d.red != RED_NONE && d.red != RED_NORM && d.red != RED_NORM_LOW))
+            return PR_NONE;
+        const bool norm = d.red != RED_NONE;
         if (d.prec == 32 && d.recon == 12)
             return d.dag ? (norm ? PR_HOP32_12_D1_NORM : PR_HOP32_12_D1_NONE)
                          : (norm ? PR_HOP32_12_D0_NORM : PR_HOP32_12_D0_NONE);
-        if (d.prec == 64 && d.recon == 18 && !d.dag) return norm ? PR_HOP64_18_D0_NORM : PR_HOP64_18_D0_NONE;
+        if (d.prec == 64 && d.recon == 18 && !d.dag && d.red != RED_NORM)
+            return norm ? PR_HOP64_18_D0_NORM_LOW : PR_HOP64_18_D0_NONE;
         return PR_NONE;
     }
     if (st.kind == STEP_BLAS) {
         if (st.b.prec != 32 || st.b.a.kind != KIND_SPINOR) return PR_NONE;
-        if (st.b.op == BLAS_CG_XR) return PR_BLAS32_CG_XR;
-        if (st.b.op == BLAS_CG_P) return PR_BLAS32_CG_P;
+        if (st.b.op == BLAS_AXMY_NORM) return PR_BLAS32_AXMY;
+        if (st.b.op == BLAS_CG_XP) return PR_BLAS32_CG_XP;
         return PR_NONE;
     }
-    if (st.c.pd == 64 && st.c.ps == 32 && st.c.a.accumulate) return PR_CONV64_32_ACC;
-    if (st.c.pd == 32 && st.c.ps == 64 && !st.c.a.accumulate) return PR_CONV32_64;
-    return PR_NONE;
+    return st.c.pd == 64 && st.c.ps == 32 && st.c.a.accumulate == 2 ? PR_CONV64_32_ACC : PR_NONE;
 }
+
+// The systems of a batch run one program: scalar steps are folded if every
+// system's can be (the persistent kernel has phases for them).
+void plan_batch_iteration(std::vector<CgSystem>& sys, const lqcd_solve_params* prm)
+{
+    bool fold = !prm->persistent;
+    for (const CgSystem& c : sys) fold = fold && c.can_fold();
+    for (CgSystem& c : sys) c.plan_iteration(fold);
+}
+
+static_assert(kMaxSys * (std::max({sizeof(DslashArgs), sizeof(BlasArgs), sizeof(ConvertArgs)}) + sizeof(FinArgs) +
+                         sizeof(int)) + 1024 <= kStepTableBytes, "a step's tables hold every system");
 
 struct BatchLayout {
     Ctl* ctl = nullptr;               // nsys x kMaxRhs control blocks
@@ -1389,11 +1512,11 @@ struct BatchProgram {
                 if (kind == STEP_DSLASH) {
                     std::memcpy(h + i * argsz, &st.d.a, argsz);
                     gx = (int)st.d.grid.x;
-                    f[i] = FinArgs{st.d.a.r.partials, st.d.slots, st.d.a.r.fin, st.d.a.ctl, st.d.a.pred};
+                    f[i] = fin_args(st.d.a.r, st.d.slots, st.d.a.ctl, st.d.a.pred);
                 } else if (kind == STEP_BLAS) {
                     std::memcpy(h + i * argsz, &st.b.a, argsz);
                     gx = (int)st.b.grid.x;
-                    f[i] = FinArgs{st.b.a.r.partials, st.b.slots, st.b.a.r.fin, st.b.a.ctl, st.b.a.pred};
+                    f[i] = fin_args(st.b.a.r, st.b.slots, st.b.a.ctl, st.b.a.pred);
                 } else {
                     std::memcpy(h + i * argsz, &st.c.a, argsz);
                     gx = (int)st.c.grid.x;
@@ -1514,6 +1637,7 @@ int solve_batch(int nsys, const lqcd_geom* geoms, const lqcd_op* ops, const void
         if ((rc = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st, forms))) return rc;
         if ((rc = sys[s].setup())) return rc;
     }
+    plan_batch_iteration(sys, prm);
     // record one iteration per system and zip the recordings into batched launches
     std::vector<Recorder> rec(nsys);
     for (int s = 0; s < nsys; ++s) {
@@ -1693,6 +1817,7 @@ int autotune_batch(int nsys, const lqcd_geom* geoms, const lqcd_op* ops, const v
             if ((result = sys[s].init(g[s], &ops[s], U[s], b[s], x[s], prm, L.plans[s], st, forms))) break;
             result = sys[s].setup();
         }
+        if (!result) plan_batch_iteration(sys, prm);
         std::vector<Recorder> rec(nsys);
         for (int s = 0; s < nsys && !result; ++s) {
             set_recorder(&rec[s]);
@@ -1853,6 +1978,13 @@ struct StagOp {
         return a;
     }
 
+    // Partial sums of a parity's hop with RED_NORM_DS, 0: not planned.
+    int norm_ds_slots() const
+    {
+        DslashPlan p;
+        return plan_stag_hop(prec, recon, RED_NORM_DS, base(rs.ctl), nrhs, dcfg, &p) == hipSuccess ? p.slots : 0;
+    }
+
     // out(parity p) = add + a * site + c * sum_mu eta_mu [U in(x+mu) - U^+ in(x-mu)]
     hipError_t hop(int p, const void* in, void* out, double c, const void* site, double a, const void* add, int red,
                    int fin, int pred, Ctl* ctl) const
@@ -1897,9 +2029,7 @@ struct StagOp {
         return launch_stag(prec, recon, red, d, nrhs, dcfg, s);
     }
 
-    hipError_t blas(int op, int n, int pred, int fin, Ctl* ctl, void* x, int64_t st_x, void* y = nullptr,
-                    int64_t st_y = 0, void* z = nullptr, int64_t st_z = 0, void* w = nullptr, int64_t st_w = 0,
-                    int nsub = 1) const
+    BlasArgs blas_args(int nsub) const
     {
         BlasArgs a{};
         a.kind = KIND_COLOUR;
@@ -1907,17 +2037,20 @@ struct StagOp {
         a.S = g.S;
         a.nsub = nsub;
         a.sub_stride = pb;
+        a.r.partials = rs.partials;
+        a.r.capacity = rs.capacity;
+        return a;
+    }
+
+    hipError_t blas(int op, int n, int pred, int fin, Ctl* ctl, void* x, int64_t st_x, void* y = nullptr,
+                    int64_t st_y = 0, int nsub = 1) const
+    {
+        BlasArgs a = blas_args(nsub);
         a.pred = pred;
         a.x = x;
         a.y = y;
-        a.z = z;
-        a.w = w;
         a.st_x = st_x;
         a.st_y = st_y;
-        a.st_z = st_z;
-        a.st_w = st_w;
-        a.r.partials = rs.partials;
-        a.r.capacity = rs.capacity;
         a.r.fin = fin;
         a.ctl = ctl;
         return launch_blas(prec, op, a, n, bcfg, s);
@@ -1965,21 +2098,43 @@ int check_stag_params(const lqcd_solve_params* p)
 
 // The CG iteration on the base system (control block ctl + base) of the
 // shifted family (N + s_i), i < n, with x_i, p_i at stride pb:
-//   w = (N + s_base) p_base, alpha and every zeta_{k+1}, alpha_i  (FIN_MS_ALPHA)
-//   x_i += alpha_i p_i
-//   r -= alpha w, ||r||^2, beta, beta_i, zeta shift, convergence  (FIN_MS_BETA)
-//   p_i = zeta_i r + beta_i p_i
+//   w = (N + s_base) p_base
+//   alpha and every zeta_{k+1}, alpha_i (FIN_MS_ALPHA); r -= alpha w, ||r||^2
+//   beta, beta_i, zeta shift, convergence (FIN_MS_BETA); x_i += alpha_i p_i, p_i = zeta_i r + beta_i p_i
+// with the scalar steps folded into the updates (CtlFold, alpha: control
+// blocks ctl -> a copy, beta: back) where the partials that their blocks read
+// are few and the copy fits beside them, else as launches of their own.
 int stag_ms_iter(const StagOp& o, const StagPlan& sp, char* x, int n, int base, double s_base)
 {
     Ctl* ctl = sp.rs.ctl;
     char* p = static_cast<char*>(sp.p);
     const int64_t pb = o.pb;
-    LQCD_K(o.normal(p + base * pb, sp.w, sp.t, s_base, 1.0, nullptr, RED_NORM_DS, FIN_MS_ALPHA, PRED_ACTIVE,
-                    ctl + base));
-    LQCD_K(o.blas(BLAS_MS_AXPY, n, PRED_ACTIVE, FIN_STORE, ctl, x, pb, p, pb));
-    LQCD_K(o.blas(BLAS_AXMY_NORM, 1, PRED_ACTIVE, FIN_MS_BETA, ctl + base, nullptr, 0, nullptr, 0, sp.r, pb, sp.w,
-                  pb));
-    LQCD_K(o.blas(BLAS_MS_P, n, PRED_ACTIVE, FIN_STORE, ctl, nullptr, 0, p, pb, sp.r, 0));
+    const int64_t slots = o.norm_ds_slots(), blocks = (o.g.Vh + o.bcfg.block - 1) / o.bcfg.block;
+    double* part = sp.rs.partials;
+    const int64_t used = 3 * slots + blocks;  // doubles
+    const bool fold = slots > 0 && 8 * used + (int64_t)sizeof(Ctl) * n <= 8 * 3 * (int64_t)sp.rs.capacity &&
+                      8 * blocks * (3 * slots + blocks) <= kFoldBytes;
+    double* part_r = fold ? part + 3 * slots : part;
+    Ctl* ctl1 = fold ? reinterpret_cast<Ctl*>(part + used) : ctl;
+    LQCD_K(o.normal(p + base * pb, sp.w, sp.t, s_base, 1.0, nullptr, RED_NORM_DS, fold ? FIN_NONE : FIN_MS_ALPHA,
+                    PRED_ACTIVE, ctl + base));
+    BlasArgs a = o.blas_args(1);
+    a.pred = PRED_ACTIVE;
+    a.z = sp.r;
+    a.w = sp.w;
+    a.ctl = ctl + base;
+    a.fam_n = n;
+    a.fam_base = base;
+    a.r.partials = part_r;
+    a.r.fin = fold ? FIN_NONE : FIN_MS_BETA;
+    if (fold) a.fold = CtlFold{ctl1, part, (int)slots, nullptr, 0, FIN_NONE};
+    LQCD_K(launch_blas(o.prec, BLAS_AXMY_NORM, a, 1, o.bcfg, o.s));
+    a.x = x;
+    a.y = p;
+    a.st_x = a.st_y = pb;  // between the shifts
+    a.ctl = ctl1;
+    if (fold) a.fold = CtlFold{ctl, part_r, (int)blocks, nullptr, 0, FIN_NONE};
+    LQCD_K(launch_blas(o.prec, BLAS_MS_XP, a, 1, o.bcfg, o.s));
     return LQCD_OK;
 }
 
@@ -2693,8 +2848,7 @@ int stag_cg_solve(const lqcd_geom* geom, const lqcd_stag_op* op, const void* U, 
     LQCD_K(launch_ctl_init(ctl, 1, prm->tol * m, 0.0, prm->maxiter, o.s));
     ShiftList sl{};
     LQCD_K(launch_ctl_init_shifts(ctl, 1, 0, sl, o.s));
-    LQCD_K(o.blas(BLAS_NORM, 1, PRED_ALWAYS, FIN_BB_FULL, ctl, const_cast<char*>(bc), 2 * pb, nullptr, 0, nullptr, 0,
-                  nullptr, 0, 2));
+    LQCD_K(o.blas(BLAS_NORM, 1, PRED_ALWAYS, FIN_BB_FULL, ctl, const_cast<char*>(bc), 2 * pb, nullptr, 0, 2));
     // bhat = m b_e - D_eo b_o ; x_e = 0
     LQCD_K(o.hop(0, bc + pb, sp.bhat, -0.5, bc, m, nullptr, RED_NONE, FIN_STORE, PRED_ALWAYS, ctl));
     LQCD_K(o.blas(BLAS_ZERO, 1, PRED_ALWAYS, FIN_STORE, ctl, nullptr, 0, xc, 2 * pb));

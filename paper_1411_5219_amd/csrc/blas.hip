@@ -55,8 +55,8 @@ static hipError_t blas_op(int op, const BlasLaunch& L, dim3 grid, dim3 block, hi
 {
     if constexpr (KIND == KIND_SPINOR) {
         switch (op) {
-            LQCD_BLAS_CASE(BLAS_CG_XR)
-            LQCD_BLAS_CASE(BLAS_CG_P)
+            LQCD_BLAS_CASE(BLAS_CG_XP)
+            LQCD_BLAS_CASE(BLAS_AXMY_NORM)
             LQCD_BLAS_CASE(BLAS_COPY)
             LQCD_BLAS_CASE(BLAS_ZERO)
             LQCD_BLAS_CASE(BLAS_SPIN_SCALE)
@@ -78,15 +78,12 @@ static hipError_t blas_op(int op, const BlasLaunch& L, dim3 grid, dim3 block, hi
     } else {
         // colour vectors: what the staggered CG and multi-shift CG use
         switch (op) {
-            LQCD_BLAS_CASE(BLAS_CG_XR)
-            LQCD_BLAS_CASE(BLAS_CG_P)
             LQCD_BLAS_CASE(BLAS_COPY)
             LQCD_BLAS_CASE(BLAS_ZERO)
             LQCD_BLAS_CASE(BLAS_SPIN_SCALE)
             LQCD_BLAS_CASE(BLAS_NORM)
             LQCD_BLAS_CASE(BLAS_XPY)
-            LQCD_BLAS_CASE(BLAS_MS_AXPY)
-            LQCD_BLAS_CASE(BLAS_MS_P)
+            LQCD_BLAS_CASE(BLAS_MS_XP)
             LQCD_BLAS_CASE(BLAS_AXMY_NORM)
         default: return hipErrorInvalidValue;
         }
@@ -120,12 +117,13 @@ hipError_t plan_blas(int prec, int op, const BlasArgs& a, int nrhs, const Launch
     p.grid = dim3(nbs * a.nsub, nrhs);
     p.a.gx = (int)p.grid.x;
     p.block = dim3(blk);
-    p.nfin = (op == BLAS_CG_XR || op == BLAS_NORM || op == BLAS_AXMY_NORM)                       ? 1
+    p.nfin = (op == BLAS_NORM || op == BLAS_AXMY_NORM)                                           ? 1
              : (op == BLAS_BI_XR || op == BLAS_NORM_DOT || op == BLAS_BL_ORTH || op == BLAS_BL_MR) ? 3
              : op == BLAS_BL_GRAM                                                                 ? 5
                                                                                                   : 0;
     p.slots = (int)p.grid.x;
     if (p.nfin && p.slots > a.r.capacity) return hipErrorInvalidValue;  // partials too small
+    if (a.r.fin == FIN_NONE) p.nfin = 0;
     return hipSuccess;
 }
 
@@ -134,7 +132,7 @@ hipError_t exec_blas(const BlasPlan& p, hipStream_t s)
     BlasLaunch L{&p.a, nullptr, nullptr, 1};
     const hipError_t e = blas_prec(p.prec, p.a.kind, p.op, L, p.grid, p.block, s);
     if (e != hipSuccess || p.nfin == 0) return e;
-    return launch_finalize(p.nfin, p.a.r.partials, p.slots, p.a.r.fin, p.a.ctl, p.a.pred, p.nrhs, s);
+    return launch_finalize(p.nfin, fin_args(p.a.r, p.slots, p.a.ctl, p.a.pred), p.nrhs, s);
 }
 
 hipError_t exec_blas_batch(const BlasPlan* plans, int n, const BlasArgs* tab, const int* offs, int total_blocks,
@@ -167,23 +165,9 @@ Recorder* active_recorder() { return g_recorder; }
 void set_recorder(Recorder* r) { g_recorder = r; }
 
 template <int N>
-__global__ void __launch_bounds__(kFinThreads) k_finalize(const double* partials, int nblocks, int count, int fin,
-                                                          Ctl* ctl, int pred)
+__global__ void __launch_bounds__(kFinThreads) k_finalize(const FinArgs f, int count)
 {
-    const int rhs = blockIdx.x;
-    Ctl* c = ctl + rhs;
-    if (pred_skip(pred, c)) return;
-    double v[N];
-    sum_partials<N>(partials + (int64_t)rhs * nblocks * N, count, v);
-    __shared__ double tot[N];
-    block_reduce_store<N>(v, tot, 0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) t[j] = tot[j];
-        finalize<N>(fin, c, t);
-    }
+    finalize_block<N>(f, blockIdx.x, count);
 }
 
 // One block per (system, right-hand side): the finalize of every system of a batched launch.
@@ -191,20 +175,7 @@ template <int N>
 __global__ void __launch_bounds__(kFinThreads) k_finalize_batch(const FinArgs* __restrict__ tab, int nrhs)
 {
     const FinArgs& f = tab[blockIdx.x / nrhs];
-    const int rhs = blockIdx.x % nrhs;
-    Ctl* c = f.ctl + rhs;
-    if (pred_skip(f.pred, c)) return;
-    double v[N];
-    sum_partials<N>(f.partials + (int64_t)rhs * f.nblocks * N, f.nblocks, v);
-    __shared__ double tot[N];
-    block_reduce_store<N>(v, tot, 0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) t[j] = tot[j];
-        finalize<N>(f.fin, c, t);
-    }
+    finalize_block<N>(f, blockIdx.x % nrhs, f.nblocks);
 }
 
 hipError_t launch_finalize_batch(int N, const FinArgs* tab, int nsys, int nrhs, hipStream_t s)
@@ -218,16 +189,15 @@ hipError_t launch_finalize_batch(int N, const FinArgs* tab, int nsys, int nrhs, 
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(int N, const double* partials, int nblocks, int fin, Ctl* ctl, int pred, int nrhs,
-                           hipStream_t s, int count)
+hipError_t launch_finalize(int N, const FinArgs& f, int nrhs, hipStream_t s, int count)
 {
-    if (!ctl) return hipErrorInvalidValue;
-    if (count < 0 || count > nblocks) count = nblocks;
+    if (!f.ctl) return hipErrorInvalidValue;
+    if (count < 0 || count > f.nblocks) count = f.nblocks;
     dim3 g(nrhs), b(kFinThreads);
-    if (N == 1) hipLaunchKernelGGL(k_finalize<1>, g, b, 0, s, partials, nblocks, count, fin, ctl, pred);
-    else if (N == 2) hipLaunchKernelGGL(k_finalize<2>, g, b, 0, s, partials, nblocks, count, fin, ctl, pred);
-    else if (N == 3) hipLaunchKernelGGL(k_finalize<3>, g, b, 0, s, partials, nblocks, count, fin, ctl, pred);
-    else if (N == 5) hipLaunchKernelGGL(k_finalize<5>, g, b, 0, s, partials, nblocks, count, fin, ctl, pred);
+    if (N == 1) hipLaunchKernelGGL(k_finalize<1>, g, b, 0, s, f, count);
+    else if (N == 2) hipLaunchKernelGGL(k_finalize<2>, g, b, 0, s, f, count);
+    else if (N == 3) hipLaunchKernelGGL(k_finalize<3>, g, b, 0, s, f, count);
+    else if (N == 5) hipLaunchKernelGGL(k_finalize<5>, g, b, 0, s, f, count);
     else return hipErrorInvalidValue;
     return hipGetLastError();
 }
@@ -235,13 +205,13 @@ hipError_t launch_finalize(int N, const double* partials, int nblocks, int fin, 
 // ---------------------------------------------------------------------------
 // Precision conversion
 
-template <int PD, int PS, bool ACC>
+template <int PD, int PS, int ACC>
 __global__ void __launch_bounds__(256) k_convert(const ConvertArgs a)
 {
     convert_block<PD, PS, ACC>(a, blockIdx.x, gridDim.x, blockIdx.y);
 }
 
-template <int PD, int PS, bool ACC>
+template <int PD, int PS, int ACC>
 __global__ void __launch_bounds__(256) k_convert_batch(const ConvertArgs* __restrict__ tab,
                                                       const int* __restrict__ offs, int nsys)
 {
@@ -260,7 +230,7 @@ struct ConvertLaunch {
     int nsys;
 };
 
-template <int PD, int PS, bool ACC>
+template <int PD, int PS, int ACC>
 static hipError_t convert_one(const ConvertLaunch& L, dim3 g, dim3 b, hipStream_t s)
 {
     if (L.tab) hipLaunchKernelGGL((k_convert_batch<PD, PS, ACC>), g, b, 0, s, L.tab, L.offs, L.nsys);
@@ -268,26 +238,24 @@ static hipError_t convert_one(const ConvertLaunch& L, dim3 g, dim3 b, hipStream_
     return hipGetLastError();
 }
 
-template <int PD, int PS>
-static hipError_t convert2(bool acc, const ConvertLaunch& L, dim3 g, dim3 b, hipStream_t s)
+static hipError_t convert_any(int pd, int ps, int acc, const ConvertLaunch& L, dim3 g, dim3 b, hipStream_t s)
 {
-    return acc ? convert_one<PD, PS, true>(L, g, b, s) : convert_one<PD, PS, false>(L, g, b, s);
-}
-
-static hipError_t convert_any(int pd, int ps, bool acc, const ConvertLaunch& L, dim3 g, dim3 b, hipStream_t s)
-{
-    if (acc && pd != 64) return hipErrorInvalidValue;
-#define LQCD_CONV(D, S_)                               \
-    if (pd == D && ps == S_) return convert2<D, S_>(acc, L, g, b, s);
-    LQCD_CONV(64, 64)
-    LQCD_CONV(64, 32)
-    LQCD_CONV(64, 16)
-    LQCD_CONV(32, 64)
-    LQCD_CONV(32, 32)
-    LQCD_CONV(32, 16)
-    LQCD_CONV(16, 64)
-    LQCD_CONV(16, 32)
-    LQCD_CONV(16, 16)
+#define LQCD_CONV(D, S_, A) \
+    if (pd == D && ps == S_ && acc == A) return convert_one<D, S_, A>(L, g, b, s);
+    LQCD_CONV(64, 64, 0)
+    LQCD_CONV(64, 32, 0)
+    LQCD_CONV(64, 16, 0)
+    LQCD_CONV(32, 64, 0)
+    LQCD_CONV(32, 32, 0)
+    LQCD_CONV(32, 16, 0)
+    LQCD_CONV(16, 64, 0)
+    LQCD_CONV(16, 32, 0)
+    LQCD_CONV(16, 16, 0)
+    LQCD_CONV(64, 64, 1)
+    LQCD_CONV(64, 32, 1)
+    LQCD_CONV(64, 16, 1)
+    LQCD_CONV(64, 32, 2)
+    LQCD_CONV(64, 16, 2)
 #undef LQCD_CONV
     return hipErrorInvalidValue;
 }
@@ -295,7 +263,12 @@ static hipError_t convert_any(int pd, int ps, bool acc, const ConvertLaunch& L, 
 hipError_t plan_convert(int pd, int ps, const ConvertArgs& a, int nrhs, ConvertPlan* out)
 {
     const int blk = 256;
-    const unsigned nbs = (unsigned)((a.Vh + blk - 1) / blk);
+    unsigned nbs = (unsigned)((a.Vh + blk - 1) / blk);
+    if (a.accumulate == 2) {
+        if (a.nsub != 1) return hipErrorInvalidValue;
+        const unsigned most = (unsigned)(512 / nrhs > 0 ? 512 / nrhs : 1);
+        if (nbs > most) nbs = most;
+    }
     out->a = a;
     out->pd = pd;
     out->ps = ps;
@@ -308,7 +281,7 @@ hipError_t plan_convert(int pd, int ps, const ConvertArgs& a, int nrhs, ConvertP
 hipError_t exec_convert(const ConvertPlan& p, hipStream_t s)
 {
     ConvertLaunch L{&p.a, nullptr, nullptr, 1};
-    return convert_any(p.pd, p.ps, p.a.accumulate != 0, L, p.grid, p.block, s);
+    return convert_any(p.pd, p.ps, p.a.accumulate, L, p.grid, p.block, s);
 }
 
 hipError_t exec_convert_batch(const ConvertPlan* plans, int n, const ConvertArgs* tab, const int* offs,
@@ -317,7 +290,7 @@ hipError_t exec_convert_batch(const ConvertPlan* plans, int n, const ConvertArgs
     if (n < 1) return hipErrorInvalidValue;
     const ConvertPlan& p0 = plans[0];
     ConvertLaunch L{nullptr, tab, offs, n};
-    return convert_any(p0.pd, p0.ps, p0.a.accumulate != 0, L, dim3((unsigned)total_blocks, p0.grid.y), p0.block, s);
+    return convert_any(p0.pd, p0.ps, p0.a.accumulate, L, dim3((unsigned)total_blocks, p0.grid.y), p0.block, s);
 }
 
 hipError_t launch_convert(int pd, int ps, const ConvertArgs& a, int nrhs, hipStream_t s)

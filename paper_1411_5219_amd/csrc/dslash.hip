@@ -69,7 +69,7 @@ static void plan_chunks(const Launch& cfg, int maxsub, int tile, int nrhs, Dslas
 static hipError_t finish_plan(int red, DslashPlan* p)
 {
     if (red != RED_NONE && p->slots > p->a.r.capacity) return hipErrorInvalidValue;  // partials too small
-    p->nfin = red == RED_NONE ? 0 : red == RED_NORM ? 1 : red == RED_DOT_AUX ? 2 : 3;
+    p->nfin = red == RED_NONE || p->a.r.fin == FIN_NONE ? 0 : red == RED_NORM || red == RED_NORM_LOW ? 1 : red == RED_DOT_AUX ? 2 : 3;
     return hipSuccess;
 }
 
@@ -152,11 +152,13 @@ hipError_t exec_dslash(const DslashPlan& p, hipStream_t s)
     DslashLaunch L{&p.a, nullptr, nullptr, 1};
     const hipError_t e = launch_dslash_prec(p, L, p.grid, s);
     if (e != hipSuccess || p.nfin == 0) return e;
-    const hipError_t f = launch_finalize(p.nfin, p.a.r.partials, p.slots, p.a.r.fin, p.a.ctl, p.a.pred, p.a.nrhs, s);
+    FinArgs fa = fin_args(p.a.r, p.slots, p.a.ctl, p.a.pred);
+    const hipError_t f = launch_finalize(p.nfin, fa, p.a.nrhs, s);
     // both parities in one launch: the even-parity blocks hold the first half of the partials
     if (f != hipSuccess || !p.a.full || !p.a.r.fin_even) return f;
-    return launch_finalize(p.nfin, p.a.r.partials, p.slots, p.a.r.fin_even, p.a.ctl, p.a.pred, p.a.nrhs, s,
-                           p.slots / 2);
+    fa.fin = p.a.r.fin_even;
+    fa.pre_partials = nullptr;
+    return launch_finalize(p.nfin, fa, p.a.nrhs, s, p.slots / 2);
 }
 
 hipError_t exec_dslash_batch(const DslashPlan* plans, int n, const DslashArgs* tab, const int* offs, int total_blocks,
@@ -192,12 +194,12 @@ hipError_t launch_dslash(int prec, int recon, bool dagger, int red, const Dslash
     return exec_dslash(p, s);
 }
 
-hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
-                       hipStream_t s)
+hipError_t plan_stag_hop(int prec, int recon, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
+                         DslashPlan* out)
 {
     if (red != RED_NONE && red != RED_NORM && red != RED_NORM_DS) return hipErrorInvalidValue;
     if (!storage_built(prec, recon)) return hipErrorInvalidValue;
-    DslashPlan p;
+    DslashPlan& p = *out;
     p.kind = PLAN_STAG;
     p.prec = prec;
     p.recon = recon;
@@ -208,7 +210,14 @@ hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int
     p.lnt = nrhs == 1 && !args.full;
     plan_chunks(cfg, cfg.block / kChunk, 1, nrhs, &p);
     p.block = dim3((unsigned)(kChunk * p.a.ch.nsub));
-    const hipError_t e = finish_plan(red, &p);
+    return finish_plan(red, &p);
+}
+
+hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
+                       hipStream_t s)
+{
+    DslashPlan p;
+    const hipError_t e = plan_stag_hop(prec, recon, red, args, nrhs, cfg, &p);
     if (e != hipSuccess) return e;
     if (Recorder* r = active_recorder()) {
         r->steps.push_back(Step{});

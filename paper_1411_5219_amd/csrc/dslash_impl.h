@@ -359,7 +359,7 @@ struct HopPipe {
 
 template <int RED>
 struct RedN {
-    static constexpr int N = RED == RED_NONE ? 1 : RED == RED_NORM ? 1 : RED == RED_DOT_AUX ? 2 : 3;
+    static constexpr int N = RED == RED_NONE ? 1 : RED == RED_NORM || RED == RED_NORM_LOW ? 1 : RED == RED_DOT_AUX ? 2 : 3;
 };
 
 // out = add + a * site + c * acc of one right-hand side, with the sums of the reduction.
@@ -394,7 +394,19 @@ __device__ __forceinline__ void hop_store(const DslashArgs& a, int64_t rr, int64
     }
     if (!valid) return;
     if (a.out) SpinorIO<PREC>::template store<LQCD_OUT_AUX>(static_cast<char*>(a.out) + rr * a.st_out + poff, S, h, o);
-    if (RED == RED_NORM || RED == RED_NORM_DS) {
+    if constexpr (RED == RED_NORM_LOW) {
+        // the residual of a reliable update, in the storage of the inner solve
+        // (as a branch of RED_NORM it slowed every FP64 hop by 2%)
+        Spinor<float> f;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) f.s[s][c] = {(float)o.s[s][c].x, (float)o.s[s][c].y};
+        char* low = static_cast<char*>(a.low) + rr * a.st_low;
+        if (a.low_prec == 32) SpinorIO<32>::store(low, S, h, f);
+        else SpinorIO<16>::store(low, S, h, f);
+    }
+    if (RED == RED_NORM || RED == RED_NORM_DS || RED == RED_NORM_LOW) {
 #pragma unroll
         for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -519,9 +531,9 @@ k_dslash_eo_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ of
     const int x = blockIdx.x;
     int s = 0;
     while (s + 1 < nsys && x >= offs[s + 1]) ++s;
+    const int bx = x - offs[s];
     // each system's range starts at a multiple of 8 (XCD remap); blocks past
     // the system's own grid are padding
-    const int bx = x - offs[s];
     if (bx >= tab[s].gx) return;
     dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(tab[s], bx);
 }
@@ -544,8 +556,11 @@ static hipError_t launch_red(int red, const DslashLaunch& L, dim3 grid, dim3 blo
     case RED_NORM: return launch_one<PREC, RECON, DAG, RED_NORM, LNT, SPLIT>(L, grid, block, s);
     case RED_NORM_DS: return launch_one<PREC, RECON, DAG, RED_NORM_DS, LNT, SPLIT>(L, grid, block, s);
     case RED_DOT_AUX: return launch_one<PREC, RECON, DAG, RED_DOT_AUX, LNT, SPLIT>(L, grid, block, s);
-    default: return hipErrorInvalidValue;
+    default: break;
     }
+    if constexpr (PREC == 64 && !DAG)
+        if (red == RED_NORM_LOW) return launch_one<PREC, RECON, DAG, RED_NORM_LOW, LNT, SPLIT>(L, grid, block, s);
+    return hipErrorInvalidValue;
 }
 
 template <int PREC, int RECON, bool LNT, int SPLIT>

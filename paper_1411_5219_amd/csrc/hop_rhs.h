@@ -240,8 +240,11 @@ static hipError_t rhs_red(int red, const DslashLaunch& L, dim3 grid, dim3 block,
     case RED_NORM: return rhs_one<PREC, RECON, DAG, RED_NORM>(L, grid, block, s);
     case RED_NORM_DS: return rhs_one<PREC, RECON, DAG, RED_NORM_DS>(L, grid, block, s);
     case RED_DOT_AUX: return rhs_one<PREC, RECON, DAG, RED_DOT_AUX>(L, grid, block, s);
-    default: return hipErrorInvalidValue;
+    default: break;
     }
+    if constexpr (PREC == 64 && !DAG)
+        if (red == RED_NORM_LOW) return rhs_one<PREC, RECON, DAG, RED_NORM_LOW>(L, grid, block, s);
+    return hipErrorInvalidValue;
 }
 
 template <int PREC, int RECON>

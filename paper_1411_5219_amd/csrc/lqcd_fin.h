@@ -10,13 +10,38 @@
 
 namespace lqcd {
 
-template <int N>
-__device__ inline void finalize(int fin, Ctl* c, const double (&v)[N])
+// ctl_step by one wavefront (every lane holds the totals): lane 0, or for the
+// multi-shift steps one lane per shift (eight shifts in one lane took 2.5 us
+// longer).  The lanes run in step, so all have read the base system before its
+// own lane changes it.
+__device__ inline void ctl_step_wave(Ctl* c, int pre, const double* pv, int fin, const double* v,
+                                     bool always = false)
 {
-    double t[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int j = 0; j < N && j < 6; ++j) t[j] = v[j];
-    finalize_totals(fin, c, t);
+    static_assert(kMaxShifts <= 64, "one lane per shift");
+    const int lane = threadIdx.x;
+    if (fin != FIN_MS_ALPHA && fin != FIN_MS_BETA) {
+        if (lane == 0) ctl_step(c, pre, pv, fin, v, always);
+        return;
+    }
+    const int n = c->ms_n, mine = c->ms_index;
+    const bool open = always || !c->done;
+    Ctl* ci = c - mine + (lane < n ? lane : mine);
+    if (fin == FIN_MS_ALPHA) {
+        const MsAlpha m = ms_alpha(c, v[1]);
+        __builtin_amdgcn_wave_barrier();
+        if (!open || lane >= n) return;
+        ms_alpha_shift(ci, m);
+        if (lane == mine) c->alpha = m.al;
+    } else {
+        const MsBeta m = ms_beta(c, v[0]);
+        __builtin_amdgcn_wave_barrier();
+        if (lane >= n) return;
+        if (open) {
+            ms_beta_shift(ci, m);
+            if (lane == mine) ms_beta_base(c, m);
+        }
+        ctl_close(ci);
+    }
 }
 
 __device__ inline bool pred_skip(int pred, const Ctl* c)

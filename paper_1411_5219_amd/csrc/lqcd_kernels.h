@@ -32,7 +32,8 @@ struct SpinCoef {
 //   RED_NORM    : ||out||^2
 //   RED_NORM_DS : ||out||^2, <out, site>          (re, im)
 //   RED_DOT_AUX : <aux, out>                      (re, im)
-enum Red { RED_NONE = 0, RED_NORM = 1, RED_NORM_DS = 2, RED_DOT_AUX = 3 };
+//   RED_NORM_LOW: ||out||^2, and out is also stored at low_prec (FP64 Wilson hops)
+enum Red { RED_NONE = 0, RED_NORM = 1, RED_NORM_DS = 2, RED_DOT_AUX = 3, RED_NORM_LOW = 4 };
 
 // Predicates on the control block evaluated at the top of a kernel.
 enum Pred {
@@ -52,6 +53,21 @@ struct RedArgs {
     int capacity;           // blocks the partials hold per right-hand side (N <= kMaxFin)
     int fin;                // Fin
     int fin_even;           // full-lattice launches: a second Fin on the even-parity blocks' partials (0: none)
+    // a scalar step of an earlier launch run before fin (null: none): its partials, slots and Fin
+    const double* pre_partials;
+    int pre_slots, pre_fin;
+};
+
+// Scalar steps that the blocks of a consuming kernel run themselves instead of
+// a launch of their own: every block sums the partials in the same order, runs
+// the steps on its copy of the control block and goes on with the result;
+// block 0 writes it to out, a copy no block of the launch reads.
+struct CtlFold {
+    Ctl* out;               // per right-hand side; null: nothing folded, a.ctl is up to date
+    const double* partials; // [nrhs][slots][N]
+    int slots;
+    const double* pre_partials;  // [nrhs][pre_slots] (null: no first step)
+    int pre_slots, pre_fin;
 };
 
 // Dslash_eo with a fused epilogue:
@@ -67,9 +83,11 @@ struct DslashArgs {
     const void* add;
     const void* aux;
     const void* U;
+    void* low;              // RED_NORM_LOW
+    int low_prec;
     SpinCoef a, c;
     // bytes between right-hand sides of each field
-    int64_t st_in, st_out, st_site, st_add, st_aux;
+    int64_t st_in, st_out, st_site, st_add, st_aux, st_low;
     int full;               // 1: both parities in one launch (fields are full-lattice)
     int64_t par_bytes;      // bytes of one parity field (full = 1)
     RedArgs r;
@@ -105,12 +123,25 @@ enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3 };
 // not by size).  FORM_WAVE exists for FP64 on one right-hand side and one parity.
 int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want);
 
+// Finalize of one reduction of one system.
+struct FinArgs {
+    const double* partials;
+    int nblocks;
+    int fin;
+    Ctl* ctl;
+    int pred;
+    const double* pre_partials;  // as in RedArgs
+    int pre_slots, pre_fin;
+};
+inline FinArgs fin_args(const RedArgs& r, int slots, Ctl* ctl, int pred)
+{
+    return FinArgs{r.partials, slots, r.fin, ctl, pred, r.pre_partials, r.pre_slots, r.pre_fin};
+}
 // Sum N block partials per right-hand side in block order and run the
-// solver's scalar step (Fin) on the totals; one block per right-hand side.
+// solver's scalar steps on the totals; one block per right-hand side.
 // count < nblocks sums only the first count partials of each right-hand
 // side (nblocks stays the stride between right-hand sides).
-hipError_t launch_finalize(int N, const double* partials, int nblocks, int fin, Ctl* ctl, int pred, int nrhs,
-                           hipStream_t s, int count = -1);
+hipError_t launch_finalize(int N, const FinArgs& f, int nrhs, hipStream_t s, int count = -1);
 
 // ---- launchers (return hipError_t) ----
 hipError_t launch_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& a, int nrhs,
@@ -130,15 +161,6 @@ struct DslashLaunch {
     int nsys;
 };
 
-// Finalize of one reduction of one system (batched finalize tables).
-struct FinArgs {
-    const double* partials;
-    int nblocks;
-    int fin;
-    Ctl* ctl;
-    int pred;
-};
-
 // A planned Dslash launch (final arguments, grid, kernel selectors).
 // Stencil of a planned hop launch.
 enum PlanKind { PLAN_WILSON = 0, PLAN_STAG = 1 };
@@ -156,6 +178,8 @@ struct DslashPlan {
 };
 hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
                        DslashPlan* out);
+hipError_t plan_stag_hop(int prec, int recon, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
+                         DslashPlan* out);
 hipError_t exec_dslash(const DslashPlan& p, hipStream_t s);
 // plans[0..n) share kernel selectors; tab / offs / fin_tab are their device
 // tables (arguments, block offsets with offs[n] = total_blocks, finalizes).
@@ -165,8 +189,7 @@ hipError_t launch_finalize_batch(int N, const FinArgs* tab, int nsys, int nrhs, 
 
 // Site-local BLAS-1 on parity fields of precision prec (all operands the same).
 enum Blas {
-    BLAS_CG_XR = 0,       // x += alpha p; r -= alpha w;           red ||r||^2
-    BLAS_CG_P = 1,        // p = z + beta p
+    BLAS_CG_XP = 1,       // x += alpha p (while xdo); p = z + beta p (while not done)
     BLAS_COPY = 2,        // y = x
     BLAS_ZERO = 3,        // y = 0
     BLAS_SPIN_SCALE = 4,  // y = coef * x                          (spin-block coefficient)
@@ -176,8 +199,7 @@ enum Blas {
     BLAS_BI_XR = 8,       // x += alpha p + omega s; r = s - omega t; red ||r||^2, <r0, r>
     BLAS_XPY = 9,         // y += x
     BLAS_NORM_DOT = 10,   // red ||x||^2, <r0, x>
-    BLAS_MS_AXPY = 11,    // x += alpha p                          (alpha of each right-hand side's Ctl)
-    BLAS_MS_P = 12,       // p = zeta z + beta p                   (zeta, beta of each Ctl)
+    BLAS_MS_XP = 11,      // x_i += alpha_i p_i (while xdo); p_i = zeta_i z + beta_i p_i (while not done), every shift
     BLAS_AXMY_NORM = 13,  // z -= alpha w;                         red ||z||^2
     // BiCGStab(2) (coefficients from each right-hand side's Ctl): y = u_0,
     // z = r_0, w = u_1 or r_1, v = u_2, r_1 or r_2, r0 = u_2 or rt
@@ -209,6 +231,8 @@ struct BlasArgs {
     int64_t st_x, st_y, st_z, st_w, st_v, st_r0;
     RedArgs r;
     Ctl* ctl;
+    int fam_n, fam_base;    // multi-shift: systems and index of the base system
+    CtlFold fold;           // BLAS_AXMY_NORM, BLAS_CG_XP, BLAS_MS_XP
     int gx;                 // planned grid.x (batched launches)
 };
 
@@ -226,7 +250,8 @@ hipError_t exec_blas_batch(const BlasPlan* plans, int n, const BlasArgs* tab, co
                            const FinArgs* fin_tab, hipStream_t s);
 
 // Precision conversion of a parity field: dst(prec_dst) = src(prec_src);
-// with accumulate, dst += src (dst FP64).  Optional FP64 ||dst||^2 reduction.
+// accumulate = 1: dst += src (dst FP64); 2: dst += src + alpha p, p at src's
+// precision, the reliable update of a CG iteration whose x still lacks alpha p.
 struct ConvertArgs {
     int Vh;
     int64_t S;
@@ -235,7 +260,10 @@ struct ConvertArgs {
     int64_t rhs_stride_dst, rhs_stride_src;
     void* dst;
     void* src;
-    int accumulate;         // dst += src
+    int accumulate;
+    const void* p;          // accumulate = 2
+    int64_t rhs_stride_p;
+    CtlFold fold;           // accumulate = 2
     int zero_src;           // src = 0 afterwards
     int pred;
     Ctl* ctl;
@@ -298,11 +326,10 @@ enum PRoutine {
     PR_HOP32_12_D1_NONE,
     PR_HOP32_12_D1_NORM,
     PR_HOP64_18_D0_NONE,
-    PR_HOP64_18_D0_NORM,
-    PR_BLAS32_CG_XR,
-    PR_BLAS32_CG_P,
+    PR_HOP64_18_D0_NORM_LOW,
+    PR_BLAS32_AXMY,
+    PR_BLAS32_CG_XP,
     PR_CONV64_32_ACC,
-    PR_CONV32_64,
     PR_NONE = -1,
 };
 constexpr int kPersistThreads = 256;   // block size of the persistent kernel

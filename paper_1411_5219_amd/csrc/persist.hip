@@ -60,26 +60,21 @@ __device__ __forceinline__ void run_routine(int routine, const void* tab, int s,
         // the FP64 hops of the reliable updates (a few per hundred iterations)
         // tip the kernel over 256 registers: they spill a little, the rest does not
         LQCD_PHOP(PR_HOP64_18_D0_NONE, 64, 18, false, RED_NONE)
-        LQCD_PHOP(PR_HOP64_18_D0_NORM, 64, 18, false, RED_NORM)
+        LQCD_PHOP(PR_HOP64_18_D0_NORM_LOW, 64, 18, false, RED_NORM_LOW)
 #undef LQCD_PHOP
-    case PR_BLAS32_CG_XR: {
+    case PR_BLAS32_AXMY: {
         const BlasArgs& a = static_cast<const BlasArgs*>(tab)[s];
-        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_CG_XR>(a, bx, a.gx, by);
+        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_AXMY_NORM>(a, bx, a.gx, by);
         break;
     }
-    case PR_BLAS32_CG_P: {
+    case PR_BLAS32_CG_XP: {
         const BlasArgs& a = static_cast<const BlasArgs*>(tab)[s];
-        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_CG_P>(a, bx, a.gx, by);
+        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_CG_XP>(a, bx, a.gx, by);
         break;
     }
     case PR_CONV64_32_ACC: {
         const ConvertArgs& a = static_cast<const ConvertArgs*>(tab)[s];
-        if (bx < a.gx) convert_block<64, 32, true>(a, bx, a.gx, by);
-        break;
-    }
-    case PR_CONV32_64: {
-        const ConvertArgs& a = static_cast<const ConvertArgs*>(tab)[s];
-        if (bx < a.gx) convert_block<32, 64, false>(a, bx, a.gx, by);
+        if (bx < a.gx) convert_block<64, 32, 2>(a, bx, a.gx, by);
         break;
     }
     default:
@@ -100,39 +95,14 @@ __device__ void run_step(const PStep& st, int nsys, PersistLds& lds)
     }
 }
 
-// Sum of one right-hand side's N partials in block order by the block's
-// threads (strided), folded in LDS in thread order.
-template <int N>
-__device__ void finalize_one(const FinArgs& f, int rhs)
-{
-    Ctl* c = f.ctl + rhs;
-    if (pred_skip(f.pred, c)) return;  // uniform over the block
-    const double* p = f.partials + (int64_t)rhs * f.nblocks * N;
-    double v[N];
-#pragma unroll
-    for (int j = 0; j < N; ++j) v[j] = 0.0;
-    for (int b = threadIdx.x; b < f.nblocks; b += blockDim.x)
-#pragma unroll
-        for (int j = 0; j < N; ++j) v[j] += p[(int64_t)b * N + j];
-    __shared__ double tot[N];
-    block_reduce_store<N>(v, tot, 0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double t[N];
-#pragma unroll
-        for (int j = 0; j < N; ++j) t[j] = tot[j];
-        finalize<N>(f.fin, c, t);
-    }
-}
-
 __device__ void run_finalize(const PStep& st, int nsys, int nrhs)
 {
     for (int v = blockIdx.x; v < nsys * nrhs; v += gridDim.x) {
         const FinArgs& f = st.fin[v / nrhs];
         const int rhs = v % nrhs;
-        if (st.nfin == 1) finalize_one<1>(f, rhs);
-        else if (st.nfin == 2) finalize_one<2>(f, rhs);
-        else finalize_one<3>(f, rhs);
+        if (st.nfin == 1) finalize_block<1>(f, rhs, f.nblocks);
+        else if (st.nfin == 2) finalize_block<2>(f, rhs, f.nblocks);
+        else finalize_block<3>(f, rhs, f.nblocks);
         __syncthreads();
     }
 }

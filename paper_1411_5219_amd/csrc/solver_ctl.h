@@ -29,6 +29,7 @@ namespace lqcd {
 
 // What the finalize of a reduction does with its totals.
 enum Fin {
+    FIN_NONE = -1,        // nothing: the partials are summed by a later kernel (see ctl_step)
     FIN_STORE = 0,        // copy totals to Ctl::red[]
     FIN_CG_ZZ = 1,        // zz = ||z||^2 (start of CGNR)
     FIN_CG_ALPHA = 2,     // ww = ||w||^2, alpha = zz / ww
@@ -113,6 +114,9 @@ struct Ctl {
     int nouter;       // outer steps ended by tol_inner
     int fallback_ok;  // the inner storage may fall back (FP16 inner)
     int bl_skip;      // BiCGStab(2): r_1 or r_2' vanished, the cycle takes no minimal-residual step
+    // CG: x += alpha p waits for the kernel that updates p.  xpend: alpha of this
+    // iteration is not in x yet; xdo: this iteration's update of x, p takes it.
+    int xpend, xdo;
 };
 
 // Parameters of a control block at the start of a solve.
@@ -173,6 +177,65 @@ LQCD_HD inline void stagnation(Ctl* c)
     c->reset_p = 1;
 }
 
+// The multi-shift steps by parts, so that the shifts can be shared out among
+// lanes: what every shift needs of the base system, then one shift.
+struct MsAlpha {
+    double al, pap, alpha_prev, beta_prev;
+    bool bad;
+};
+// pap = Re <w, p> = <p, A p> of the base system c
+LQCD_HD inline MsAlpha ms_alpha(const Ctl* c, double pap)
+{
+    MsAlpha m;
+    m.bad = !finite(pap) || !(pap > 0.0);
+    m.al = m.bad ? 0.0 : c->rr / pap;
+    m.pap = pap;
+    m.alpha_prev = c->alpha_prev;
+    m.beta_prev = c->beta_prev;
+    return m;
+}
+LQCD_HD inline void ms_alpha_shift(Ctl* ci, const MsAlpha& m)
+{
+    if (ci->done) return;
+    if (m.bad) { fail(ci, finite(m.pap) ? LQCD_EBREAKDOWN : LQCD_ENONFINITE); return; }
+    // zeta_{k+1} = zeta_k zeta_{k-1} alpha_{k-1}
+    //   / (alpha_k beta_{k-1} (zeta_{k-1} - zeta_k) + zeta_{k-1} alpha_{k-1} (1 + sigma alpha_k))
+    const double den = m.al * m.beta_prev * (ci->zeta_prev - ci->zeta) +
+                       ci->zeta_prev * m.alpha_prev * (1.0 + ci->sigma * m.al);
+    const double zn = ci->zeta * ci->zeta_prev * m.alpha_prev / den;
+    if (!finite(zn) || ci->zeta == 0.0) { fail(ci, LQCD_ENONFINITE); return; }
+    ci->zeta_next = zn;
+    ci->alpha = m.al * zn / ci->zeta;
+    ci->xpend = 1;
+}
+struct MsBeta {
+    double rr, be;
+    int it;
+};
+LQCD_HD inline MsBeta ms_beta(const Ctl* c, double rr)
+{
+    return {rr, c->rr > 0.0 ? rr / c->rr : 0.0, c->iter + 1};
+}
+LQCD_HD inline void ms_beta_shift(Ctl* ci, const MsBeta& m)
+{
+    if (ci->done) return;
+    if (!finite(m.rr)) { fail(ci, LQCD_ENONFINITE); return; }
+    const double q = ci->zeta_next / ci->zeta;
+    ci->beta = m.be * q * q;
+    ci->zeta_prev = ci->zeta;
+    ci->zeta = ci->zeta_next;
+    ci->iter = m.it;
+    if (ci->zeta * ci->zeta * m.rr <= ci->thresh) ci->done = 1;
+    else if (m.it >= ci->iter_limit) fail(ci, LQCD_ENOCONV);
+}
+LQCD_HD inline void ms_beta_base(Ctl* c, const MsBeta& m)
+{
+    c->iter = m.it;
+    c->alpha_prev = c->alpha;
+    c->beta_prev = m.be;
+    c->rr = m.rr;
+}
+
 // v holds the reduction totals, zero-padded to 6 entries.  Runs for one
 // right-hand side (multi-shift: for every shift of the family) after the
 // kernel that produced the partials.
@@ -196,6 +259,7 @@ LQCD_HD inline void finalize_totals(int fin, Ctl* c, const double* v)
     case FIN_CG_RR:
         c->rr = v[0];
         c->iter += 1;
+        c->xpend = 1;
         if (!finite(v[0])) { fail(c, LQCD_ENONFINITE); break; }
         if (c->delta2 > 0.0) {
             // mixed precision: never stop on the low-precision recursion;
@@ -235,6 +299,7 @@ LQCD_HD inline void finalize_totals(int fin, Ctl* c, const double* v)
         c->rr_max = v[0];
         c->nupdates += 1;
         c->last_upd_iter = c->iter;
+        c->xpend = 0;  // the update has taken alpha p with the low-precision x
         if (!finite(v[0])) { fail(c, LQCD_ENONFINITE); break; }
         if (v[0] <= c->thresh) { c->done = 1; break; }
         // the FP64 residual did not fall since the previous update: stagnation
@@ -453,52 +518,46 @@ LQCD_HD inline void finalize_totals(int fin, Ctl* c, const double* v)
         break;
     }
     case FIN_MS_ALPHA: {
-        // v[1] = Re <w, p> = <p, A p> of the base system
-        Ctl* c0 = c - c->ms_index;
-        const double pap = v[1];
-        const bool bad = !finite(pap) || !(pap > 0.0);
-        const double al = bad ? 0.0 : c->rr / pap;
-        for (int i = 0; i < c->ms_n; ++i) {
-            Ctl* ci = c0 + i;
-            if (ci->done) continue;
-            if (bad) { fail(ci, finite(pap) ? LQCD_EBREAKDOWN : LQCD_ENONFINITE); continue; }
-            // zeta_{k+1} = zeta_k zeta_{k-1} alpha_{k-1}
-            //   / (alpha_k beta_{k-1} (zeta_{k-1} - zeta_k) + zeta_{k-1} alpha_{k-1} (1 + sigma alpha_k))
-            const double den = al * c->beta_prev * (ci->zeta_prev - ci->zeta) +
-                               ci->zeta_prev * c->alpha_prev * (1.0 + ci->sigma * al);
-            const double zn = ci->zeta * ci->zeta_prev * c->alpha_prev / den;
-            if (!finite(zn) || ci->zeta == 0.0) { fail(ci, LQCD_ENONFINITE); continue; }
-            ci->zeta_next = zn;
-            ci->alpha = al * zn / ci->zeta;
-        }
-        c->alpha = al;  // the base system's alpha (its zeta is 1)
+        const MsAlpha m = ms_alpha(c, v[1]);
+        for (int i = 0; i < c->ms_n; ++i) ms_alpha_shift(c - c->ms_index + i, m);
+        c->alpha = m.al;  // the base system's alpha (its zeta is 1)
         break;
     }
     case FIN_MS_BETA: {
-        Ctl* c0 = c - c->ms_index;
-        const double rr = v[0];
-        const double be = c->rr > 0.0 ? rr / c->rr : 0.0;
-        const int it = c->iter + 1;
-        for (int i = 0; i < c->ms_n; ++i) {
-            Ctl* ci = c0 + i;
-            if (ci->done) continue;
-            if (!finite(rr)) { fail(ci, LQCD_ENONFINITE); continue; }
-            const double q = ci->zeta_next / ci->zeta;
-            ci->beta = be * q * q;
-            ci->zeta_prev = ci->zeta;
-            ci->zeta = ci->zeta_next;
-            ci->iter = it;
-            if (ci->zeta * ci->zeta * rr <= ci->thresh) ci->done = 1;
-            else if (it >= ci->iter_limit) fail(ci, LQCD_ENOCONV);
-        }
-        c->iter = it;
-        c->alpha_prev = c->alpha;
-        c->beta_prev = be;
-        c->rr = rr;
+        const MsBeta m = ms_beta(c, v[0]);
+        for (int i = 0; i < c->ms_n; ++i) ms_beta_shift(c - c->ms_index + i, m);
+        ms_beta_base(c, m);
         break;
     }
     default:
         break;
+    }
+}
+
+// The last scalar step of a CG iteration: the kernel that updates x and p
+// takes x += alpha p if it is still to be taken.
+LQCD_HD constexpr bool closes_iteration(int fin) { return fin == FIN_CG_BETA || fin == FIN_MS_BETA; }
+LQCD_HD inline void ctl_close(Ctl* c)
+{
+    c->xdo = c->xpend;
+    c->xpend = 0;
+}
+
+// One or two scalar steps of a solve in a row: pre (a step whose result no
+// kernel needed until now; FIN_NONE: none), then fin.  A step is skipped once
+// the solve is done (fin not with always), and the reliable update's when none
+// was requested.  multi-shift: c is the base system.
+LQCD_HD inline void ctl_step(Ctl* c, int pre, const double* pv, int fin, const double* v, bool always = false)
+{
+    if (pre == FIN_RU_RR && !c->update) pre = FIN_NONE;
+#if defined(__HIPCC__)
+#pragma nounroll  // one copy of the steps in the kernel
+#endif
+    for (int i = pre == FIN_NONE ? 1 : 0; i < 2; ++i)
+        if (!c->done || (i == 1 && always)) finalize_totals(i == 0 ? pre : fin, c, i == 0 ? pv : v);
+    if (closes_iteration(fin)) {
+        Ctl* c0 = c - c->ms_index;
+        for (int i = 0; i < (c->ms_n > 0 ? c->ms_n : 1); ++i) ctl_close(c0 + i);
     }
 }
 
