@@ -37,7 +37,7 @@ KERNEL_SOURCES = ["csrc/dslash_impl.h", "csrc/block_order.h", "csrc/chunks.h", "
 
 
 # sources of the pseudo-fermion force kernel
-FORCE_SOURCES = ["csrc/force.hip", "csrc/dslash_impl.h", "csrc/block_order.h", "csrc/lqcd_device.h",
+FORCE_SOURCES = ["csrc/force.hip", "csrc/dslash_impl.h", "csrc/block_order.h", "csrc/chunks.h", "csrc/lqcd_device.h",
                  "csrc/lqcd_kernels.h"]
 
 
