@@ -1373,7 +1373,7 @@ constexpr int kMaxSteps = 32;
 // the systems together.  The persistent kernel runs tiles.
 BatchForms batch_forms(const std::vector<Geom>& g, const lqcd_op* ops, const lqcd_solve_params* prm)
 {
-    if (prm->persistent) return {FORM_TILE, FORM_TILE};
+    if (prm->persistent) return {FORM_TILE_WAVE, FORM_TILE_WAVE};
     int recon = 18;
     for (size_t i = 0; i < g.size(); ++i) recon = std::min(recon, (int)ops[i].recon);
     const int want = FORM_BY_SIZE, n = (int)g.size();
@@ -1399,7 +1399,7 @@ int persist_routine(const std::vector<std::vector<Step>>& steps, size_t k)
     }
     if (st.kind == STEP_DSLASH) {
         const DslashPlan& d = st.d;
-        if (d.kind != PLAN_WILSON || d.split != 0 || (d.red != RED_NONE && d.red != RED_NORM && d.red != RED_NORM_LOW))
+        if (d.kind != PLAN_WILSON || d.split != 0 || d.halves != 1 || (d.red != RED_NONE && d.red != RED_NORM && d.red != RED_NORM_LOW))
             return PR_NONE;
         const bool norm = d.red != RED_NONE;
         if (d.prec == 32 && d.recon == 12)
@@ -1462,7 +1462,7 @@ bool same_kernel(const Step& a, const Step& b)
 {
     if (a.kind != b.kind) return false;
     if (a.kind == STEP_DSLASH)
-        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split &&
+        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split && a.d.halves == b.d.halves &&
                a.d.lnt == b.d.lnt && a.d.red == b.d.red &&
                a.d.dag == b.d.dag && a.d.a.nrhs == b.d.a.nrhs && a.d.grid.y == b.d.grid.y;
     if (a.kind == STEP_BLAS)

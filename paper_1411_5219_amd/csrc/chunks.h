@@ -65,12 +65,12 @@ struct ChunkGrid {
 // order; k >= 1: layers, in z-slabs of the largest divisor of the layers with at most
 // k planes; block and ygroup: the sites of a layer that are neighbours in the order
 // (block requests of work-items, one per site, times ygroup).
-inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int ygroup, int maxsub)
+inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int ygroup, int maxsub, int idle_max = 20)
 {
     ChunkArgs c = {};
     const int plane = g.Lxh * g.L[1];
     const int64_t flat = (g.Vh + kChunk - 1) / kChunk;
-    // One plane per layer where its last chunk leaves at most a twentieth of
+    // One plane per layer where its last chunk leaves at most one of idle_max of
     // the lanes idle, else the fewest planes (a divisor of Lz up to 8) that do,
     // or that leave the fewest idle: 20^3x8 has 200 sites per plane, 78% of four
     // chunks, but 800 in four planes, 96% of 13 (FP64 Schur complement on four
@@ -81,7 +81,7 @@ inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int 
         if (g.L[2] % n) continue;
         const int64_t idle = (int64_t)chunks_of(n) * kChunk - (int64_t)plane * n;
         const int64_t best = (int64_t)chunks_of(c.planes) * kChunk - (int64_t)plane * c.planes;
-        if (20 * best <= (int64_t)chunks_of(c.planes) * kChunk) break;
+        if (idle_max * best <= (int64_t)chunks_of(c.planes) * kChunk) break;
         if (idle * chunks_of(c.planes) < best * chunks_of(n)) c.planes = n;
     }
     const int per = chunks_of(c.planes), layers = g.L[2] / c.planes;

@@ -22,9 +22,12 @@ hipError_t launch_stag_64(int recon, int red, bool lnt, const DslashLaunch& L, d
 hipError_t launch_stag_32(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 hipError_t launch_stag_16(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 
-hipError_t launch_rhs_64(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
-hipError_t launch_rhs_32(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
-hipError_t launch_rhs_16(int recon, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_rhs_64(int recon, int halves, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
+                         hipStream_t s);
+hipError_t launch_rhs_32(int recon, int halves, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
+                         hipStream_t s);
+hipError_t launch_rhs_16(int recon, int halves, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
+                         hipStream_t s);
 
 static hipError_t launch_dslash_prec(const DslashPlan& p, const DslashLaunch& L, dim3 grid, hipStream_t s)
 {
@@ -35,9 +38,9 @@ static hipError_t launch_dslash_prec(const DslashPlan& p, const DslashLaunch& L,
         return hipErrorInvalidValue;
     }
     if (p.split == 0) {
-        if (p.prec == 64) return launch_rhs_64(p.recon, p.dag, p.red, L, grid, p.block, s);
-        if (p.prec == 32) return launch_rhs_32(p.recon, p.dag, p.red, L, grid, p.block, s);
-        if (p.prec == 16) return launch_rhs_16(p.recon, p.dag, p.red, L, grid, p.block, s);
+        if (p.prec == 64) return launch_rhs_64(p.recon, p.halves, p.dag, p.red, L, grid, p.block, s);
+        if (p.prec == 32) return launch_rhs_32(p.recon, p.halves, p.dag, p.red, L, grid, p.block, s);
+        if (p.prec == 16) return launch_rhs_16(p.recon, p.halves, p.dag, p.red, L, grid, p.block, s);
         return hipErrorInvalidValue;
     }
     if (p.prec == 64) return launch_dslash_64(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
@@ -50,12 +53,12 @@ static ChunkGrid chunk_grid(const Geom& g) { return ChunkGrid{{g.L[0], g.L[1], g
 
 // Block order and grid of a launch whose blocks cover at most maxsub chunks
 // of 64 sites each, for `tile` right-hand sides per block.
-static void plan_chunks(const Launch& cfg, int maxsub, int tile, int nrhs, DslashPlan* p)
+static void plan_chunks(const Launch& cfg, int maxsub, int tile, int nrhs, DslashPlan* p, int idle_max = 20)
 {
     DslashArgs& a = p->a;
     a.swizzle = cfg.swizzle;
     a.nrhs = nrhs;
-    a.ch = plan_chunk_order(chunk_grid(a.g), cfg.order, cfg.block, cfg.ygroup, maxsub);
+    a.ch = plan_chunk_order(chunk_grid(a.g), cfg.order, cfg.block, cfg.ygroup, maxsub, idle_max);
     a.ch.tile = tile;
     p->slots = a.ch.nsp * (a.full ? 2 : 1);
     a.ch.nblk = p->slots;
@@ -90,13 +93,15 @@ static bool storage_built(int prec, int recon)
 // 38.2; 24^3x8, half full, 20.2 and 18.5; 40^3x6, uneven, 66 and 59; FP64/12
 // 48^3x8 103 and 99).
 // Several: a tile of them per block (hop_rhs.h) once the pairs of all of them
-// would no longer run at once, three waves per SIMD; below that the pairs are
-// faster, each on its own right-hand side (Schur complement, FP32/12: 8^3x4
-// with four 9.8 us against 13.3, 16^3x8 with four 15.0 against 16.8, with
-// twelve 33.1 against 29.7; FP64/18 20^3x8 with two 35.3 against 46.5), and
-// with two or three in FP16 storage, whose tiles wait for LDS (48^3x12 with
-// two 135 against 147, 28^3x8 with three 34.0 against 36.4, with four 41.0
-// against 40.6).
+// would no longer run at once, two waves per SIMD in FP64 and three below;
+// before that the pairs are faster, each on its own right-hand side (Schur
+// complement, FP32/12: 8^3x4 with four 9.8 us against 13.3, 16^3x8 with four
+// 15.0 against 16.8, with twelve 33.1 against 29.7; FP64/18 20^3x8 with two
+// 35.6 against 45.5, 20^3x6 with four 47 against 41).  FP64/12 stays with pairs
+// up to five waves per SIMD: tiles hold all 18 reals in LDS (20^3x8 with four
+// 53 against 61, 24^3x8 with three 71 against 68); so does FP16 storage with
+// two or three, whose tiles wait for LDS (48^3x12 with two 135 against 147,
+// 28^3x8 with three 34.0 against 36.4, with four 41.0 against 40.6).
 int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want)
 {
     if (want != FORM_BY_SIZE) return want;
@@ -107,7 +112,12 @@ int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int
         chunks += (g[i].Vh + kChunk - 1) / kChunk;
         even = even && c.planes == 1 && c.nsub > 1 && c.chunks % c.nsub == 0;
     }
-    if (nrhs > 1) return 2 * chunks * nrhs <= 3 * kSimds || (prec == 16 && nrhs <= 3) ? FORM_PAIR : FORM_TILE;
+    if (nrhs > 1) {
+        const int64_t waves = 2 * chunks * nrhs;
+        const bool pair = prec == 64 ? waves <= (recon == 12 ? 5 : 2) * kSimds
+                                     : waves <= 3 * kSimds || (prec == 16 && nrhs <= 3);
+        return pair ? FORM_PAIR : FORM_TILE;
+    }
     return prec == 64 && recon == 18 && !full && even && chunks >= 2 * kSimds ? FORM_WAVE : FORM_PAIR;
 }
 
@@ -123,7 +133,8 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
     p.red = red;
     p.a = args;
     const int form = hop_form(prec, recon, args.full != 0, &args.g, 1, nrhs, cfg.form);
-    if (form == FORM_TILE) {
+    p.halves = 1;
+    if (form == FORM_TILE || form == FORM_TILE_WAVE) {
         // Several right-hand sides share a block and the links in its LDS:
         // as few tiles of at most kMaxTile as there can be, of even sizes
         const int ntiles = (nrhs + kMaxTile - 1) / kMaxTile, tile = (nrhs + ntiles - 1) / ntiles;
@@ -134,10 +145,18 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
         // against 75; FP32 Schur, 12 right-hand sides, is faster in groups of
         // 4: 207 us against 213)
         if (prec == 64 || args.full) c.block = cfg.block / 2;
-        plan_chunks(c, 1, tile, nrhs, &p);
+        // FP32 and FP64 tiles take a plane of which a sixteenth is idle by itself
+        // (44^3x6, four right-hand sides: FP64 386 us against 439, FP32 145
+        // against 175; FP16 is faster with fewer idle lanes); FP64, two blocks
+        // per compute unit, in few rounds takes the layers with the fewest idle
+        // lanes (20^3x8
+        // makes 512 blocks of five planes, 520 of four: FP64/18, three 52 -> 41 us)
+        const int64_t blocks = (int64_t)((args.g.Vh + kChunk - 1) / kChunk) * ntiles;
+        plan_chunks(c, 1, tile, nrhs, &p, prec == 16 ? 20 : prec == 64 && blocks <= 2 * kSimds ? 40 : 16);
         p.split = 0;
         p.lnt = false;
-        p.block = dim3((unsigned)(kChunk * tile));
+        p.halves = form == FORM_TILE && tile <= 2 ? 2 : 1;
+        p.block = dim3((unsigned)(kChunk * tile * p.halves));
     } else {
         p.lnt = nrhs == 1 && !args.full;
         p.split = form == FORM_WAVE ? 1 : 2;
@@ -207,6 +226,7 @@ hipError_t plan_stag_hop(int prec, int recon, int red, const DslashArgs& args, i
     p.red = red;
     p.a = args;
     p.split = 1;
+    p.halves = 1;
     p.lnt = nrhs == 1 && !args.full;
     plan_chunks(cfg, cfg.block / kChunk, 1, nrhs, &p);
     p.block = dim3((unsigned)(kChunk * p.a.ch.nsub));

@@ -3,10 +3,10 @@
 // unit).
 //
 // A block serves 64 output sites for up to four right-hand sides, one per
-// wave.  The waves first share the loading of the eight links of the sites
-// and leave them in LDS with their third row rebuilt; after one barrier each
-// wave runs the eight hops of its right-hand side with the spinors from
-// memory and the links from LDS.
+// wave (two of them: two waves each).  The waves first share the loading of
+// the eight links of the sites and leave them in LDS with their third row
+// rebuilt; after one barrier each wave runs the hops of its right-hand side
+// with the spinors from memory and the links from LDS.
 //
 // Bounds: reads from beyond L2 (each XCD works on an eighth of the lattice and
 // re-reads its surface), and VALU issue in FP16 storage.  Against one
@@ -90,7 +90,8 @@ struct RhsTune {
     static constexpr int waves = PREC == 64 ? 2 : PREC == 32 ? 3 : 4;
 };
 
-template <int PREC, int RECON, bool DAG>
+// Hops K0 .. K1 - 1 of one right-hand side.
+template <int PREC, int RECON, bool DAG, int K0, int K1>
 struct RhsPipe {
     using R = typename SpinorIO<PREC>::R;
     static constexpr int D = RhsTune<PREC>::depth;
@@ -105,7 +106,7 @@ struct RhsPipe {
     template <int K>
     __device__ __forceinline__ void load()
     {
-        if constexpr (K < 8) nb[K % D].load(in, a.g.S, g.template get<K>().nb);
+        if constexpr (K < K1) nb[K % D].load(in, a.g.S, g.template get<K>().nb);
     }
     template <int K>
     __device__ __forceinline__ void step()
@@ -127,9 +128,9 @@ struct RhsPipe {
     }
     __device__ __forceinline__ void first()
     {
-        load<0>();
-        if constexpr (D > 1) load<1>();
-        if constexpr (D > 2) load<2>();
+        load<K0>();
+        if constexpr (D > 1) load<K0 + 1>();
+        if constexpr (D > 2) load<K0 + 2>();
     }
     __device__ __forceinline__ void run()
     {
@@ -137,21 +138,30 @@ struct RhsPipe {
         for (int s = 0; s < 4; ++s)
 #pragma unroll
             for (int c = 0; c < 3; ++c) acc.s[s][c] = {R(0), R(0)};
-        step<0>();
-        step<1>();
-        step<2>();
-        step<3>();
-        step<4>();
-        step<5>();
-        step<6>();
-        step<7>();
+        step<K0>();
+        step<K0 + 1>();
+        step<K0 + 2>();
+        step<K0 + 3>();
+        if constexpr (K1 - K0 == 8) {
+            step<4>();
+            step<5>();
+            step<6>();
+            step<7>();
+        }
     }
 };
 
-// Block bx of the launch.
-template <int PREC, int RECON, bool DAG, int RED>
+// Block bx of the launch.  HALVES = 2: two waves per right-hand side, wave 0 of
+// them runs the x and y hops, wave 1 the z and t hops, whose sum it leaves in
+// LDS.  For tiles of two: their links take the LDS of a tile of four, which
+// lets two blocks of two waves run on a compute unit in FP64 and four in FP32,
+// half the waves its registers allow (two right-hand sides: FP32/12 Schur
+// complement 48^3x6 117 -> 101 us, 26^3x8 35 -> 32; FP64/18 32^3x8 118 -> 110;
+// FP64/12 full matrix 24^3x8 48 -> 41).
+template <int PREC, int RECON, bool DAG, int RED, int HALVES>
 __device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<PREC, RECON>& lds)
 {
+    using R = typename SpinorIO<PREC>::R;
     constexpr int N = RedN<RED>::N;
     const int lane = (int)threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
@@ -172,28 +182,64 @@ __device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<
     const SiteGeo geo = site_geo(a.g, s, p);
     const int64_t S = a.g.S;
     const int64_t poff = a.full ? p * a.par_bytes : 0, ioff = a.full ? (1 - p) * a.par_bytes : 0;
-    const bool run = (mask >> wave) & 1u;
-    const int64_t rr = rhs0 + wave;
-    RhsPipe<PREC, RECON, DAG> pipe{lds, a, geo, static_cast<const char*>(a.in) + rr * a.st_in + ioff, lane, {}, {}};
-    if (run) pipe.first();
-    for (int k = wave; k < 8; k += nw) {
-        // link of hop k: of this site (forward) or of the neighbour (backward)
-        int l = s.h;
-        if (k == 1) l = geo.get<1>().nb;
-        else if (k == 3) l = geo.get<3>().nb;
-        else if (k == 5) l = geo.get<5>().nb;
-        else if (k == 7) l = geo.get<7>().nb;
-        Lnk<PREC, RECON> L;
-        L.template load<false>(a.U, S, (k & ~1) + ((k & 1) ? 1 - p : p), l);
-        lds.put(k, lane, L);
+    const int mine = HALVES == 2 ? wave >> 1 : wave;
+    const bool run = (mask >> mine) & 1u;
+    const int64_t rr = rhs0 + mine;
+    const char* in = static_cast<const char*>(a.in) + rr * a.st_in + ioff;
+    auto links = [&]() {
+        for (int k = wave; k < 8; k += nw) {
+            // link of hop k: of this site (forward) or of the neighbour (backward)
+            int l = s.h;
+            if (k == 1) l = geo.get<1>().nb;
+            else if (k == 3) l = geo.get<3>().nb;
+            else if (k == 5) l = geo.get<5>().nb;
+            else if (k == 7) l = geo.get<7>().nb;
+            Lnk<PREC, RECON> L;
+            L.template load<false>(a.U, S, (k & ~1) + ((k & 1) ? 1 - p : p), l);
+            lds.put(k, lane, L);
+        }
+    };
+    Spinor<R> acc;
+    if constexpr (HALVES == 1) {
+        RhsPipe<PREC, RECON, DAG, 0, 8> pipe{lds, a, geo, in, lane, {}, {}};
+        if (run) pipe.first();
+        links();
+        __syncthreads();
+        if (!run) return;
+        pipe.run();
+        acc = pipe.acc;
+    } else {
+        links();
+        __syncthreads();
+        if (run) {
+            if ((wave & 1) == 0) {
+                RhsPipe<PREC, RECON, DAG, 0, 4> pipe{lds, a, geo, in, lane, {}, {}};
+                pipe.first();
+                pipe.run();
+                acc = pipe.acc;
+            } else {
+                RhsPipe<PREC, RECON, DAG, 4, 8> pipe{lds, a, geo, in, lane, {}, {}};
+                pipe.first();
+                pipe.run();
+                acc = pipe.acc;
+            }
+        }
+        __syncthreads();  // the links have been read
+        cplx<R>* sum = reinterpret_cast<cplx<R>*>(&lds) + (mine * 12) * kChunk + lane;
+        static_assert(sizeof(lds) >= 2 * 12 * kChunk * sizeof(cplx<R>), "the sums of a tile of two fit");
+        if (run && (wave & 1)) {
+#pragma unroll
+            for (int k = 0; k < 12; ++k) sum[k * kChunk] = acc.s[k / 3][k % 3];
+        }
+        __syncthreads();
+        if (!run || (wave & 1)) return;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) acc.s[k / 3][k % 3] = acc.s[k / 3][k % 3] + sum[k * kChunk];
     }
-    __syncthreads();
-    if (!run) return;
-    pipe.run();
     double tot[N];
 #pragma unroll
     for (int j = 0; j < N; ++j) tot[j] = 0.0;
-    hop_store<PREC, RED>(a, rr, poff, s.h, s.valid, pipe.acc, tot);
+    hop_store<PREC, RED>(a, rr, poff, s.h, s.valid, acc, tot);
     if constexpr (RED != RED_NONE) {
         wave_reduce<N>(tot);
         const int64_t nsl = a.ch.nsp * (a.full ? 2 : 1), slot = (int)b + p * (a.full ? a.ch.nsp : 0);
@@ -203,15 +249,15 @@ __device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<
     }
 }
 
-template <int PREC, int RECON, bool DAG, int RED>
+template <int PREC, int RECON, bool DAG, int RED, int HALVES>
 __global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
 k_hop_rhs(const DslashArgs a)
 {
     __shared__ RhsLinks<PREC, RECON> lds;
-    rhs_block<PREC, RECON, DAG, RED>(a, blockIdx.x, lds);
+    rhs_block<PREC, RECON, DAG, RED, HALVES>(a, blockIdx.x, lds);
 }
 
-template <int PREC, int RECON, bool DAG, int RED>
+template <int PREC, int RECON, bool DAG, int RED, int HALVES>
 __global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
 k_hop_rhs_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
@@ -221,37 +267,40 @@ k_hop_rhs_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs
     while (s + 1 < nsys && x >= offs[s + 1]) ++s;
     const int bx = x - offs[s];
     if (bx >= tab[s].gx) return;  // padding of the system's range
-    rhs_block<PREC, RECON, DAG, RED>(tab[s], bx, lds);
+    rhs_block<PREC, RECON, DAG, RED, HALVES>(tab[s], bx, lds);
 }
 
-template <int PREC, int RECON, bool DAG, int RED>
+template <int PREC, int RECON, bool DAG, int RED, int HALVES>
 static hipError_t rhs_one(const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
-    if (L.tab) hipLaunchKernelGGL((k_hop_rhs_batch<PREC, RECON, DAG, RED>), grid, block, 0, s, L.tab, L.offs, L.nsys);
-    else hipLaunchKernelGGL((k_hop_rhs<PREC, RECON, DAG, RED>), grid, block, 0, s, *L.a);
+    if (L.tab) hipLaunchKernelGGL((k_hop_rhs_batch<PREC, RECON, DAG, RED, HALVES>), grid, block, 0, s, L.tab, L.offs, L.nsys);
+    else hipLaunchKernelGGL((k_hop_rhs<PREC, RECON, DAG, RED, HALVES>), grid, block, 0, s, *L.a);
     return hipGetLastError();
 }
 
-template <int PREC, int RECON, bool DAG>
+template <int PREC, int RECON, bool DAG, int HALVES>
 static hipError_t rhs_red(int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
     switch (red) {
-    case RED_NONE: return rhs_one<PREC, RECON, DAG, RED_NONE>(L, grid, block, s);
-    case RED_NORM: return rhs_one<PREC, RECON, DAG, RED_NORM>(L, grid, block, s);
-    case RED_NORM_DS: return rhs_one<PREC, RECON, DAG, RED_NORM_DS>(L, grid, block, s);
-    case RED_DOT_AUX: return rhs_one<PREC, RECON, DAG, RED_DOT_AUX>(L, grid, block, s);
+    case RED_NONE: return rhs_one<PREC, RECON, DAG, RED_NONE, HALVES>(L, grid, block, s);
+    case RED_NORM: return rhs_one<PREC, RECON, DAG, RED_NORM, HALVES>(L, grid, block, s);
+    case RED_NORM_DS: return rhs_one<PREC, RECON, DAG, RED_NORM_DS, HALVES>(L, grid, block, s);
+    case RED_DOT_AUX: return rhs_one<PREC, RECON, DAG, RED_DOT_AUX, HALVES>(L, grid, block, s);
     default: break;
     }
     if constexpr (PREC == 64 && !DAG)
-        if (red == RED_NORM_LOW) return rhs_one<PREC, RECON, DAG, RED_NORM_LOW>(L, grid, block, s);
+        if (red == RED_NORM_LOW) return rhs_one<PREC, RECON, DAG, RED_NORM_LOW, HALVES>(L, grid, block, s);
     return hipErrorInvalidValue;
 }
 
 template <int PREC, int RECON>
-inline hipError_t launch_rhs(bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
+inline hipError_t launch_rhs(int halves, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
-    return dag ? rhs_red<PREC, RECON, true>(red, L, grid, block, s)
-               : rhs_red<PREC, RECON, false>(red, L, grid, block, s);
+    if (halves == 2)
+        return dag ? rhs_red<PREC, RECON, true, 2>(red, L, grid, block, s)
+                   : rhs_red<PREC, RECON, false, 2>(red, L, grid, block, s);
+    return dag ? rhs_red<PREC, RECON, true, 1>(red, L, grid, block, s)
+               : rhs_red<PREC, RECON, false, 1>(red, L, grid, block, s);
 }
 
 }  // namespace lqcd

@@ -117,8 +117,9 @@ struct Launch {
 
 // How the waves of a Wilson hop share sites and right-hand sides: one wave or
 // a pair of waves per chunk of 64 sites and right-hand side, or a tile of
-// right-hand sides per chunk with its links in LDS.
-enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3 };
+// right-hand sides per chunk with its links in LDS, and in this one wave per
+// right-hand side, or (FORM_TILE only, by size) two.
+enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3, FORM_TILE_WAVE = 4 };
 // The form for launches on nrhs right-hand sides of the n lattices g (want if
 // not by size).  FORM_WAVE exists for FP64 on one right-hand side and one parity.
 int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want);
@@ -171,6 +172,7 @@ struct DslashPlan {
     int kind;   // PlanKind
     int prec, recon, red;
     int split;  // waves per chunk of sites, 0: several right-hand sides per block
+    int halves; // split = 0: waves per right-hand side
     bool dag;
     bool lnt;   // streaming link loads (no other block of the launch reads the links)
     int nfin;   // values per finalize (0: no reduction)

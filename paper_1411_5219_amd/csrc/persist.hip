@@ -50,7 +50,7 @@ __device__ __forceinline__ void run_routine(int routine, const void* tab, int s,
 #define LQCD_PHOP(ID, P, RC, DG, RD)                                                    \
     case ID: {                                                                          \
         const DslashArgs& a = static_cast<const DslashArgs*>(tab)[s];                   \
-        if (bx < a.gx) rhs_block<P, RC, DG, RD>(a, bx, lds.l##P);                       \
+        if (bx < a.gx) rhs_block<P, RC, DG, RD, 1>(a, bx, lds.l##P);                       \
         break;                                                                          \
     }
         LQCD_PHOP(PR_HOP32_12_D0_NONE, 32, 12, false, RED_NONE)

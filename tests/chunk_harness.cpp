@@ -8,10 +8,10 @@ extern "C" {
 // Every block, chunk and lane of a plan: counts[h] is raised for each valid
 // lane of parity p; returns the first inconsistency (0: none) and the plan's
 // blocks in *nsp.
-int chunk_cover(const int* L, int order, int block, int ygroup, int maxsub, int p, int* counts, int* nsp)
+int chunk_cover(const int* L, int order, int block, int ygroup, int maxsub, int idle, int p, int* counts, int* nsp)
 {
     ChunkGrid g{{L[0], L[1], L[2], L[3]}, L[0] / 2, L[0] / 2 * L[1] * L[2] * L[3]};
-    const ChunkArgs c = plan_chunk_order(g, order, block, ygroup, maxsub);
+    const ChunkArgs c = plan_chunk_order(g, order, block, ygroup, maxsub, idle);
     *nsp = c.nsp;
     if (c.nsub < 1 || c.nsub > maxsub) return 1;
     for (int b = 0; b < c.nsp; ++b)

@@ -42,13 +42,13 @@ def test_every_site_once(lib, L):
     for order in (0, 1, 2, 3, 5, 64):
         for block in (64, 128, 192, 256):
             for ygroup in (1, 2, 3, 64):
-                for maxsub in (1, block // 64):
+                for maxsub, idle in ((1, 16), (1, 20), (1, 40), (block // 64, 20)):
                     for p in (0, 1):
                         counts = np.zeros(Vh, dtype=np.int32)
                         nsp = ctypes.c_int()
-                        bad = lib.chunk_cover(Li, order, block, ygroup, maxsub, p,
+                        bad = lib.chunk_cover(Li, order, block, ygroup, maxsub, idle, p,
                                               counts.ctypes.data_as(ctypes.POINTER(ctypes.c_int)), ctypes.byref(nsp))
-                        case = (order, block, ygroup, maxsub, p)
+                        case = (order, block, ygroup, maxsub, idle, p)
                         assert bad == 0, case
                         assert (counts == 1).all(), case
                         assert nsp.value <= slots, case

@@ -110,3 +110,54 @@ def test_staggered_block_edges(mods, L4, prec, recon):
         ref = S.apply_M(U, chi[k], L4, theta, 0.1)
         err = np.linalg.norm(got[k] - ref, axis=-1)
         assert err.max() <= TOL[prec] * np.sqrt(np.mean(np.linalg.norm(ref, axis=-1) ** 2)), k
+
+
+# lattices just large enough for tiles of two right-hand sides (two waves each), with ragged last chunks
+@pytest.mark.parametrize("L4,prec,recon", [((44, 20, 20, 4), 64, 18), ((44, 48, 20, 4), 64, 12), ((44, 28, 20, 4), 32, 12),
+                                           ((42, 30, 20, 4), 32, 18)])
+@pytest.mark.parametrize("dagger", [0, 1])
+def test_two_rhs_tiles(mods, L4, prec, recon, dagger):
+    torch, fields, lqcd = mods
+    theta, kappa, mu = (0.2, 0.0, -0.4, math.pi), 0.14, 0.03
+    print(f"\n[case] two-rhs tiles L={L4} prec={prec}/{recon} dagger={dagger}", flush=True)
+    psi = gaussian_spinor(L4, seed=44, nrhs=2)
+    lat = fields.Lattice(L4, theta)
+    o = lqcd.op(kappa, mu, prec, recon)
+    Ud = lat.gauge(gauge_field(L4, "exp", eps=0.4, seed=43), prec, recon)
+    pair, single = lat.spinor(psi, prec), [lat.spinor(psi[k], prec) for k in range(2)]
+    out = lat.zeros(lqcd.FIELD_SPINOR_FULL, prec, nrhs=2)
+    lqcd.dslash_apply(lat.g, o, Ud, pair, out, dagger=dagger, nrhs=2)
+    got = lat.unpack(out, prec, nrhs=2).reshape(2, lat.V, 4, 3)
+    sch = lat.zeros(lqcd.FIELD_SPINOR_PARITY, prec, nrhs=2)
+    lqcd.dslash_eo_apply(lat.g, o, Ud, lat.parity_view(pair, 0, prec, 2), sch, 0, lqcd.OP_SCHUR, dagger, 2, lat.workspace(o))
+    pb = lat.nbytes(lqcd.FIELD_SPINOR_PARITY, prec)
+    for k in range(2):
+        # one right-hand side at a time: the kernels the other tests hold to the oracle
+        one = lat.zeros(lqcd.FIELD_SPINOR_FULL, prec)
+        lqcd.dslash_apply(lat.g, o, Ud, single[k], one, dagger=dagger)
+        assert site_rel_err(got[k], lat.unpack(one, prec).reshape(lat.V, 4, 3)) <= TOL[prec], ("full", k)
+        f = torch.zeros(2, 2 * pb, dtype=torch.uint8, device="cuda")
+        f[0, :pb] = sch.view(2, pb)[k]
+        lqcd.dslash_eo_apply(lat.g, o, Ud, lat.parity_view(single[k], 0, prec), f[1, :pb], 0, lqcd.OP_SCHUR, dagger, 1,
+                             lat.workspace(o))
+        a, b = (lat.unpack(f[i].contiguous(), prec).reshape(lat.V, 4, 3) for i in range(2))
+        ev = W.parity(L4) == 0
+        assert site_rel_err(a[ev], b[ev]) <= TOL[prec], ("schur", k)
+
+
+def test_two_rhs_tiles_norms(mods):
+    """The reductions of such tiles: a mixed solve whose inner and outer hops both run them."""
+    torch, fields, lqcd = mods
+    L4, theta, kappa, mu, tol = (44, 28, 20, 4), (0.0, 0.0, 0.0, math.pi), 0.12, 0.05, 1e-10
+    print(f"\n[case] two-rhs tiles, solve L={L4}", flush=True)
+    U, b = gauge_field(L4, "exp", eps=0.4, seed=45), gaussian_spinor(L4, seed=46, nrhs=2)
+    lat = fields.Lattice(L4, theta)
+    o = lqcd.op(kappa, mu, 64, 18)
+    p = lqcd.solve_params(nrhs=2, tol=tol, maxiter=500, eo=1, inner_prec=32, inner_recon=12, delta_reliable=0.01)
+    x = lat.zeros(lqcd.FIELD_SPINOR_FULL, 64, nrhs=2)
+    rc, info = lqcd.cg_solve(lat.g, o, lat.gauge(U), lat.spinor(b), x, p, lat.workspace(o, p))
+    assert rc == 0, info
+    got = lat.unpack(x, 64, nrhs=2).reshape(2, lat.V, 4, 3)
+    for k in range(2):
+        tr = W.true_residual(U, got[k], b[k], L4, theta, kappa, mu)
+        assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol
