@@ -23,10 +23,8 @@ template <int PREC, int KIND, int OP>
 __global__ void __launch_bounds__(256) k_blas_batch(const BlasArgs* __restrict__ tab, const int* __restrict__ offs,
                                                    int nsys)
 {
-    const int x = blockIdx.x;
-    int s = 0;
-    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
-    const int bx = x - offs[s];
+    int bx;
+    const int s = batch_system(offs, nsys, &bx);
     if (bx >= tab[s].gx) return;  // padding of the system's range
     blas_block<PREC, KIND, OP>(tab[s], bx, tab[s].gx, blockIdx.y);
 }
@@ -140,8 +138,11 @@ hipError_t exec_blas_batch(const BlasPlan* plans, int n, const BlasArgs* tab, co
 {
     if (n < 1) return hipErrorInvalidValue;
     const BlasPlan& p0 = plans[0];
-    BlasLaunch L{nullptr, tab, offs, n};
-    const hipError_t e = blas_prec(p0.prec, p0.a.kind, p0.op, L, dim3((unsigned)total_blocks, p0.grid.y), p0.block, s);
+    unsigned gx = 0;
+    for (int i = 0; i < n; ++i) gx = plans[i].grid.x > gx ? plans[i].grid.x : gx;
+    const BatchGrid bg = batch_grid(n, gx, p0.grid.y, (unsigned)total_blocks, offs);
+    BlasLaunch L{nullptr, tab, bg.offs, n};
+    const hipError_t e = blas_prec(p0.prec, p0.a.kind, p0.op, L, bg.grid, p0.block, s);
     if (e != hipSuccess || p0.nfin == 0) return e;
     return launch_finalize_batch(p0.nfin, fin_tab, n, p0.nrhs, s);
 }
@@ -215,10 +216,8 @@ template <int PD, int PS, int ACC>
 __global__ void __launch_bounds__(256) k_convert_batch(const ConvertArgs* __restrict__ tab,
                                                       const int* __restrict__ offs, int nsys)
 {
-    const int x = blockIdx.x;
-    int s = 0;
-    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
-    const int bx = x - offs[s];
+    int bx;
+    const int s = batch_system(offs, nsys, &bx);
     if (bx >= tab[s].gx) return;  // padding of the system's range
     convert_block<PD, PS, ACC>(tab[s], bx, tab[s].gx, blockIdx.y);
 }
@@ -289,8 +288,11 @@ hipError_t exec_convert_batch(const ConvertPlan* plans, int n, const ConvertArgs
 {
     if (n < 1) return hipErrorInvalidValue;
     const ConvertPlan& p0 = plans[0];
-    ConvertLaunch L{nullptr, tab, offs, n};
-    return convert_any(p0.pd, p0.ps, p0.a.accumulate, L, dim3((unsigned)total_blocks, p0.grid.y), p0.block, s);
+    unsigned gx = 0;
+    for (int i = 0; i < n; ++i) gx = plans[i].grid.x > gx ? plans[i].grid.x : gx;
+    const BatchGrid bg = batch_grid(n, gx, p0.grid.y, (unsigned)total_blocks, offs);
+    ConvertLaunch L{nullptr, tab, bg.offs, n};
+    return convert_any(p0.pd, p0.ps, p0.a.accumulate, L, bg.grid, p0.block, s);
 }
 
 hipError_t launch_convert(int pd, int ps, const ConvertArgs& a, int nrhs, hipStream_t s)

@@ -528,12 +528,9 @@ template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopTune<PREC, SPLIT>::waves)))
 k_dslash_eo_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
-    const int x = blockIdx.x;
-    int s = 0;
-    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
-    const int bx = x - offs[s];
-    // each system's range starts at a multiple of 8 (XCD remap); blocks past
-    // the system's own grid are padding
+    int bx;
+    const int s = batch_system(offs, nsys, &bx);
+    // blocks past the system's own grid are padding
     if (bx >= tab[s].gx) return;
     dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(tab[s], bx);
 }

@@ -262,10 +262,8 @@ __global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per
 k_hop_rhs_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
     __shared__ RhsLinks<PREC, RECON> lds;
-    const int x = blockIdx.x;
-    int s = 0;
-    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
-    const int bx = x - offs[s];
+    int bx;
+    const int s = batch_system(offs, nsys, &bx);
     if (bx >= tab[s].gx) return;  // padding of the system's range
     rhs_block<PREC, RECON, DAG, RED, HALVES>(tab[s], bx, lds);
 }

@@ -154,6 +154,36 @@ hipError_t launch_dslash(int prec, int recon, bool dagger, int red, const Dslash
 hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
                        hipStream_t s);
 
+// Grid of a batched launch.  Systems of about one size lie along z, each padded
+// to the widest, so that a block knows its system at once; offs is null then.
+// Others lie one after the other along x and a block searches offs, a trip to
+// memory before the one for its arguments (mixed solves of four lattices of 1728
+// to 4096 sites, four right-hand sides each: 5.85 ms searched, 5.55 along z).
+struct BatchGrid {
+    dim3 grid;
+    const int* offs;
+};
+inline BatchGrid batch_grid(int nsys, unsigned widest, unsigned gy, unsigned total, const int* offs)
+{
+    const unsigned gx = (widest + 7) / 8 * 8;  // whole rounds over the XCDs
+    if ((uint64_t)gx * nsys <= 2 * (uint64_t)total) return {dim3(gx, gy, (unsigned)nsys), nullptr};
+    return {dim3(total, gy), offs};
+}
+#if defined(__HIPCC__)
+__device__ __forceinline__ int batch_system(const int* offs, int nsys, int* bx)
+{
+    const int x = blockIdx.x;
+    if (!offs) {
+        *bx = x;
+        return blockIdx.z;
+    }
+    int s = 0;
+    while (s + 1 < nsys && x >= offs[s + 1]) ++s;
+    *bx = x - offs[s];
+    return s;
+}
+#endif
+
 // One Dslash launch, or a batch of nsys argument sets in device memory.
 struct DslashLaunch {
     const DslashArgs* a;

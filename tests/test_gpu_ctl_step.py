@@ -72,3 +72,40 @@ def test_multishift(mods, L4, n):
         x = lat.unpack_colour(full)
         res = np.linalg.norm((b - S.normal_e(U, x, L4, THETA, mass) - sh * x).ravel()) / np.linalg.norm(b.ravel())
         assert res <= tol and abs(res - info[i]["true_resid"]) <= 1e-3 * tol + 1e-15, (i, res, info[i])
+
+
+# one system much wider than the others (their blocks lie in a row), equal ones (one grid plane each), and a 2^4
+# system, for which the whole batch keeps launches for its scalar steps
+@pytest.mark.parametrize("lattices", [[(4, 4, 4, 4), (16, 16, 16, 4), (4, 6, 4, 2)], [(6, 6, 4, 4), (4, 6, 6, 4)],
+                                      [(2, 2, 2, 2), (4, 6, 4, 4)]])
+@pytest.mark.parametrize("inner,nrhs", [(64, 1), (32, 2)])
+@pytest.mark.parametrize("use_graph", [0, 1])
+def test_batch(mods, lattices, inner, nrhs, use_graph):
+    torch, fields, lqcd = mods
+    mu, tol = 0.05, 1e-10
+    print(f"\n[case] ctl step batch {lattices} inner={inner} nrhs={nrhs} graph={use_graph}", flush=True)
+    geoms, ops, Us, bs, xs, host = [], [], [], [], [], []
+    for i, L4 in enumerate(lattices):
+        kappa = 0.12 + 0.01 * i
+        U, b = gauge_field(L4, "exp", eps=0.4, seed=65 + i), gaussian_spinor(L4, seed=75 + i, nrhs=nrhs)
+        lat = fields.Lattice(L4, THETA)
+        geoms.append(lat.g)
+        ops.append(lqcd.op(kappa, mu))
+        Us.append(lat.gauge(U))
+        bs.append(lat.spinor(b if nrhs > 1 else b[0]))
+        xs.append(lat.zeros(lqcd.FIELD_SPINOR_FULL, 64, nrhs=nrhs))
+        host.append((L4, kappa, U, b, lat))
+    p = lqcd.solve_params(tol=tol, maxiter=2000, nrhs=nrhs, inner_prec=inner, inner_recon=18 if inner == 64 else 12,
+                          use_graph=use_graph)
+    ws = torch.empty(lqcd.lqcd_workspace_bytes_batch(geoms, ops, p), dtype=torch.uint8, device="cuda")
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        rc, infos = lqcd.cg_solve_batch(geoms, ops, Us, bs, xs, p, ws, stream=s)
+    torch.cuda.synchronize()
+    assert rc == 0, infos
+    for i, (L4, kappa, U, b, lat) in enumerate(host):
+        x = lat.unpack(xs[i], 64, nrhs=nrhs).reshape(nrhs, lat.V, 4, 3)
+        for k in range(nrhs):
+            tr = W.true_residual(U, x[k], b[k], L4, THETA, kappa, mu)
+            assert tr <= tol and abs(tr - infos[i][k]["true_resid"]) <= 1e-3 * tol, (i, k, tr)
