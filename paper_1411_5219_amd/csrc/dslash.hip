@@ -160,7 +160,12 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
     } else {
         p.lnt = nrhs == 1 && !args.full;
         p.split = form == FORM_WAVE ? 1 : 2;
-        plan_chunks(cfg, p.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
+        Launch c = cfg;
+        // in FP64 both parities crowd the L2: half the group of blocks, as in
+        // tiles (FP64/18 32^3x8 54.8 -> 50.4 us, 48^3x12 326 -> 319; FP32/12
+        // 48^3x12 is faster with whole groups, 136 us against 138)
+        if (args.full && prec == 64) c.block = cfg.block / 2;
+        plan_chunks(c, p.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
         p.block = dim3((unsigned)(kChunk * (p.split == 2 ? 2 : p.a.ch.nsub)));
     }
     return finish_plan(red, &p);
