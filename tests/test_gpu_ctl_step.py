@@ -109,3 +109,28 @@ def test_batch(mods, lattices, inner, nrhs, use_graph):
         for k in range(nrhs):
             tr = W.true_residual(U, x[k], b[k], L4, THETA, kappa, mu)
             assert tr <= tol and abs(tr - infos[i][k]["true_resid"]) <= 1e-3 * tol, (i, k, tr)
+
+
+def test_update_hops_over_many_blocks(mods):
+    """A mixed solve whose update hops stride over more than four rounds of blocks: thirteen right-hand sides that need
+    updates in different iterations, one of them zero."""
+    torch, fields, lqcd = mods
+    L4, nrhs, kappa, mu, tol = (24, 20, 24, 6), 13, 0.13, 0.05, 1e-10
+    print(f"\n[case] update hops over many blocks L={L4} nrhs={nrhs}", flush=True)
+    U, b = gauge_field(L4, "exp", eps=0.4, seed=91), gaussian_spinor(L4, seed=92, nrhs=nrhs)
+    b[5] = 0.0
+    for k in range(0, nrhs, 3):  # a point source
+        b[k] = 0.0
+        b[k].reshape(-1)[k] = 1.0
+    lat = fields.Lattice(L4, THETA)
+    o = lqcd.op(kappa, mu, 64, 18)
+    p = lqcd.solve_params(nrhs=nrhs, tol=tol, maxiter=500, eo=1, inner_prec=32, inner_recon=12, delta_reliable=0.02)
+    xd = lat.zeros(lqcd.FIELD_SPINOR_FULL, 64, nrhs=nrhs)
+    rc, info = lqcd.cg_solve(lat.g, o, lat.gauge(U), lat.spinor(b), xd, p, lat.workspace(o, p))
+    assert rc == 0, info
+    x = lat.unpack(xd, 64, nrhs=nrhs).reshape(nrhs, lat.V, 4, 3)
+    assert not x[5].any()
+    for k in (0, 4, 12):
+        tr = W.true_residual(U, x[k], b[k], L4, THETA, kappa, mu)
+        assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol, (k, tr, info[k])
+    assert all(i["true_resid"] <= tol for i in info)
