@@ -15,7 +15,7 @@
 // FP32/12 75.5 us), FP16 storage by memory and VALU issue together (33.9 us;
 // 39.7 with operands converted before use), small lattices by launch and
 // latency.  Both parities in one launch are bound by memory too, with each
-// link read once: 48^3x12 FP64/18 386 -> 330 us against two parities one after
+// link read once: 48^3x12 FP64/18 386 -> 320 us against two parities one after
 // the other.
 //
 // In the chiral basis gamma_mu = [[0, B_mu], [B_mu^+, 0]] with

@@ -682,10 +682,11 @@ __device__ __forceinline__ void wave_reduce(double (&v)[N])
 // Block-level part of a reduction: the wavefront folds its N sums with
 // butterfly shuffles, the waves are combined in LDS in wave order, and
 // thread 0 writes the block's N partial sums to partials[bid * N + j].
-// A separate one-block-per-right-hand-side kernel (k_finalize) sums the
-// partials in block order after the kernel boundary has made them visible,
-// so totals depend only on the grid shape, never on scheduling, and no
-// device-wide fence is needed.  Block size: a multiple of 64, <= 1024.
+// The partials are summed in a fixed order after the kernel boundary has made
+// them visible, by one block per right-hand side (k_finalize) or by every block
+// of the kernel that needs the result (CtlFold), so totals depend only on the
+// grid shapes, never on scheduling, and no device-wide fence is needed.  Block
+// size: a multiple of 64, <= 1024.
 template <int N>
 __device__ void block_reduce_store(double (&v)[N], double* partials, int bid)
 {

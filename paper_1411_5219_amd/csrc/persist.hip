@@ -6,7 +6,7 @@
 // per system and their per-system argument tables, see BatchProgram in
 // abi.cpp).  Here each step is a phase: the blocks of the grid stride over
 // the step's blocks of all systems and run the same block routine the
-// standalone kernel would (dslash_block, blas_block, convert_block); a step
+// standalone kernel would (rhs_block, blas_block, convert_block); a step
 // with a reduction is followed by its finalize as a phase of its own (one
 // block per system and right-hand side sums the partials in block order and
 // runs the solver's scalar step).  A step that would do nothing for every
