@@ -160,8 +160,11 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
+        # the handle of torch's current stream without the Stream object that
+        # torch.cuda.current_stream() makes around it: 0.3 us instead of 2.8, in
+        # calls that otherwise take 6 (16^3x8 FP64 hops back to back 8.8 -> 6.4)
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -161,3 +161,12 @@ def test_two_rhs_tiles_norms(mods):
     for k in range(2):
         tr = W.true_residual(U, got[k], b[k], L4, theta, kappa, mu)
         assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol
+
+
+def test_calls_follow_the_current_stream(mods):
+    torch, fields, lqcd = mods
+    s = torch.cuda.Stream()
+    assert lqcd._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(s):
+        assert lqcd._stream(None) == s.cuda_stream == lqcd._stream(s)
+    assert lqcd._stream(None) == torch.cuda.current_stream().cuda_stream != s.cuda_stream
