@@ -385,7 +385,6 @@ struct Op {
     hipStream_t s = nullptr;
     RedScratch rs;
     Launch dcfg, bcfg;
-    int form = FORM_BY_SIZE;
     // a scalar step its reductions' finalize runs first (see RedArgs)
     const double* pre_partials = nullptr;
     int pre_slots = 0, pre_fin = FIN_NONE;
@@ -397,7 +396,6 @@ struct Op {
     void tune()
     {
         dcfg = launch_for(nrhs > 1 ? LQCD_KERNEL_DSLASH_RHS : LQCD_KERNEL_DSLASH, prec, recon, g, nrhs);
-        dcfg.form = form;
         bcfg = launch_for(LQCD_KERNEL_BLAS, prec);
     }
 
@@ -896,7 +894,10 @@ int solver_finish(const Op& o, bool eo, char* bc, char* xc)
     return LQCD_OK;
 }
 
-// HopForm of a system's outer and inner hops (given for the systems of a batch).
+// HopForm of the iteration's outer (FP64) and inner hops, given for the systems
+// of a batch: chosen for the operator and the right-hand sides of the
+// iteration, so no other launch of the solve (set-up, start, the final
+// residual of the full matrix) may take them over.
 struct BatchForms {
     int outer, inner;
 };
@@ -923,11 +924,13 @@ struct CgSystem {
     Ctl *ctl0 = nullptr, *ctl1 = nullptr, *ctl2 = nullptr;
     double *part = nullptr, *part_r = nullptr, *part_u = nullptr;
     int slots = 0, slots_r = 0, slots_u = 0;
+    BatchForms forms = {FORM_BY_SIZE, FORM_BY_SIZE};
 
     int init(const Geom& g, const lqcd_op* opi, const void* U, const void* b, void* x, const lqcd_solve_params* prm_,
-             const SolverPlan& plan, hipStream_t s, BatchForms forms = {FORM_BY_SIZE, FORM_BY_SIZE})
+             const SolverPlan& plan, hipStream_t s, BatchForms f = {FORM_BY_SIZE, FORM_BY_SIZE})
     {
         prm = prm_;
+        forms = f;
         sp = plan;
         eo = prm->eo != 0;
         mixed = prm->inner_prec != 64;
@@ -943,7 +946,6 @@ struct CgSystem {
         o.pb = parity_bytes(g, 64);
         o.s = s;
         o.rs = sp.rs;
-        o.form = forms.outer;
         o.tune();
         pb = o.pb;
         fb = 2 * pb;
@@ -964,7 +966,6 @@ struct CgSystem {
             lo.recon = prm->inner_recon;
             lo.U = sp.Ulo;
             lo.pb = parity_bytes(g, lo.prec);
-            lo.form = forms.inner;
             lo.tune();
             xl = sp.lo[0];
             r = sp.lo[1];
@@ -979,6 +980,19 @@ struct CgSystem {
 
     // The operator of the iteration, and its vectors' stride between right-hand sides.
     const Op& inner() const { return mixed ? lo : o; }
+    // ... and that of its residual, as the iteration launches them.
+    Op iter_inner() const
+    {
+        Op q = inner();
+        q.dcfg.form = mixed ? forms.inner : forms.outer;
+        return q;
+    }
+    Op iter_outer() const
+    {
+        Op q = o;
+        q.dcfg.form = forms.outer;
+        return q;
+    }
     // Blocks per right-hand side of a BLAS step on the iteration's vectors.
     int64_t blas_blocks() const
     {
@@ -994,8 +1008,8 @@ struct CgSystem {
         // the two copies of the control blocks live in partials no step uses
         const int64_t region = sizeof(double) * (int64_t)sp.rs.capacity * nrhs;
         if (region < (int64_t)sizeof(Ctl) * nrhs) return false;
-        const int64_t n = inner().norm_slots(!eo), b = blas_blocks();
-        const int64_t pre = mixed ? o.norm_slots(false) : b;
+        const int64_t n = iter_inner().norm_slots(!eo), b = blas_blocks();
+        const int64_t pre = mixed ? iter_outer().norm_slots(false) : b;
         return n > 0 && (int64_t)sizeof(double) * nrhs * b * (2 * n + pre) <= kFoldBytes;
     }
     // Launches of one iteration.  The scalar steps are alpha (from ||w||^2), rr
@@ -1021,17 +1035,17 @@ struct CgSystem {
             ctl1 = reinterpret_cast<Ctl*>(part + 3 * region);
             ctl2 = mixed ? reinterpret_cast<Ctl*>(part + 4 * region) : ctl1;
         }
-        slots = inner().norm_slots(!eo);
+        h1 = h2 = iter_inner();
+        hu = iter_outer();
+        slots = h1.norm_slots(!eo);
         slots_r = (int)blas_blocks();
-        slots_u = mixed ? o.norm_slots(false) : 0;
-        h1 = h2 = inner();
+        slots_u = mixed ? hu.norm_slots(false) : 0;
         h2.rs.ctl = ctl2;
         if (!folded) {
             h2.pre_partials = mixed ? part_u : part_r;
             h2.pre_slots = mixed ? slots_u : slots_r;
             h2.pre_fin = mixed ? FIN_RU_RR : FIN_CG_RR;
         }
-        hu = o;
         hu.rs.ctl = ctl2;
         hu.rs.partials = part_u;
         if (mixed) {
@@ -1143,6 +1157,7 @@ struct CgSystem {
             // r = bhat - Mhat x (in FP64, stored low) ; rr_max ; x_low = 0 ; z = Mhat^+ r ; p = z
             Op first = hu;
             first.rs = o.rs;
+            first.dcfg = o.dcfg;
             LQCD_K(residual(first, nullptr, RED_NORM_LOW, FIN_RR_INIT, PRED_ACTIVE));
             LQCD_K(lo.blas(BLAS_ZERO, 1, PRED_ACTIVE, FIN_STORE, nullptr, xl));
         }
@@ -1376,9 +1391,9 @@ BatchForms batch_forms(const std::vector<Geom>& g, const lqcd_op* ops, const lqc
     if (prm->persistent) return {FORM_TILE_WAVE, FORM_TILE_WAVE};
     int recon = 18;
     for (size_t i = 0; i < g.size(); ++i) recon = std::min(recon, (int)ops[i].recon);
-    const int want = FORM_BY_SIZE, n = (int)g.size();
-    return {hop_form(64, recon, prm->eo == 0, g.data(), n, prm->nrhs, want),
-            hop_form(prm->inner_prec, prm->inner_recon, prm->eo == 0, g.data(), n, prm->nrhs, want)};
+    const int n = (int)g.size();
+    return {hop_form(64, recon, prm->eo == 0, g.data(), n, prm->nrhs),
+            hop_form(prm->inner_prec, prm->inner_recon, prm->eo == 0, g.data(), n, prm->nrhs)};
 }
 static_assert(kMaxSteps <= kMaxPersistSteps, "the persistent program holds every recorded step");
 // Polls of a grid barrier slot before the persistent kernel gives up (each

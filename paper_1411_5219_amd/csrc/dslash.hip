@@ -6,11 +6,6 @@
 
 namespace lqcd {
 
-// Right-hand sides of a block (the kernel's bound).  Their spinors share the
-// XCD's L2: 32^3x8 FP32/12 Schur on 12 right-hand sides 207 us with 4 per
-// block, 218 with 3, 245 with 2; 8 per block read more from beyond L2 (296).
-constexpr int kMaxTile = 4;
-
 hipError_t launch_dslash_64(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
                             dim3 block, hipStream_t s);
 hipError_t launch_dslash_32(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
@@ -82,43 +77,11 @@ static bool storage_built(int prec, int recon)
            (prec == 16 && recon == 12);
 }
 
-// Which waves serve a launch's sites and right-hand sides, for the n systems
-// of a batch together.
-// One right-hand side: a pair of waves per chunk (see dslash_block) except
-// where one wave per chunk fills every wave slot of the chip, two per SIMD at
-// its register count, planes split evenly into blocks of such waves, and each
-// link is read once and whole: there FP64/18, which streams at the memory's
-// rate either way, loses by the second wave's indices and the exchange
-// (48^3x12 186 us with one wave, 193 with two; 32^3x8, exactly full, 36.5 and
-// 38.2; 24^3x8, half full, 20.2 and 18.5; 40^3x6, uneven, 66 and 59; FP64/12
-// 48^3x8 103 and 99).
-// Several: a tile of them per block (hop_rhs.h) once the pairs of all of them
-// would no longer run at once, two waves per SIMD in FP64 and three below;
-// before that the pairs are faster, each on its own right-hand side (Schur
-// complement, FP32/12: 8^3x4 with four 9.8 us against 13.3, 16^3x8 with four
-// 15.0 against 16.8, with twelve 33.1 against 29.7; FP64/18 20^3x8 with two
-// 35.6 against 45.5, 20^3x6 with four 47 against 41).  FP64/12 stays with pairs
-// up to five waves per SIMD: tiles hold all 18 reals in LDS (20^3x8 with four
-// 53 against 61, 24^3x8 with three 71 against 68); so does FP16 storage with
-// two or three, whose tiles wait for LDS (48^3x12 with two 135 against 147,
-// 28^3x8 with three 34.0 against 36.4, with four 41.0 against 40.6).
-int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want)
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs)
 {
-    if (want != FORM_BY_SIZE) return want;
-    int64_t chunks = 0;
-    bool even = true;
-    for (int i = 0; i < n; ++i) {
-        const ChunkArgs c = plan_chunk_order(chunk_grid(g[i]), 1, 256, 1, 4);
-        chunks += (g[i].Vh + kChunk - 1) / kChunk;
-        even = even && c.planes == 1 && c.nsub > 1 && c.chunks % c.nsub == 0;
-    }
-    if (nrhs > 1) {
-        const int64_t waves = 2 * chunks * nrhs;
-        const bool pair = prec == 64 ? waves <= (recon == 12 ? 5 : 2) * kSimds
-                                     : waves <= 3 * kSimds || (prec == 16 && nrhs <= 3);
-        return pair ? FORM_PAIR : FORM_TILE;
-    }
-    return prec == 64 && recon == 18 && !full && even && chunks >= 2 * kSimds ? FORM_WAVE : FORM_PAIR;
+    std::vector<ChunkGrid> c;
+    for (int i = 0; i < n; ++i) c.push_back(chunk_grid(g[i]));
+    return hop_form(prec, recon, full, c.data(), n, nrhs);
 }
 
 hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
@@ -132,13 +95,14 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
     p.dag = dagger;
     p.red = red;
     p.a = args;
-    const int form = hop_form(prec, recon, args.full != 0, &args.g, 1, nrhs, cfg.form);
-    p.halves = 1;
-    if (form == FORM_TILE || form == FORM_TILE_WAVE) {
-        // Several right-hand sides share a block and the links in its LDS:
-        // as few tiles of at most kMaxTile as there can be, of even sizes
-        const int ntiles = (nrhs + kMaxTile - 1) / kMaxTile, tile = (nrhs + ntiles - 1) / ntiles;
-        Launch c = cfg;
+    const ChunkGrid grid = chunk_grid(args.g);
+    const int form = cfg.form != FORM_BY_SIZE ? cfg.form : hop_form(prec, recon, args.full != 0, &grid, 1, nrhs);
+    const HopShape h = hop_shape(form, args.full != 0, nrhs);
+    p.split = h.split;
+    p.halves = h.halves;
+    p.lnt = h.lnt;
+    Launch c = cfg;
+    if (h.split == 0) {
         // half the group of blocks where a block's spinors are twice as large
         // or both parities share the L2 (32^3x8, 4 right-hand sides: FP64
         // Schur 198 us against 204, FP64 full 173 against 203, FP32/18 full 61
@@ -151,22 +115,16 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
         // per compute unit, in few rounds takes the layers with the fewest idle
         // lanes (20^3x8
         // makes 512 blocks of five planes, 520 of four: FP64/18, three 52 -> 41 us)
-        const int64_t blocks = (int64_t)((args.g.Vh + kChunk - 1) / kChunk) * ntiles;
-        plan_chunks(c, 1, tile, nrhs, &p, prec == 16 ? 20 : prec == 64 && blocks <= 2 * kSimds ? 40 : 16);
-        p.split = 0;
-        p.lnt = false;
-        p.halves = form == FORM_TILE && tile <= 2 ? 2 : 1;
-        p.block = dim3((unsigned)(kChunk * tile * p.halves));
+        const int64_t blocks = (int64_t)((args.g.Vh + kChunk - 1) / kChunk) * ((nrhs + h.tile - 1) / h.tile);
+        plan_chunks(c, 1, h.tile, nrhs, &p, prec == 16 ? 20 : prec == 64 && blocks <= 2 * kSimds ? 40 : 16);
+        p.block = dim3((unsigned)(kChunk * h.tile * h.halves));
     } else {
-        p.lnt = nrhs == 1 && !args.full;
-        p.split = form == FORM_WAVE ? 1 : 2;
-        Launch c = cfg;
         // in FP64 both parities crowd the L2: half the group of blocks, as in
         // tiles (FP64/18 32^3x8 54.8 -> 50.4 us, 48^3x12 326 -> 319; FP32/12
         // 48^3x12 is faster with whole groups, 136 us against 138)
         if (args.full && prec == 64) c.block = cfg.block / 2;
-        plan_chunks(c, p.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
-        p.block = dim3((unsigned)(kChunk * (p.split == 2 ? 2 : p.a.ch.nsub)));
+        plan_chunks(c, h.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
+        p.block = dim3((unsigned)(kChunk * (h.split == 2 ? 2 : p.a.ch.nsub)));
     }
     return finish_plan(red, &p);
 }

@@ -568,8 +568,7 @@ static hipError_t launch_dag(bool dag, int red, const DslashLaunch& L, dim3 grid
 }
 
 // Streaming link loads for one parity (each link has one reader), cached ones
-// for both parities in one launch (each link has two).  One wave per chunk is
-// built only where it can be the faster split: FP64, one parity.
+// for both parities in one launch (each link has two).
 template <int PREC, int RECON>
 inline hipError_t launch_hop(int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
                              hipStream_t s)
@@ -577,7 +576,7 @@ inline hipError_t launch_hop(int split, bool lnt, bool dag, int red, const Dslas
     if (split == 2)
         return lnt ? launch_dag<PREC, RECON, true, 2>(dag, red, L, grid, block, s)
                    : launch_dag<PREC, RECON, false, 2>(dag, red, L, grid, block, s);
-    if constexpr (PREC == 64)
+    if constexpr (hop_built(PREC, 1, true))
         if (split == 1 && lnt) return launch_dag<PREC, RECON, true, 1>(dag, red, L, grid, block, s);
     return hipErrorInvalidValue;
 }

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "chunks.h"
+#include "hop_form.h"
 #include "solver_ctl.h"
 
 namespace lqcd {
@@ -45,8 +46,6 @@ enum Pred {
 
 // Most values one reduction produces per block (BiCGStab(2)'s Gram step).
 constexpr int kMaxFin = 5;
-
-constexpr int kSimds = 1024;  // 256 compute units of 4 SIMDs
 
 struct RedArgs {
     double* partials;       // [nrhs][nblocks][N]
@@ -112,17 +111,11 @@ struct Launch {
     int rhs_group = 4; // right-hand sides put four of them in a block whatever these say
     int ygroup = 1;    // blocks of a plane interleaved after t, in units of the block request (1: none)
     int rhs_lanes = 1;
-    int form = 0;      // HopForm of Wilson hops (set where several launches must run the same kernel)
+    int form = FORM_BY_SIZE;  // HopForm of Wilson hops (given where several launches must run the same kernel)
 };
 
-// How the waves of a Wilson hop share sites and right-hand sides: one wave or
-// a pair of waves per chunk of 64 sites and right-hand side, or a tile of
-// right-hand sides per chunk with its links in LDS, and in this one wave per
-// right-hand side, or (FORM_TILE only, by size) two.
-enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3, FORM_TILE_WAVE = 4 };
-// The form for launches on nrhs right-hand sides of the n lattices g (want if
-// not by size).  FORM_WAVE exists for FP64 on one right-hand side and one parity.
-int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, int want);
+// hop_form of the n lattices g (by size).
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs);
 
 // Finalize of one reduction of one system.
 struct FinArgs {
