@@ -199,11 +199,13 @@ typedef struct {
  *           XCD's L2 cache; k in 2..64: the same blocks in z-slabs of
  *           T planes (T the largest divisor of Lz not above k), z fastest
  *           within a slab, then t, then the slab, which brings the z
- *           neighbours closer in the block order.
+ *           neighbours closer in the block order.  With several right-hand
+ *           sides and 1, lattices of a long time extent whose planes do not
+ *           fill whole chunks run in memory order.
  *   rhs_tile (1, 2 or 4), rhs_group (0, or 2..16), rhs_lanes (0, 1, 2, 4, 8 or
  *           16): checked and kept, without effect: launches on several
  *           right-hand sides put up to four of them in a block, which share
- *           its links.
+ *           its links, or lay their blocks next to each other, by size.
  *   ygroup  hop kernels with order >= 1: 0 or 1 (none), or G in 2..64: G times
  *           as many neighbouring blocks of an xy plane run right after t (then
  *           z), so the rows a block's y-hops read beyond its edge come from L2;

@@ -990,7 +990,8 @@ struct CgSystem {
     Op iter_outer() const
     {
         Op q = o;
-        q.dcfg.form = forms.outer;
+        q.dcfg.form = mixed && forms.outer == FORM_BY_SIZE ? hop_form(64, o.recon, false, &o.g, 1, nrhs, true)
+                                                           : forms.outer;
         return q;
     }
     // Blocks per right-hand side of a BLAS step on the iteration's vectors.
@@ -1392,7 +1393,7 @@ BatchForms batch_forms(const std::vector<Geom>& g, const lqcd_op* ops, const lqc
     int recon = 18;
     for (size_t i = 0; i < g.size(); ++i) recon = std::min(recon, (int)ops[i].recon);
     const int n = (int)g.size();
-    return {hop_form(64, recon, prm->eo == 0, g.data(), n, prm->nrhs),
+    return {hop_form(64, recon, prm->eo == 0, g.data(), n, prm->nrhs, prm->inner_prec != 64),
             hop_form(prm->inner_prec, prm->inner_recon, prm->eo == 0, g.data(), n, prm->nrhs)};
 }
 static_assert(kMaxSteps <= kMaxPersistSteps, "the persistent program holds every recorded step");
@@ -1477,8 +1478,8 @@ bool same_kernel(const Step& a, const Step& b)
 {
     if (a.kind != b.kind) return false;
     if (a.kind == STEP_DSLASH)
-        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split && a.d.halves == b.d.halves &&
-               a.d.lnt == b.d.lnt && a.d.red == b.d.red &&
+        return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split &&
+               a.d.halves == b.d.halves && a.d.lnt == b.d.lnt && a.d.next == b.d.next && a.d.red == b.d.red &&
                a.d.dag == b.d.dag && a.d.a.nrhs == b.d.a.nrhs && a.d.grid.y == b.d.grid.y;
     if (a.kind == STEP_BLAS)
         return a.b.prec == b.b.prec && a.b.op == b.b.op && a.b.nrhs == b.b.nrhs && a.b.block.x == b.b.block.x;

@@ -9,19 +9,6 @@
 
 namespace lqcd {
 
-// Right-hand-side tile and logical block of hardware block bx.  Every tile
-// takes a multiple of 8 hardware blocks, so that with the XCD remap a spatial
-// block runs on the same XCD for every tile and a later tile can find the
-// links in that XCD's L2; false for the padding.
-__device__ __forceinline__ bool tile_block(const DslashArgs& a, int bx, uint32_t* tile, uint32_t* b)
-{
-    *tile = fdiv(a.ch.stride, (uint32_t)bx);
-    const int x = bx - (int)(*tile * a.ch.stride.d);
-    if (x >= a.ch.nblk) return false;
-    *b = (uint32_t)(a.swizzle ? xcd_swizzle(x, a.ch.nblk) : x);
-    return true;
-}
-
 // Neighbour of an output site for hop K = 2 mu + (0 forward, 1 backward):
 // the neighbour's parity-local index, the link block (mu, parity) and the
 // parity-local site the link is stored at, and whether the hop crosses the

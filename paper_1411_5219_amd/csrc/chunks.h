@@ -50,8 +50,11 @@ struct ChunkArgs {
     int nsub;        // chunks per block
     int nsp;         // spatial blocks per parity
     int tile;        // right-hand sides per block
-    int nblk;        // blocks of one right-hand-side tile (tiles run one after the other)
-    FastDiv stride;  // hardware blocks of a tile: nblk, with several tiles rounded up to a multiple of 8
+    int nblk;        // blocks of one right-hand-side tile
+    // Tiles run one after the other, or (hops by pairs of waves) next to each
+    // other on each spatial block.
+    FastDiv stride;  // one after the other: hardware blocks of a tile, nblk, with several rounded up to a multiple of 8
+    FastDiv tiles;   // next to each other: how many
     FastDiv Lxh, Ly, Lz, Lt, plane, group, slabs, ztile;
 };
 
@@ -60,6 +63,25 @@ struct ChunkGrid {
     int L[4];
     int Lxh, Vh;
 };
+
+// xy planes of a layer: one where its last chunk leaves at most one of idle_max
+// of the lanes idle, else the fewest planes (a divisor of Lz up to 8) that do,
+// or that leave the fewest idle: 20^3x8 has 200 sites per plane, 78% of four
+// chunks, but 800 in four planes, 96% of 13 (FP64 Schur complement on four
+// right-hand sides 66.7 us with one plane, 59.9 with four).
+inline int layer_planes(const ChunkGrid& g, int idle_max)
+{
+    const int plane = g.Lxh * g.L[1];
+    auto lanes_of = [&](int n) { return (int64_t)((plane * n + kChunk - 1) / kChunk) * kChunk; };
+    int planes = 1;
+    for (int n = 1; n <= 8 && n <= g.L[2]; ++n) {
+        if (g.L[2] % n) continue;
+        const int64_t idle = lanes_of(n) - (int64_t)plane * n, best = lanes_of(planes) - (int64_t)plane * planes;
+        if (idle_max * best <= lanes_of(planes)) break;
+        if (idle * lanes_of(planes) < best * lanes_of(n)) planes = n;
+    }
+    return planes;
+}
 
 // Plan for blocks of at most maxsub chunks of 64 sites.  order 0: memory
 // order; k >= 1: layers, in z-slabs of the largest divisor of the layers with at most
@@ -70,20 +92,8 @@ inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int 
     ChunkArgs c = {};
     const int plane = g.Lxh * g.L[1];
     const int64_t flat = (g.Vh + kChunk - 1) / kChunk;
-    // One plane per layer where its last chunk leaves at most one of idle_max of
-    // the lanes idle, else the fewest planes (a divisor of Lz up to 8) that do,
-    // or that leave the fewest idle: 20^3x8 has 200 sites per plane, 78% of four
-    // chunks, but 800 in four planes, 96% of 13 (FP64 Schur complement on four
-    // right-hand sides 66.7 us with one plane, 59.9 with four).
     auto chunks_of = [&](int n) { return (plane * n + kChunk - 1) / kChunk; };
-    c.planes = 1;
-    for (int n = 1; n <= 8 && n <= g.L[2]; ++n) {
-        if (g.L[2] % n) continue;
-        const int64_t idle = (int64_t)chunks_of(n) * kChunk - (int64_t)plane * n;
-        const int64_t best = (int64_t)chunks_of(c.planes) * kChunk - (int64_t)plane * c.planes;
-        if (idle_max * best <= (int64_t)chunks_of(c.planes) * kChunk) break;
-        if (idle * chunks_of(c.planes) < best * chunks_of(n)) c.planes = n;
-    }
+    c.planes = layer_planes(g, idle_max);
     const int per = chunks_of(c.planes), layers = g.L[2] / c.planes;
     // chunks of layers unless memory order is asked for; a lattice so wide and
     // flat that its ragged layers would take more slots than the caller's
@@ -122,6 +132,55 @@ inline ChunkArgs plan_chunk_order(const ChunkGrid& g, int order, int block, int 
     c.slabs = make_fastdiv((uint32_t)(layers / ztile));
     c.ztile = make_fastdiv((uint32_t)ztile);
     return c;
+}
+
+// Lays out a launch of `slots` blocks per tile (all parities); returns its
+// hardware blocks.
+inline unsigned plan_tiles(ChunkArgs* c, int slots, int tile, bool adjacent, int nrhs)
+{
+    const unsigned ntiles = (unsigned)((nrhs + tile - 1) / tile), n = (unsigned)slots;
+    const unsigned stride = ntiles > 1 && !adjacent ? (n + 7) / 8 * 8 : n;
+    c->tile = tile;
+    c->nblk = slots;
+    c->tiles = make_fastdiv(ntiles);
+    c->stride = make_fastdiv(stride);
+    return stride * ntiles;
+}
+
+// Block index remap that hands each XCD a contiguous range of logical
+// blocks.  Workgroups are dispatched round-robin over the 8 XCDs, so
+// hardware block b runs on XCD b % 8; giving that XCD logical blocks
+// [start(b%8), start(b%8) + count) keeps neighbouring sites in one L2.
+LQCD_CHUNK_FN int xcd_swizzle(int b, int nb)
+{
+    const int q = nb >> 3, rem = nb & 7;
+    const int xcd = b & 7, k = b >> 3;
+    const int start = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
+    return start + k;
+}
+
+// Right-hand-side tile and logical block of hardware block bx, tiles one after
+// the other.  Every tile takes a multiple of 8 hardware blocks, so that with
+// the XCD remap a spatial block runs on the same XCD for every tile and a later
+// tile can find the links in that XCD's L2; false for the padding.
+LQCD_CHUNK_FN bool tile_after_tile(const ChunkArgs& c, int swizzle, int bx, uint32_t* tile, uint32_t* b)
+{
+    *tile = fdiv(c.stride, (uint32_t)bx);
+    const int x = bx - (int)(*tile * c.stride.d);
+    if (x >= c.nblk) return false;
+    *b = (uint32_t)(swizzle ? xcd_swizzle(x, c.nblk) : x);
+    return true;
+}
+
+// The same with the tiles next to each other: with the XCD remap they run one
+// after the other on one XCD, and all but the first find the links in its L2.
+// No hardware block is padding: a second test at the top of the kernel, or the
+// two orders as one function, lengthened the smallest hops by 0.1 to 0.8 us.
+LQCD_CHUNK_FN void tile_by_tile(const ChunkArgs& c, int swizzle, int bx, uint32_t* tile, uint32_t* b)
+{
+    const uint32_t y = (uint32_t)(swizzle ? xcd_swizzle(bx, c.nblk * (int)c.tiles.d) : bx);
+    *b = fdiv(c.tiles, y);
+    *tile = y - *b * c.tiles.d;
 }
 
 struct SitePos {

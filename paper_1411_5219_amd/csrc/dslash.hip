@@ -6,12 +6,12 @@
 
 namespace lqcd {
 
-hipError_t launch_dslash_64(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
-                            dim3 block, hipStream_t s);
-hipError_t launch_dslash_32(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
-                            dim3 block, hipStream_t s);
-hipError_t launch_dslash_16(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
-                            dim3 block, hipStream_t s);
+hipError_t launch_dslash_64(int recon, int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L,
+                            dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_dslash_32(int recon, int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L,
+                            dim3 grid, dim3 block, hipStream_t s);
+hipError_t launch_dslash_16(int recon, int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L,
+                            dim3 grid, dim3 block, hipStream_t s);
 
 hipError_t launch_stag_64(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
 hipError_t launch_stag_32(int recon, int red, bool lnt, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s);
@@ -38,9 +38,9 @@ static hipError_t launch_dslash_prec(const DslashPlan& p, const DslashLaunch& L,
         if (p.prec == 16) return launch_rhs_16(p.recon, p.halves, p.dag, p.red, L, grid, p.block, s);
         return hipErrorInvalidValue;
     }
-    if (p.prec == 64) return launch_dslash_64(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
-    if (p.prec == 32) return launch_dslash_32(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
-    if (p.prec == 16) return launch_dslash_16(p.recon, p.split, p.lnt, p.dag, p.red, L, grid, p.block, s);
+    if (p.prec == 64) return launch_dslash_64(p.recon, p.split, p.lnt, p.next, p.dag, p.red, L, grid, p.block, s);
+    if (p.prec == 32) return launch_dslash_32(p.recon, p.split, p.lnt, p.next, p.dag, p.red, L, grid, p.block, s);
+    if (p.prec == 16) return launch_dslash_16(p.recon, p.split, p.lnt, p.next, p.dag, p.red, L, grid, p.block, s);
     return hipErrorInvalidValue;
 }
 
@@ -48,19 +48,14 @@ static ChunkGrid chunk_grid(const Geom& g) { return ChunkGrid{{g.L[0], g.L[1], g
 
 // Block order and grid of a launch whose blocks cover at most maxsub chunks
 // of 64 sites each, for `tile` right-hand sides per block.
-static void plan_chunks(const Launch& cfg, int maxsub, int tile, int nrhs, DslashPlan* p, int idle_max = 20)
+static void plan_chunks(const Launch& cfg, int maxsub, int tile, bool adjacent, int nrhs, DslashPlan* p, int idle_max = 20)
 {
     DslashArgs& a = p->a;
     a.swizzle = cfg.swizzle;
     a.nrhs = nrhs;
     a.ch = plan_chunk_order(chunk_grid(a.g), cfg.order, cfg.block, cfg.ygroup, maxsub, idle_max);
-    a.ch.tile = tile;
     p->slots = a.ch.nsp * (a.full ? 2 : 1);
-    a.ch.nblk = p->slots;
-    const int ntiles = (nrhs + tile - 1) / tile;
-    const unsigned stride = ntiles > 1 ? (p->slots + 7) / 8 * 8 : p->slots;
-    a.ch.stride = make_fastdiv(stride);
-    p->grid = dim3(stride * (unsigned)ntiles);
+    p->grid = dim3(plan_tiles(&a.ch, p->slots, tile, adjacent, nrhs));
     a.gx = (int)p->grid.x;
 }
 
@@ -77,11 +72,11 @@ static bool storage_built(int prec, int recon)
            (prec == 16 && recon == 12);
 }
 
-int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs)
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, bool rare)
 {
     std::vector<ChunkGrid> c;
     for (int i = 0; i < n; ++i) c.push_back(chunk_grid(g[i]));
-    return hop_form(prec, recon, full, c.data(), n, nrhs);
+    return hop_form(prec, recon, full, c.data(), n, nrhs, rare);
 }
 
 hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& args, int nrhs, const Launch& cfg,
@@ -97,35 +92,23 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
     p.a = args;
     const ChunkGrid grid = chunk_grid(args.g);
     const int form = cfg.form != FORM_BY_SIZE ? cfg.form : hop_form(prec, recon, args.full != 0, &grid, 1, nrhs);
-    const HopShape h = hop_shape(form, args.full != 0, nrhs);
+    const HopShape h = hop_shape(prec, recon, args.full != 0, grid, nrhs, form);
     p.split = h.split;
     p.halves = h.halves;
     p.lnt = h.lnt;
+    p.next = h.next;
     Launch c = cfg;
-    if (h.split == 0) {
-        // half the group of blocks where a block's spinors are twice as large
-        // or both parities share the L2 (32^3x8, 4 right-hand sides: FP64
-        // Schur 198 us against 204, FP64 full 173 against 203, FP32/18 full 61
-        // against 75; FP32 Schur, 12 right-hand sides, is faster in groups of
-        // 4: 207 us against 213)
-        if (prec == 64 || args.full) c.block = cfg.block / 2;
-        // FP32 and FP64 tiles take a plane of which a sixteenth is idle by itself
-        // (44^3x6, four right-hand sides: FP64 386 us against 439, FP32 145
-        // against 175; FP16 is faster with fewer idle lanes); FP64, two blocks
-        // per compute unit, in few rounds takes the layers with the fewest idle
-        // lanes (20^3x8
-        // makes 512 blocks of five planes, 520 of four: FP64/18, three 52 -> 41 us)
-        const int64_t blocks = (int64_t)((args.g.Vh + kChunk - 1) / kChunk) * ((nrhs + h.tile - 1) / h.tile);
-        plan_chunks(c, 1, h.tile, nrhs, &p, prec == 16 ? 20 : prec == 64 && blocks <= 2 * kSimds ? 40 : 16);
-        p.block = dim3((unsigned)(kChunk * h.tile * h.halves));
-    } else {
-        // in FP64 both parities crowd the L2: half the group of blocks, as in
-        // tiles (FP64/18 32^3x8 54.8 -> 50.4 us, 48^3x12 326 -> 319; FP32/12
-        // 48^3x12 is faster with whole groups, 136 us against 138)
-        if (args.full && prec == 64) c.block = cfg.block / 2;
-        plan_chunks(c, h.split == 2 ? 1 : cfg.block / kChunk, 1, nrhs, &p);
-        p.block = dim3((unsigned)(kChunk * (h.split == 2 ? 2 : p.a.ch.nsub)));
-    }
+    // half the group of blocks where a tile's spinors are twice as large or
+    // both parities share the L2 (32^3x8, 4 right-hand sides: FP64 Schur 198 us
+    // against 204, FP64 full 173 against 203, FP32/18 full 61 against 75; FP32
+    // Schur, 12 right-hand sides, is faster in groups of 4: 207 us against 213;
+    // one right-hand side, FP64/18 full 32^3x8 54.8 -> 50.4, 48^3x12 326 -> 319,
+    // but FP32/12 48^3x12 136 us with whole groups, 138 with halves)
+    if (h.split == 0 ? prec == 64 || args.full : prec == 64 && args.full) c.block = cfg.block / 2;
+    if (h.memory && cfg.order == 1) c.order = 0;
+    plan_chunks(c, h.split == 1 ? cfg.block / kChunk : 1, h.tile, h.next, nrhs, &p, h.idle);
+    const int waves = h.split == 0 ? h.tile * h.halves : h.split == 2 ? 2 : p.a.ch.nsub;
+    p.block = dim3((unsigned)(kChunk * waves));
     return finish_plan(red, &p);
 }
 
@@ -192,8 +175,9 @@ hipError_t plan_stag_hop(int prec, int recon, int red, const DslashArgs& args, i
     p.a = args;
     p.split = 1;
     p.halves = 1;
+    p.next = false;
     p.lnt = nrhs == 1 && !args.full;
-    plan_chunks(cfg, cfg.block / kChunk, 1, nrhs, &p);
+    plan_chunks(cfg, cfg.block / kChunk, 1, false, nrhs, &p);
     p.block = dim3((unsigned)(kChunk * p.a.ch.nsub));
     return finish_plan(red, &p);
 }

@@ -3,11 +3,11 @@
 
 namespace lqcd {
 
-hipError_t launch_dslash_64(int recon, int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid,
-                            dim3 block, hipStream_t s)
+hipError_t launch_dslash_64(int recon, int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L,
+                            dim3 grid, dim3 block, hipStream_t s)
 {
-    if (recon == 18) return launch_hop<64, 18>(split, lnt, dag, red, L, grid, block, s);
-    if (recon == 12) return launch_hop<64, 12>(split, lnt, dag, red, L, grid, block, s);
+    if (recon == 18) return launch_hop<64, 18>(split, lnt, next, dag, red, L, grid, block, s);
+    if (recon == 12) return launch_hop<64, 12>(split, lnt, next, dag, red, L, grid, block, s);
     return hipErrorInvalidValue;
 }
 

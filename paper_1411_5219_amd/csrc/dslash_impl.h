@@ -453,7 +453,7 @@ struct SplitLds<R, 1> {};
 // 13.9 -> 7.0, 24^3x8 20.2 -> 18.5; FP32/12 20^3x6 8.1 -> 6.3), and a shorter
 // drain at the end of a large launch (48^3x12 FP32/12 77.0 -> 75.5).  The
 // plan chooses (see plan_dslash).
-template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT, bool NEXT>
 __device__ __forceinline__ void dslash_block(const DslashArgs& a, int bx)
 {
     using R = typename SpinorIO<PREC>::R;
@@ -461,7 +461,9 @@ __device__ __forceinline__ void dslash_block(const DslashArgs& a, int bx)
     constexpr int D = HopTune<PREC, SPLIT>::depth;
     __shared__ SplitLds<R, SPLIT> lds;
     uint32_t rhs, b;
-    if (!tile_block(a, bx, &rhs, &b) || pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
+    if constexpr (NEXT) tile_by_tile(a.ch, a.swizzle, bx, &rhs, &b);
+    else if (!tile_after_tile(a.ch, a.swizzle, bx, &rhs, &b)) return;
+    if (pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
     const int lane = (int)threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     int p = a.parity;
@@ -514,17 +516,17 @@ __device__ __forceinline__ void dslash_block(const DslashArgs& a, int bx)
     }
 }
 
-template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT, bool NEXT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopTune<PREC, SPLIT>::waves)))
 k_dslash_eo(const DslashArgs a)
 {
-    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(a, blockIdx.x);
+    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT, NEXT>(a, blockIdx.x);
 }
 
 // Several systems (lattices of different sizes) in one launch: block x of the
 // flattened grid belongs to system s with offs[s] <= x < offs[s + 1]; each
 // system's arguments come from the device table tab.
-template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT, bool NEXT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HopTune<PREC, SPLIT>::waves)))
 k_dslash_eo_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
@@ -532,52 +534,53 @@ k_dslash_eo_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ of
     const int s = batch_system(offs, nsys, &bx);
     // blocks past the system's own grid are padding
     if (bx >= tab[s].gx) return;
-    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT>(tab[s], bx);
+    dslash_block<PREC, RECON, DAG, RED, LNT, SPLIT, NEXT>(tab[s], bx);
 }
 
-template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool DAG, int RED, bool LNT, int SPLIT, bool NEXT>
 static hipError_t launch_one(const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
     if (L.tab)
-        hipLaunchKernelGGL((k_dslash_eo_batch<PREC, RECON, DAG, RED, LNT, SPLIT>), grid, block, 0, s, L.tab, L.offs,
+        hipLaunchKernelGGL((k_dslash_eo_batch<PREC, RECON, DAG, RED, LNT, SPLIT, NEXT>), grid, block, 0, s, L.tab, L.offs,
                            L.nsys);
-    else hipLaunchKernelGGL((k_dslash_eo<PREC, RECON, DAG, RED, LNT, SPLIT>), grid, block, 0, s, *L.a);
+    else hipLaunchKernelGGL((k_dslash_eo<PREC, RECON, DAG, RED, LNT, SPLIT, NEXT>), grid, block, 0, s, *L.a);
     return hipGetLastError();
 }
 
-template <int PREC, int RECON, bool DAG, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool DAG, bool LNT, int SPLIT, bool NEXT>
 static hipError_t launch_red(int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
     switch (red) {
-    case RED_NONE: return launch_one<PREC, RECON, DAG, RED_NONE, LNT, SPLIT>(L, grid, block, s);
-    case RED_NORM: return launch_one<PREC, RECON, DAG, RED_NORM, LNT, SPLIT>(L, grid, block, s);
-    case RED_NORM_DS: return launch_one<PREC, RECON, DAG, RED_NORM_DS, LNT, SPLIT>(L, grid, block, s);
-    case RED_DOT_AUX: return launch_one<PREC, RECON, DAG, RED_DOT_AUX, LNT, SPLIT>(L, grid, block, s);
+    case RED_NONE: return launch_one<PREC, RECON, DAG, RED_NONE, LNT, SPLIT, NEXT>(L, grid, block, s);
+    case RED_NORM: return launch_one<PREC, RECON, DAG, RED_NORM, LNT, SPLIT, NEXT>(L, grid, block, s);
+    case RED_NORM_DS: return launch_one<PREC, RECON, DAG, RED_NORM_DS, LNT, SPLIT, NEXT>(L, grid, block, s);
+    case RED_DOT_AUX: return launch_one<PREC, RECON, DAG, RED_DOT_AUX, LNT, SPLIT, NEXT>(L, grid, block, s);
     default: break;
     }
     if constexpr (PREC == 64 && !DAG)
-        if (red == RED_NORM_LOW) return launch_one<PREC, RECON, DAG, RED_NORM_LOW, LNT, SPLIT>(L, grid, block, s);
+        if (red == RED_NORM_LOW) return launch_one<PREC, RECON, DAG, RED_NORM_LOW, LNT, SPLIT, NEXT>(L, grid, block, s);
     return hipErrorInvalidValue;
 }
 
-template <int PREC, int RECON, bool LNT, int SPLIT>
+template <int PREC, int RECON, bool LNT, int SPLIT, bool NEXT>
 static hipError_t launch_dag(bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block, hipStream_t s)
 {
-    return dag ? launch_red<PREC, RECON, true, LNT, SPLIT>(red, L, grid, block, s)
-               : launch_red<PREC, RECON, false, LNT, SPLIT>(red, L, grid, block, s);
+    return dag ? launch_red<PREC, RECON, true, LNT, SPLIT, NEXT>(red, L, grid, block, s)
+               : launch_red<PREC, RECON, false, LNT, SPLIT, NEXT>(red, L, grid, block, s);
 }
 
 // Streaming link loads for one parity (each link has one reader), cached ones
 // for both parities in one launch (each link has two).
 template <int PREC, int RECON>
-inline hipError_t launch_hop(int split, bool lnt, bool dag, int red, const DslashLaunch& L, dim3 grid, dim3 block,
-                             hipStream_t s)
+inline hipError_t launch_hop(int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L, dim3 grid,
+                             dim3 block, hipStream_t s)
 {
+    if (split == 2 && next) return lnt ? hipErrorInvalidValue : launch_dag<PREC, RECON, false, 2, true>(dag, red, L, grid, block, s);
     if (split == 2)
-        return lnt ? launch_dag<PREC, RECON, true, 2>(dag, red, L, grid, block, s)
-                   : launch_dag<PREC, RECON, false, 2>(dag, red, L, grid, block, s);
-    if constexpr (hop_built(PREC, 1, true))
-        if (split == 1 && lnt) return launch_dag<PREC, RECON, true, 1>(dag, red, L, grid, block, s);
+        return lnt ? launch_dag<PREC, RECON, true, 2, false>(dag, red, L, grid, block, s)
+                   : launch_dag<PREC, RECON, false, 2, false>(dag, red, L, grid, block, s);
+    if constexpr (hop_built(PREC, 1, true, false))
+        if (split == 1 && lnt && !next) return launch_dag<PREC, RECON, true, 1, false>(dag, red, L, grid, block, s);
     return hipErrorInvalidValue;
 }
 

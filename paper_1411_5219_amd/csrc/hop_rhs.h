@@ -167,7 +167,7 @@ __device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nw = (int)blockDim.x >> 6;
     uint32_t tile, b;
-    if (!tile_block(a, bx, &tile, &b)) return;
+    if (!tile_after_tile(a.ch, a.swizzle, bx, &tile, &b)) return;
     const int rhs0 = (int)tile * a.ch.tile, nr = min(a.ch.tile, a.nrhs - rhs0);
     // right-hand sides of the tile that run
     const bool on = lane < nr && !pred_skip(a.pred, a.ctl ? a.ctl + rhs0 + min(lane, nr - 1) : nullptr);

@@ -709,16 +709,4 @@ __device__ void block_reduce_store(double (&v)[N], double* partials, int bid)
     }
 }
 
-// Block index remap that hands each XCD a contiguous range of logical
-// blocks.  Workgroups are dispatched round-robin over the 8 XCDs, so
-// hardware block b runs on XCD b % 8; giving that XCD logical blocks
-// [start(b%8), start(b%8) + count) keeps neighbouring sites in one L2.
-__device__ __forceinline__ int xcd_swizzle(int b, int nb)
-{
-    const int q = nb >> 3, rem = nb & 7;
-    const int xcd = b & 7, k = b >> 3;
-    const int start = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
-    return start + k;
-}
-
 }  // namespace lqcd

@@ -107,15 +107,15 @@ struct Launch {
     int block = 128;
     int swizzle = 1;
     int order = 0;     // 0: memory order, 1: t-fastest chunks of xy planes, k > 1: z-slabs of k planes (hops)
-    int rhs_tile = 4;  // rhs_tile, rhs_group, rhs_lanes: part of the C ABI's struct; launches on several
-    int rhs_group = 4; // right-hand sides put four of them in a block whatever these say
+    int rhs_tile = 4;  // rhs_tile, rhs_group, rhs_lanes: part of the C ABI's struct, without effect
+    int rhs_group = 4; // (hop_form chooses how right-hand sides share links)
     int ygroup = 1;    // blocks of a plane interleaved after t, in units of the block request (1: none)
     int rhs_lanes = 1;
     int form = FORM_BY_SIZE;  // HopForm of Wilson hops (given where several launches must run the same kernel)
 };
 
-// hop_form of the n lattices g (by size).
-int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs);
+// hop_form of the n lattices g.
+int hop_form(int prec, int recon, bool full, const Geom* g, int n, int nrhs, bool rare = false);
 
 // Finalize of one reduction of one system.
 struct FinArgs {
@@ -198,6 +198,7 @@ struct DslashPlan {
     int halves; // split = 0: waves per right-hand side
     bool dag;
     bool lnt;   // streaming link loads (no other block of the launch reads the links)
+    bool next;  // right-hand sides next to each other in the block order
     int nfin;   // values per finalize (0: no reduction)
     int slots;  // partial slots per right-hand side
 };

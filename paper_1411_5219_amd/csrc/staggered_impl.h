@@ -69,7 +69,7 @@ __device__ __forceinline__ void stag_block(const DslashArgs& a, int bx)
     using R = typename ColourIO<PREC>::R;
     constexpr int N = StagRedN<RED>::N;
     uint32_t rhs, b;
-    if (!tile_block(a, bx, &rhs, &b)) return;
+    if (!tile_after_tile(a.ch, a.swizzle, bx, &rhs, &b)) return;
     if (pred_skip(a.pred, a.ctl ? a.ctl + rhs : nullptr)) return;
     int p = a.parity;
     if (a.full) {  // both parities in one launch, adjacent in the block order: the second finds the links in L2

@@ -25,21 +25,48 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(so)
 
 
-def choose(lib, prec, recon, full, lattices, nrhs):
+def choose(lib, prec, recon, full, lattices, nrhs, rare=0):
     flat = [v for L in lattices for v in L]
-    out = (ctypes.c_int * 5)()
-    form = lib.form_of(prec, recon, full, (ctypes.c_int * len(flat))(*flat), len(lattices), nrhs, out)
-    return form, dict(zip(("split", "halves", "tile", "lnt", "built"), out))
+    out = (ctypes.c_int * 6)()
+    form = lib.form_of(prec, recon, full, (ctypes.c_int * len(flat))(*flat), len(lattices), nrhs, rare, out)
+    return form, dict(zip(("split", "halves", "tile", "lnt", "next", "built"), out))
 
 
 @pytest.mark.parametrize("prec,recon", STORAGES)
 def test_every_choice_is_built(lib, prec, recon):
     batches = [[L] for L in LATTICES] + [list(p) for p in itertools.combinations(LATTICES, 2)] + [[(16, 16, 16, 8)] * 8]
-    for lattices, full, nrhs in itertools.product(batches, (0, 1), range(1, 17)):
-        form, h = choose(lib, prec, recon, full, lattices, nrhs)
-        case = (lattices, full, nrhs, form, h)
+    for lattices, full, nrhs, rare in itertools.product(batches, (0, 1), range(1, 17), (0, 1)):
+        form, h = choose(lib, prec, recon, full, lattices, nrhs, rare)
+        case = (lattices, full, nrhs, rare, form, h)
         assert h["built"], case
         assert h["split"] in (0, 1, 2) and h["halves"] in (1, 2), case
         assert 1 <= h["tile"] <= 4 and h["tile"] * h["halves"] <= 4, case
         assert h["split"] == 0 or h["tile"] == 1, case
         assert h["lnt"] == (nrhs == 1 and not full), case
+
+
+def test_every_block_once(lib):
+    """Blocks of every tile of right-hand sides, in either order of the tiles."""
+    for slots, swizzle, adjacent in itertools.product((1, 2, 7, 8, 9, 64, 100), (0, 1), (0, 1)):
+        for nrhs, tile in itertools.product((1, 2, 3, 4, 5, 7, 8, 13, 16, 37), (1, 2, 3, 4)):
+            ntiles = -(-nrhs // tile)
+            counts = (ctypes.c_int * (ntiles * slots))()
+            case = (slots, swizzle, nrhs, tile, adjacent)
+            assert lib.block_cover(slots, tile, adjacent, nrhs, swizzle, counts) == 0, case
+            assert set(counts) == {1}, case
+
+
+PAIR, TILE, NEXT = 2, 3, 5
+
+
+@pytest.mark.parametrize("L,prec,recon,full,nrhs,rare,form", [
+    # the right-hand sides of a chunk next to each other where tiles, or one right-hand side after the other, were slower
+    ((24, 24, 24, 8), 64, 18, 0, 8, 0, NEXT), ((26, 26, 26, 8), 64, 12, 0, 12, 0, NEXT), ((10, 14, 18, 22), 64, 18, 1, 8, 0, NEXT),
+    ((32, 32, 32, 8), 32, 12, 0, 3, 0, NEXT), ((36, 36, 36, 8), 32, 12, 0, 8, 0, NEXT), ((24, 24, 24, 16), 32, 12, 0, 12, 0, NEXT),
+    # tiles stay where the links of one round fit the LDS, on large lattices of whole planes, and for reliable updates
+    ((20, 20, 20, 8), 64, 18, 0, 3, 0, TILE), ((32, 32, 32, 8), 64, 18, 0, 12, 0, TILE), ((24, 24, 24, 8), 64, 18, 0, 8, 1, TILE),
+    ((32, 32, 32, 8), 32, 12, 0, 12, 0, TILE), ((24, 24, 24, 8), 32, 12, 1, 8, 0, TILE), ((48, 48, 48, 24), 16, 12, 0, 2, 0, TILE),
+    # and pairs one right-hand side after the other where all of them run at once
+    ((8, 8, 8, 4), 64, 18, 0, 16, 0, PAIR), ((16, 16, 16, 8), 32, 12, 0, 4, 0, PAIR)])
+def test_choices(lib, L, prec, recon, full, nrhs, rare, form):
+    assert choose(lib, prec, recon, full, [L], nrhs, rare)[0] == form
