@@ -95,7 +95,8 @@ inline int hop_form(int prec, int recon, bool full, const ChunkGrid* g, int n, i
         in_long += long_layers(g[i]) ? own : 0;
     }
     // links once, each spinor of the hop's parity or parities read and written once
-    const int64_t mb = sites * (8 * recon + nrhs * 2 * 24 * (full ? 2 : 1)) * (prec / 8) / 1000000;
+    const int spinor = 3 * prec + (prec == 16 ? 4 : 0);  // bytes (FP16: with the site's scale)
+    const int64_t mb = sites * (recon * prec + (full ? 4 : 2) * nrhs * spinor) / 1000000;
     const bool layers = 2 * in_layers > chunks;
     bool pair;
     if (prec == 16) pair = nrhs <= 3 && mb <= 512;
