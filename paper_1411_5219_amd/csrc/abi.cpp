@@ -1386,10 +1386,10 @@ constexpr size_t kStepTableBytes = 16 * 1024;  // per recorded step: arguments, 
 constexpr int kMaxSteps = 32;
 // Form of the hops of a batch (outer FP64, inner prm->inner_prec): every system
 // of a step runs the same kernel, so the rule of a single launch is applied to
-// the systems together.  The persistent kernel runs tiles.
+// the systems together.  The persistent kernel runs one wave per chunk.
 BatchForms batch_forms(const std::vector<Geom>& g, const lqcd_op* ops, const lqcd_solve_params* prm)
 {
-    if (prm->persistent) return {FORM_TILE_WAVE, FORM_TILE_WAVE};
+    if (prm->persistent) return {FORM_WAVE, FORM_WAVE};
     int recon = 18;
     for (size_t i = 0; i < g.size(); ++i) recon = std::min(recon, (int)ops[i].recon);
     const int n = (int)g.size();
@@ -1415,7 +1415,8 @@ int persist_routine(const std::vector<std::vector<Step>>& steps, size_t k)
     }
     if (st.kind == STEP_DSLASH) {
         const DslashPlan& d = st.d;
-        if (d.kind != PLAN_WILSON || d.split != 0 || d.halves != 1 || (d.red != RED_NONE && d.red != RED_NORM && d.red != RED_NORM_LOW))
+        if (d.kind != PLAN_WILSON || d.split != 1 || !d.next ||
+            (d.red != RED_NONE && d.red != RED_NORM && d.red != RED_NORM_LOW))
             return PR_NONE;
         const bool norm = d.red != RED_NONE;
         if (d.prec == 32 && d.recon == 12)

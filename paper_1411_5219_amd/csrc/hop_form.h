@@ -20,8 +20,9 @@ constexpr int kMaxTile = 4;
 // a pair of waves per chunk of 64 sites and right-hand side, the right-hand
 // sides one after the other or (FORM_NEXT, pairs) next to each other in the
 // block order, or a tile of right-hand sides per chunk with its links in LDS,
-// and in this one wave per right-hand side, or (FORM_TILE only, by size) two.
-enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3, FORM_TILE_WAVE = 4, FORM_NEXT = 5 };
+// and in this one wave per right-hand side, or (tiles of two) two.  FORM_WAVE on
+// several right-hand sides, next to each other, is the persistent kernel's.
+enum HopForm { FORM_BY_SIZE = 0, FORM_WAVE = 1, FORM_PAIR = 2, FORM_TILE = 3, FORM_NEXT = 5 };
 
 // What hop_form and hop_shape know of a lattice: whether its planes leave
 // lanes of their last chunk idle, so that chunks run over several of them, and
@@ -135,12 +136,12 @@ inline HopShape hop_shape(int prec, int recon, bool full, const ChunkGrid& g, in
 {
     HopShape s = {};
     const int64_t chunks = (g.Vh + kChunk - 1) / kChunk;
-    if (form == FORM_TILE || form == FORM_TILE_WAVE) {
+    if (form == FORM_TILE) {
         // several right-hand sides share a block and the links in its LDS: as
         // few tiles of at most kMaxTile as there can be, of even sizes
         const int ntiles = (nrhs + kMaxTile - 1) / kMaxTile;
         s.tile = (nrhs + ntiles - 1) / ntiles;
-        s.halves = form == FORM_TILE && s.tile <= 2 ? 2 : 1;
+        s.halves = s.tile <= 2 ? 2 : 1;
         const bool crowded = full && recon == 12 && g.L[3] < 10 && (nrhs >= 4 || chunks > kSimds);
         s.idle = prec == 16 ? 20 : prec == 64 ? (chunks * ntiles <= 2 * kSimds ? 40 : 8) : crowded ? 8 : 16;
         s.memory = prec == 64 && nrhs > 1 && long_layers(g);
@@ -150,9 +151,11 @@ inline HopShape hop_shape(int prec, int recon, bool full, const ChunkGrid& g, in
     s.halves = 1;
     s.tile = 1;
     s.lnt = nrhs == 1 && !full;
-    s.next = form == FORM_NEXT;
+    s.next = form == FORM_NEXT || (form == FORM_WAVE && nrhs > 1);
     s.idle = s.next && prec == 32 ? 12 : 20;
     s.memory = nrhs > 1 && long_layers(g) && (prec == 64 || (s.next && prec == 32 && recon == 12 && !full && nrhs >= 4));
+    // the persistent kernel's blocks have four waves: all of them busy
+    if (form == FORM_WAVE && nrhs > 1) s.memory = plan_chunk_order(g, 1, 256, 1, 4, s.idle).nsub < 4;
     return s;
 }
 

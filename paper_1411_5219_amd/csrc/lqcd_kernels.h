@@ -345,7 +345,7 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 // ---- persistent batched solver (persist.hip)
 // Block routines a phase of the persistent kernel runs: the steps of the
 // mixed-precision CGNR iteration with FP32/12 inner and FP64/18 outer hops on
-// several right-hand sides (one wave each).
+// several right-hand sides (one wave per chunk of sites and right-hand side).
 enum PRoutine {
     PR_HOP32_12_D0_NONE = 0,
     PR_HOP32_12_D0_NORM,

@@ -6,7 +6,7 @@
 // per system and their per-system argument tables, see BatchProgram in
 // abi.cpp).  Here each step is a phase: the blocks of the grid stride over
 // the step's blocks of all systems and run the same block routine the
-// standalone kernel would (rhs_block, blas_block, convert_block); a step
+// standalone kernel would (dslash_block, blas_block, convert_block); a step
 // with a reduction is followed by its finalize as a phase of its own (one
 // block per system and right-hand side sums the partials in block order and
 // runs the solver's scalar step).  A step that would do nothing for every
@@ -29,28 +29,43 @@
 // The grid never exceeds the blocks the device keeps resident at once (the
 // launch is cooperative, so the runtime refuses a larger one), which the
 // barrier needs, nor the largest phase (more blocks would only wait).
-#include "hop_rhs.h"
+#include "dslash_impl.h"
 #include "site_ops.h"
 
 namespace lqcd {
 
 namespace {
 
+// One system's arguments of a step.  In LDS: the compiler reads arguments
+// where they are used, and from memory every hop that crosses the boundary
+// waited for its phase (four right-hand sides: 8^3x4 6.06 -> 5.33 ms, 32^3x8
+// 10.8 -> 9.5).
+union PersistArgs {
+    DslashArgs d;
+    BlasArgs b;
+    ConvertArgs c;
+    uint32_t w[(sizeof(DslashArgs) > sizeof(BlasArgs) ? sizeof(DslashArgs) : sizeof(BlasArgs)) / 4];
+};
+static_assert(sizeof(ConvertArgs) <= sizeof(PersistArgs::w) && sizeof(DslashArgs) % 4 == 0 && sizeof(BlasArgs) % 4 == 0 &&
+              sizeof(ConvertArgs) % 4 == 0, "arguments are copied by words");
+static_assert(PR_HOP64_18_D0_NORM_LOW < PR_BLAS32_AXMY && PR_BLAS32_CG_XP < PR_CONV64_32_ACC, "routines by argument type");
+
 // Block routines a phase may run (the ones of the mixed FP32/12-inner,
 // FP64/18-outer CGNR iteration on several right-hand sides).
-// links: LDS of the hops' link tiles, shared by the storages.
-union PersistLds {
-    RhsLinks<64, 18> l64;
-    RhsLinks<32, 12> l32;
-};
-
-__device__ __forceinline__ void run_routine(int routine, const void* tab, int s, int bx, int by, PersistLds& lds)
+//
+// Hops: one wave per chunk of sites and right-hand side, without LDS or a
+// barrier of their own.  A block works through its share of a phase alone, two
+// blocks to a compute unit, so what counts is how soon its next loads go out:
+// tiles with the links in LDS load, wait and pass a barrier before the first
+// hop, and leave waves idle where a tile has fewer than four right-hand sides
+// (FP32/12 inner, tiles against waves, two right-hand sides: 16^3x8 + 20^3x8 +
+// 24^3x8 37.2 ms against 31.0, 32^3x8 + 8^3x4 20.3 against 14.5).
+__device__ __forceinline__ void run_routine(int routine, const PersistArgs& args, int bx, int by)
 {
     switch (routine) {
 #define LQCD_PHOP(ID, P, RC, DG, RD)                                                    \
     case ID: {                                                                          \
-        const DslashArgs& a = static_cast<const DslashArgs*>(tab)[s];                   \
-        if (bx < a.gx) rhs_block<P, RC, DG, RD, 1>(a, bx, lds.l##P);                       \
+        if (bx < args.d.gx) dslash_block<P, RC, DG, RD, false, 1, true>(args.d, bx);    \
         break;                                                                          \
     }
         LQCD_PHOP(PR_HOP32_12_D0_NONE, 32, 12, false, RED_NONE)
@@ -62,36 +77,40 @@ __device__ __forceinline__ void run_routine(int routine, const void* tab, int s,
         LQCD_PHOP(PR_HOP64_18_D0_NONE, 64, 18, false, RED_NONE)
         LQCD_PHOP(PR_HOP64_18_D0_NORM_LOW, 64, 18, false, RED_NORM_LOW)
 #undef LQCD_PHOP
-    case PR_BLAS32_AXMY: {
-        const BlasArgs& a = static_cast<const BlasArgs*>(tab)[s];
-        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_AXMY_NORM>(a, bx, a.gx, by);
+    case PR_BLAS32_AXMY:
+        if (bx < args.b.gx) blas_block<32, KIND_SPINOR, BLAS_AXMY_NORM>(args.b, bx, args.b.gx, by);
         break;
-    }
-    case PR_BLAS32_CG_XP: {
-        const BlasArgs& a = static_cast<const BlasArgs*>(tab)[s];
-        if (bx < a.gx) blas_block<32, KIND_SPINOR, BLAS_CG_XP>(a, bx, a.gx, by);
+    case PR_BLAS32_CG_XP:
+        if (bx < args.b.gx) blas_block<32, KIND_SPINOR, BLAS_CG_XP>(args.b, bx, args.b.gx, by);
         break;
-    }
-    case PR_CONV64_32_ACC: {
-        const ConvertArgs& a = static_cast<const ConvertArgs*>(tab)[s];
-        if (bx < a.gx) convert_block<64, 32, 2>(a, bx, a.gx, by);
+    case PR_CONV64_32_ACC:
+        if (bx < args.c.gx) convert_block<64, 32, 2>(args.c, bx, args.c.gx, by);
         break;
-    }
     default:
         break;
     }
 }
 
 // The blocks of one step: virtual block v = x + total * y over all systems.
-__device__ void run_step(const PStep& st, int nsys, PersistLds& lds)
+__device__ void run_step(const PStep& st, int nsys, PersistArgs& args)
 {
     const int total = st.total * st.gy;
+    const int size = st.routine < PR_BLAS32_AXMY     ? (int)sizeof(DslashArgs)
+                     : st.routine < PR_CONV64_32_ACC ? (int)sizeof(BlasArgs)
+                                                     : (int)sizeof(ConvertArgs);
+    int have = -1;  // system whose arguments are in LDS
     for (int v = blockIdx.x; v < total; v += gridDim.x) {
         const int x = v % st.total, y = v / st.total;
         int s = 0;
         while (s + 1 < nsys && x >= st.offs[s + 1]) ++s;
-        run_routine(st.routine, st.tab, s, x - st.offs[s], y, lds);
-        __syncthreads();  // the block reductions' LDS is reused by the next virtual block
+        if (s != have) {
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(static_cast<const char*>(st.tab) + (int64_t)s * size);
+            for (int i = threadIdx.x; i < size / 4; i += kPersistThreads) args.w[i] = src[i];
+            __syncthreads();
+            have = s;
+        }
+        run_routine(st.routine, args, x - st.offs[s], y);
+        __syncthreads();  // the block reductions' LDS and the arguments are reused by the next virtual block
     }
 }
 
@@ -190,7 +209,7 @@ __device__ bool all_done(const PProgram& P)
 __global__ void __launch_bounds__(kPersistThreads) __attribute__((amdgpu_waves_per_eu(2)))
 k_batch_persistent(const PProgram* __restrict__ prog)
 {
-    __shared__ PersistLds lds;
+    __shared__ PersistArgs args;
     const PProgram& P = *prog;
     unsigned epoch = 0;
     for (int it = 0; it < P.max_iter; ++it) {
@@ -204,7 +223,7 @@ k_batch_persistent(const PProgram* __restrict__ prog)
                 if (!no_update) no_update = !any_active(P, PRED_UPDATE);
                 if (no_update) continue;
             }
-            run_step(st, P.nsys, lds);
+            run_step(st, P.nsys, args);
             if (!grid_sync(P, ++epoch)) return;
             if (st.nfin) {
                 run_finalize(st, P.nsys, P.nrhs);

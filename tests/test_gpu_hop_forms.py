@@ -160,3 +160,34 @@ def test_reductions_of_several_rhs(mods, L4, inner, nrhs):
     for k in range(nrhs):
         tr = W.true_residual(U, got[k], b[k], L4, THETA, kappa, mu)
         assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol, k
+
+
+@pytest.mark.parametrize("nrhs", [2, 3, 5, 16])
+def test_persistent_batch(mods, nrhs):
+    """The persistent kernel's hops, one wave per chunk: planes of whole blocks,
+    a ragged last chunk and chunks over several planes, right-hand sides that
+    the kernel's blocks share unevenly."""
+    torch, fields, lqcd = mods
+    mu, tol = 0.03, 1e-10
+    systems = [((32, 16, 4, 4), 0.12), ((20, 18, 4, 4), 0.13), ((6, 10, 4, 12), 0.11)]
+    print(f"\n[case] persistent batch nrhs={nrhs}", flush=True)
+    geoms, ops, Us, bs, xs, host = [], [], [], [], [], []
+    for i, (L4, kappa) in enumerate(systems):
+        U, b = gauge_field(L4, "exp", eps=0.4, seed=67 + i), gaussian_spinor(L4, seed=77 + i, nrhs=nrhs)
+        lat = fields.Lattice(L4, THETA)
+        host.append((L4, kappa, U, b, lat))
+        geoms.append(lat.g)
+        ops.append(lqcd.op(kappa, mu))
+        Us.append(lat.gauge(U))
+        bs.append(lat.spinor(b))
+        xs.append(lat.zeros(lqcd.FIELD_SPINOR_FULL, 64, nrhs=nrhs))
+    p = lqcd.solve_params(tol=tol, maxiter=1000, eo=1, nrhs=nrhs, inner_prec=32, inner_recon=12, delta_reliable=0.05,
+                          persistent=1)
+    ws = torch.empty(lqcd.lqcd_workspace_bytes_batch(geoms, ops, p), dtype=torch.uint8, device="cuda")
+    rc, infos = lqcd.cg_solve_batch(geoms, ops, Us, bs, xs, p, ws)
+    assert rc == 0 and infos[0][0]["persistent_launches"] >= 1, infos
+    for (L4, kappa, U, b, lat), x, info in zip(host, xs, infos):
+        got = lat.unpack(x, 64, nrhs=nrhs).reshape(nrhs, lat.V, 4, 3)
+        for k in range(nrhs):
+            tr = W.true_residual(U, got[k], b[k], L4, THETA, kappa, mu)
+            assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol, (L4, k)
