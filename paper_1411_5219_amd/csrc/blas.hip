@@ -102,6 +102,17 @@ static hipError_t blas_prec(int prec, int kind, int op, const BlasLaunch& L, dim
     return hipErrorInvalidValue;
 }
 
+// Shares of the shifts of a multi-shift update: a thread passes over the shifts
+// one after the other, each a load and a store later, and few blocks do not hide
+// this; so as many shares as give the card's SIMDs a wave each (a solve with 32
+// shifts: 8^3x4 5.13 -> 3.16 ms, 12^3x8 8.09 -> 6.06, 16^3x8 8.21 -> 6.83;
+// one share from 24^3x8 on).
+static int shift_shares(int64_t blocks, int blk, int nshift)
+{
+    const int64_t waves = blocks * (blk / 64);
+    return (int)std::max<int64_t>(1, std::min<int64_t>(nshift, kSimds / waves));
+}
+
 hipError_t plan_blas(int prec, int op, const BlasArgs& a, int nrhs, const Launch& cfg, BlasPlan* out)
 {
     if (prec != 64 && prec != 32 && prec != 16) return hipErrorInvalidValue;
@@ -112,7 +123,8 @@ hipError_t plan_blas(int prec, int op, const BlasArgs& a, int nrhs, const Launch
     p.nrhs = nrhs;
     const int blk = cfg.block;
     const unsigned nbs = (unsigned)((a.Vh + blk - 1) / blk);
-    p.grid = dim3(nbs * a.nsub, nrhs);
+    p.a.fam_gy = op == BLAS_MS_XP ? shift_shares(nbs * a.nsub, blk, a.fam_n) : 1;
+    p.grid = dim3(nbs * a.nsub, op == BLAS_MS_XP ? p.a.fam_gy : nrhs);
     p.a.gx = (int)p.grid.x;
     p.block = dim3(blk);
     p.nfin = (op == BLAS_NORM || op == BLAS_AXMY_NORM)                                           ? 1

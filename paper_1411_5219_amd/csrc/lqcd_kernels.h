@@ -258,6 +258,7 @@ struct BlasArgs {
     RedArgs r;
     Ctl* ctl;
     int fam_n, fam_base;    // multi-shift: systems and index of the base system
+    int fam_gy;             // BLAS_MS_XP: shares of the shifts, one along grid.y each (plan_blas)
     CtlFold fold;           // BLAS_AXMY_NORM, BLAS_CG_XP, BLAS_MS_XP
     int gx;                 // planned grid.x (batched launches)
 };

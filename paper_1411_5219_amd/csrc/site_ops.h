@@ -142,7 +142,8 @@ __device__ __forceinline__ void blas_block(const BlasArgs& a, int bx, int nbx, i
     constexpr int NC = F::NC;
     constexpr int N = BlasRed<OP>::N;
     constexpr int NN = N > 0 ? N : 1;
-    const int rhs = by;
+    // BLAS_MS_XP (one right-hand side): by is a share of the shifts
+    const int rhs = OP == BLAS_MS_XP ? 0 : by;
     // each sub-field covers nbs whole blocks, so the sub-field is uniform per block
     const int nbs = nbx / a.nsub;
     const int sub = bx / nbs;
@@ -161,7 +162,8 @@ __device__ __forceinline__ void blas_block(const BlasArgs& a, int bx, int nbx, i
             // multi-shift: the whole family steps with its base system
             const int n = MS ? a.fam_n : 1, cur = MS ? a.fam_base : 0;
             const Ctl* c0 = OP == BLAS_AXMY_NORM ? ctl - cur : ctl;
-            c0 = fold_ctl<BlasFold<KIND, OP>::N, FIN>(a.fold, c0, a.fold.out + rhs, n, cur, rhs, bx == 0, lds);
+            c0 = fold_ctl<BlasFold<KIND, OP>::N, FIN>(a.fold, c0, a.fold.out + rhs, n, cur, rhs,
+                                                       bx == 0 && (OP != BLAS_MS_XP || by == 0), lds);
             ctl = OP == BLAS_AXMY_NORM ? c0 + cur : c0;
             if (OP == BLAS_AXMY_NORM && ctl->done) return;
         } else if (OP == BLAS_AXMY_NORM && pred_skip(a.pred, ctl)) {
@@ -282,11 +284,11 @@ __device__ __forceinline__ void blas_block(const BlasArgs& a, int bx, int nbx, i
             F::store(P(a.z, a.st_z), S, h, r);
         } else if (OP == BLAS_MS_XP) {
             // every shift's x_i += alpha_i p_i ; p_i = zeta_i z + beta_i p_i,
-            // z and each p_i read once for both
+            // z and each p_i read once for both; shifts by, by + fam_gy, ...
             Vec z;
             F::load(P(a.z, a.st_z), S, h, z);
-            char *xi = static_cast<char*>(a.x) + soff, *pi = static_cast<char*>(a.y) + soff;
-            for (int i = 0; i < a.fam_n; ++i, xi += a.st_x, pi += a.st_y) {
+            char *xi = static_cast<char*>(a.x) + soff + by * a.st_x, *pi = static_cast<char*>(a.y) + soff + by * a.st_y;
+            for (int i = by; i < a.fam_n; i += a.fam_gy, xi += a.fam_gy * a.st_x, pi += a.fam_gy * a.st_y) {
                 const Ctl& c = ctl[i];
                 const bool dox = c.xdo != 0, dop = c.done == 0;
                 if (!dox && !dop) continue;

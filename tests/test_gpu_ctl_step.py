@@ -74,6 +74,12 @@ def test_multishift(mods, L4, n):
         assert res <= tol and abs(res - info[i]["true_resid"]) <= 1e-3 * tol + 1e-15, (i, res, info[i])
 
 
+@pytest.mark.parametrize("L4,n", [((16, 16, 16, 8), 7), ((18, 14, 10, 12), 6), ((6, 4, 4, 10), 32)])
+def test_multishift_shares(mods, L4, n):
+    """The multi-shift update in shares of the shifts: uneven ones, and one each."""
+    test_multishift(mods, L4, n)
+
+
 # one system much wider than the others (their blocks lie in a row), equal ones (one grid plane each), and a 2^4
 # system, for which the whole batch keeps launches for its scalar steps
 @pytest.mark.parametrize("lattices", [[(4, 4, 4, 4), (16, 16, 16, 4), (4, 6, 4, 2)], [(6, 6, 4, 4), (4, 6, 6, 4)],
