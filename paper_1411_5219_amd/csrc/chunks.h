@@ -147,6 +147,16 @@ inline unsigned plan_tiles(ChunkArgs* c, int slots, int tile, bool adjacent, int
     return stride * ntiles;
 }
 
+// Right-hand sides of one launch whose blocks, `slots` to a tile of them, have
+// `threads` work-items: as even parts as keep the work-items along x below 2^32,
+// HIP's limit (plan_tiles adds at most 7 blocks to a tile).
+inline int rhs_per_launch(int slots, int tile, int threads, int nrhs)
+{
+    const int64_t most = (int64_t)0xffffffff / threads / ((int64_t)slots + 7) * tile;
+    const int64_t parts = (nrhs + most - 1) / most;
+    return (int)((nrhs + parts - 1) / parts);
+}
+
 // Block index remap that hands each XCD a contiguous range of logical
 // blocks.  Workgroups are dispatched round-robin over the 8 XCDs, so
 // hardware block b runs on XCD b % 8; giving that XCD logical blocks

@@ -146,12 +146,34 @@ hipError_t exec_dslash_batch(const DslashPlan* plans, int n, const DslashArgs* t
     return launch_finalize_batch(p0.nfin, fin_tab, n, p0.a.nrhs, s);
 }
 
+// Very many right-hand sides (an application of the matrix, no reduction and no
+// control blocks): several launches, each on at most n of them.
+template <class F>
+static hipError_t launch_parts(int red, DslashArgs a, int nrhs, int n, F launch)
+{
+    if (red != RED_NONE || a.ctl) return hipErrorInvalidValue;
+    for (int k = 0; k < nrhs; k += n) {
+        const hipError_t e = launch(a, nrhs - k < n ? nrhs - k : n);
+        if (e != hipSuccess) return e;
+        a.in = static_cast<const char*>(a.in) + n * a.st_in;
+        a.out = static_cast<char*>(a.out) + n * a.st_out;
+        if (a.site) a.site = static_cast<const char*>(a.site) + n * a.st_site;
+        if (a.add) a.add = static_cast<const char*>(a.add) + n * a.st_add;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_dslash(int prec, int recon, bool dagger, int red, const DslashArgs& args, int nrhs,
                          const Launch& cfg, hipStream_t s)
 {
     DslashPlan p;
     hipError_t e = plan_dslash(prec, recon, dagger, red, args, nrhs, cfg, &p);
     if (e != hipSuccess) return e;
+    const int n = rhs_per_launch(p.slots, p.a.ch.tile, (int)p.block.x, nrhs);
+    if (n < nrhs)
+        return launch_parts(red, args, nrhs, n, [&](const DslashArgs& a, int m) {
+            return launch_dslash(prec, recon, dagger, red, a, m, cfg, s);
+        });
     if (Recorder* r = active_recorder()) {
         r->steps.push_back(Step{});
         r->steps.back().kind = STEP_DSLASH;
@@ -186,8 +208,13 @@ hipError_t launch_stag(int prec, int recon, int red, const DslashArgs& args, int
                        hipStream_t s)
 {
     DslashPlan p;
-    const hipError_t e = plan_stag_hop(prec, recon, red, args, nrhs, cfg, &p);
+    hipError_t e = plan_stag_hop(prec, recon, red, args, nrhs, cfg, &p);
     if (e != hipSuccess) return e;
+    const int n = rhs_per_launch(p.slots, 1, (int)p.block.x, nrhs);
+    if (n < nrhs)
+        return launch_parts(red, args, nrhs, n, [&](const DslashArgs& a, int m) {
+            return launch_stag(prec, recon, red, a, m, cfg, s);
+        });
     if (Recorder* r = active_recorder()) {
         r->steps.push_back(Step{});
         r->steps.back().kind = STEP_DSLASH;

@@ -41,4 +41,18 @@ int block_cover(int slots, int tile, int adjacent, int nrhs, int swizzle, int* c
     }
     return 0;
 }
+
+// rhs_per_launch, and the work-items along x of a launch of that many.
+int parts_of(int slots, int tile, int threads, int nrhs, long long* items)
+{
+    ChunkArgs c = {};
+    const int n = rhs_per_launch(slots, tile, threads, nrhs);
+    long long worst = 0;
+    for (int adjacent = 0; adjacent < 2; ++adjacent) {
+        const long long v = (long long)plan_tiles(&c, slots, tile, adjacent != 0, n) * threads;
+        worst = v > worst ? v : worst;
+    }
+    *items = worst;
+    return n;
+}
 }

@@ -237,3 +237,30 @@ def test_launch_shapes_bitwise_and_autotune(mods):
     finally:
         lqcd.lqcd_set_launch(lqcd.KERNEL_STAG, 64, **saved)
         lqcd.lqcd_tune_cache_clear()
+
+
+def test_very_many_rhs(mods):
+    """More right-hand sides than one launch's 2^32 work-items: the same bytes as one at a time."""
+    torch, fields, lqcd = mods
+    L4, nrhs = (24, 24, 16, 8), 60000
+    lat = fields.Lattice(L4, (0.0, 0.0, 0.0, math.pi))
+    size = lat.nbytes(lqcd.FIELD_COLOUR_FULL, 16)
+    assert lat.V * nrhs > 2**32
+    if torch.cuda.mem_get_info()[0] < 2.2 * size * nrhs:
+        pytest.skip("needs two fields of 71 GB")
+    print(f"\n[case] stag full M L={L4} prec=16 nrhs={nrhs}", flush=True)
+    U, _ = _setup(L4)
+    Ud, op = lat.gauge(U, 16, 12), lqcd.stag_op(0.13, 16, 12)
+    inp = torch.zeros((nrhs, size), dtype=torch.uint8, device="cuda")
+    out = torch.empty_like(inp)
+    some = [0, 1, nrhs // 2 - 1, nrhs // 2, nrhs // 2 + 1, nrhs - 1]
+    for k in some:
+        inp[k] = lat.colour(PS.colour_field(L4, 2100 + k), 16)
+    lqcd.stag_apply(lat.g, op, Ud, inp, out, 0, nrhs)
+    for k in some:
+        one = torch.empty_like(inp[k])
+        lqcd.stag_apply(lat.g, op, Ud, inp[k], one, 0, 1)
+        got, ref = (lat.unpack_colour(f, 16) for f in (out[k], one))
+        assert np.abs(ref).max() > 0 and np.array_equal(got, ref), k
+    del inp, out
+    torch.cuda.empty_cache()

@@ -56,6 +56,23 @@ def test_every_block_once(lib):
             assert set(counts) == {1}, case
 
 
+def test_launches_of_many_rhs(lib):
+    """Up to 65535 right-hand sides: launches of fewer than 2^32 work-items, as few
+    and as even as can be."""
+    items = ctypes.c_longlong()
+    for slots, tile, threads, nrhs in itertools.product((1, 288, 1152, 86016, 688128), (1, 2, 3, 4), (64, 128, 256),
+                                                        (1, 16, 17, 4096, 60000, 65535)):
+        n = lib.parts_of(slots, tile, threads, nrhs, ctypes.byref(items))
+        case = (slots, tile, threads, nrhs, n)
+        assert 1 <= n <= nrhs and items.value < 2**32, case
+        parts = -(-nrhs // n)
+        assert n - (nrhs - (parts - 1) * n) < parts, case
+        if (slots + 7) * -(-nrhs // tile) * threads < 2**32:
+            assert n == nrhs, case
+        else:
+            assert parts == 1 or (slots + 7) * (-(-nrhs // (parts - 1)) // tile) * threads >= 2**32 - (slots + 7) * threads, case
+
+
 PAIR, TILE, NEXT = 2, 3, 5
 
 
