@@ -600,11 +600,11 @@ int plan_solver(const Geom& g, const lqcd_op* op, const lqcd_solve_params* prm, 
     const bool eo = prm->eo != 0;
     const int64_t vec = (eo ? 1 : 2) * pb * nrhs;
     const bool mixed = prm->inner_prec != 64;
-    // FP64 vectors: CG eo: r p w z t bhat | BiCG eo: r r0 p v s t tmp bhat
+    // FP64 vectors: CG eo: r p w z t bhat, mixed: t64 bhat | BiCG eo: r r0 p v s t tmp bhat
     //               CG full: r p w z     | BiCG full: r r0 p v s t
     //               BiCGStab(2) eo: r_0 r_1 r_2 u_0 u_1 u_2 rt tmp bhat (full: the first 7)
     int nv = 0;
-    if (method == M_CG) nv = mixed ? 3 : (eo ? 6 : 4);
+    if (method == M_CG) nv = mixed ? 2 : (eo ? 6 : 4);
     else if (prm->bicgstab_ell == 2) nv = eo ? 9 : 7;
     else nv = eo ? 8 : 6;
     for (int i = 0; i < nv; ++i) sp->v[i] = ar.take((size_t)vec);
@@ -959,8 +959,8 @@ struct CgSystem {
             t = eo ? sp.v[4] : nullptr;
             bhat = eo ? sp.v[5] : nullptr;
         } else {
-            t64 = sp.v[1];
-            bhat = sp.v[2];
+            t64 = sp.v[0];
+            bhat = sp.v[1];
             lo = o;
             lo.prec = prm->inner_prec;
             lo.recon = prm->inner_recon;

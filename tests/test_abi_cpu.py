@@ -416,3 +416,16 @@ def test_tune_cache_read_from_environment(tmp_path):
         r = subprocess.run([sys.executable, "-c", code], env=env, capture_output=True, text=True, timeout=120)
         assert r.returncode == 0, r.stderr
         assert r.stdout.strip().startswith(want), r.stdout
+
+
+@pytest.mark.parametrize("prec,recon,held", [(32, 12, 32), (32, 18, 32), (16, 12, 32)])
+@pytest.mark.parametrize("nrhs", [1, 3, 16])
+def test_mixed_workspace(prec, recon, held, nrhs):
+    """A mixed CG holds two FP64 vectors, six at its inner storage (one it may
+    fall back to) and links; an FP64 workspace holds eight (BiCGStab)."""
+    from paper_1411_5219_amd import lqcd as L
+    g, o = L.geom((8, 8, 8, 8)), L.op(0.16, 0.005)
+    vec = {p: L.lqcd_field_bytes(g, L.FIELD_SPINOR_PARITY, p, 18) * nrhs for p in (64, 32)}
+    extra = 2 * vec[64] + 6 * vec[held] + L.lqcd_field_bytes(g, L.FIELD_GAUGE, held, recon) - 8 * vec[64]
+    mixed = L.lqcd_workspace_bytes(g, o, L.solve_params(nrhs=nrhs, inner_prec=prec, inner_recon=recon))
+    assert abs(mixed - L.lqcd_workspace_bytes(g, o, L.solve_params(nrhs=nrhs)) - extra) <= 256 * 10  # each aligned
