@@ -1481,7 +1481,7 @@ bool same_kernel(const Step& a, const Step& b)
     if (a.kind == STEP_DSLASH)
         return a.d.kind == b.d.kind && a.d.prec == b.d.prec && a.d.recon == b.d.recon && a.d.split == b.d.split &&
                a.d.halves == b.d.halves && a.d.lnt == b.d.lnt && a.d.next == b.d.next && a.d.red == b.d.red &&
-               a.d.dag == b.d.dag && a.d.a.nrhs == b.d.a.nrhs && a.d.grid.y == b.d.grid.y;
+               a.d.dag == b.d.dag && a.d.a.nrhs == b.d.a.nrhs;
     if (a.kind == STEP_BLAS)
         return a.b.prec == b.b.prec && a.b.op == b.b.op && a.b.nrhs == b.b.nrhs && a.b.block.x == b.b.block.x;
     return a.c.pd == b.c.pd && a.c.ps == b.c.ps && a.c.a.accumulate == b.c.a.accumulate && a.c.grid.y == b.c.grid.y;
@@ -1570,7 +1570,7 @@ struct BatchProgram {
             int nfin = 0;
             for (int i = 0; i < nsys; ++i) {
                 const Step& q = steps[i][k];
-                const unsigned y = q.kind == STEP_DSLASH ? q.d.grid.y : q.kind == STEP_BLAS ? q.b.grid.y : q.c.grid.y;
+                const unsigned y = q.kind == STEP_DSLASH ? 1u : q.kind == STEP_BLAS ? q.b.grid.y : q.c.grid.y;
                 gy = y > gy ? y : gy;
             }
             if (st.kind == STEP_DSLASH) nfin = st.d.nfin;

@@ -131,15 +131,14 @@ hipError_t exec_dslash_batch(const DslashPlan* plans, int n, const DslashArgs* t
 {
     if (n < 1) return hipErrorInvalidValue;
     const DslashPlan& p0 = plans[0];
-    unsigned gy = p0.grid.y, bx = p0.block.x, gx = p0.grid.x;
+    unsigned bx = p0.block.x, gx = p0.grid.x;
     for (int i = 1; i < n; ++i) {
         gx = plans[i].grid.x > gx ? plans[i].grid.x : gx;
-        gy = plans[i].grid.y > gy ? plans[i].grid.y : gy;
         bx = plans[i].block.x > bx ? plans[i].block.x : bx;
     }
     DslashPlan q = p0;
     q.block = dim3(bx);
-    const BatchGrid bg = batch_grid(n, gx, gy, (unsigned)total_blocks, offs);
+    const BatchGrid bg = batch_grid(n, gx, 1, (unsigned)total_blocks, offs);
     DslashLaunch L{nullptr, tab, bg.offs, n};
     const hipError_t e = launch_dslash_prec(q, L, bg.grid, s);
     if (e != hipSuccess || p0.nfin == 0) return e;

@@ -301,6 +301,7 @@ struct HopTune {
 template <int PREC, int RECON, bool DAG, bool LNT, int D, int K0, int K1>
 struct HopPipe {
     using R = typename SpinorIO<PREC>::R;
+    static_assert(D == 1 || D == 2, "loads of run()");
     const char* in;
     const DslashArgs& a;
     const SiteGeo& g;
@@ -343,8 +344,6 @@ struct HopPipe {
         if constexpr (D > 1) {
             load<K0>();
             load<K0 + 1>();
-            if constexpr (D > 2) load<K0 + 2>();
-            if constexpr (D > 3) load<K0 + 3>();
         }
         step<K0>();
         step<K0 + 1>();
@@ -575,11 +574,12 @@ template <int PREC, int RECON>
 inline hipError_t launch_hop(int split, bool lnt, bool next, bool dag, int red, const DslashLaunch& L, dim3 grid,
                              dim3 block, hipStream_t s)
 {
-    if (split == 2 && next) return lnt ? hipErrorInvalidValue : launch_dag<PREC, RECON, false, 2, true>(dag, red, L, grid, block, s);
-    if (split == 2)
+    if constexpr (hop_built(PREC, RECON, 2, false, true))
+        if (split == 2 && next && !lnt) return launch_dag<PREC, RECON, false, 2, true>(dag, red, L, grid, block, s);
+    if (split == 2 && !next)
         return lnt ? launch_dag<PREC, RECON, true, 2, false>(dag, red, L, grid, block, s)
                    : launch_dag<PREC, RECON, false, 2, false>(dag, red, L, grid, block, s);
-    if constexpr (hop_built(PREC, 1, true, false))
+    if constexpr (hop_built(PREC, RECON, 1, true, false))
         if (split == 1 && lnt && !next) return launch_dag<PREC, RECON, true, 1, false>(dag, red, L, grid, block, s);
     return hipErrorInvalidValue;
 }

@@ -159,11 +159,14 @@ inline HopShape hop_shape(int prec, int recon, bool full, const ChunkGrid& g, in
     return s;
 }
 
-// Whether the launch's kernel is built.  One wave per chunk is built only
-// where it can be the faster split: FP64 on one parity and right-hand side.
-constexpr bool hop_built(int prec, int split, bool lnt, bool next)
+// Whether the launch's kernel is built: what hop_form chooses.  One wave per
+// chunk can be the faster split with FP64/18 on one parity and right-hand side,
+// pairs next to each other with every storage but FP32/18.
+constexpr bool hop_built(int prec, int recon, int split, bool lnt, bool next)
 {
-    return split == 1 ? prec == 64 && lnt && !next : split == 2 ? !(lnt && next) : !lnt && !next;
+    return split == 1   ? prec == 64 && recon == 18 && lnt && !next
+           : split == 2 ? !next || (!lnt && !(prec == 32 && recon == 18))
+                        : !lnt && !next;
 }
 
 }  // namespace lqcd

@@ -23,8 +23,6 @@
 
 namespace lqcd {
 
-constexpr int kRhsTile = 4;  // most right-hand sides per block
-
 // The links of a block's sites, [hop][words of the link][site]: nine entries,
 // or for FP16 storage the halves of rows 0 and 1 and the third row in FP32.
 template <int PREC, int RECON>
@@ -95,6 +93,7 @@ template <int PREC, int RECON, bool DAG, int K0, int K1>
 struct RhsPipe {
     using R = typename SpinorIO<PREC>::R;
     static constexpr int D = RhsTune<PREC>::depth;
+    static_assert(D == 1 || D == 2, "loads of first()");
     const RhsLinks<PREC, RECON>& lds;
     const DslashArgs& a;
     const SiteGeo& g;
@@ -130,7 +129,6 @@ struct RhsPipe {
     {
         load<K0>();
         if constexpr (D > 1) load<K0 + 1>();
-        if constexpr (D > 2) load<K0 + 2>();
     }
     __device__ __forceinline__ void run()
     {
@@ -250,7 +248,7 @@ __device__ __forceinline__ void rhs_block(const DslashArgs& a, int bx, RhsLinks<
 }
 
 template <int PREC, int RECON, bool DAG, int RED, int HALVES>
-__global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
+__global__ void __launch_bounds__(64 * kMaxTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
 k_hop_rhs(const DslashArgs a)
 {
     __shared__ RhsLinks<PREC, RECON> lds;
@@ -265,7 +263,7 @@ k_hop_rhs(const DslashArgs a)
 // launch costs no more (24^3x6, FP16 inner, four: 6.32 ms against 6.45 strided).
 constexpr int kLoopBlocks = 512;  // two per compute unit (a multiple of the XCDs)
 template <int RECON, int RED>
-__global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<64>::waves)))
+__global__ void __launch_bounds__(64 * kMaxTile) __attribute__((amdgpu_waves_per_eu(RhsTune<64>::waves)))
 k_hop_rhs_update(const DslashArgs a)
 {
     __shared__ RhsLinks<64, RECON> lds;
@@ -279,7 +277,7 @@ k_hop_rhs_update(const DslashArgs a)
 }
 
 template <int PREC, int RECON, bool DAG, int RED, int HALVES>
-__global__ void __launch_bounds__(64 * kRhsTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
+__global__ void __launch_bounds__(64 * kMaxTile) __attribute__((amdgpu_waves_per_eu(RhsTune<PREC>::waves)))
 k_hop_rhs_batch(const DslashArgs* __restrict__ tab, const int* __restrict__ offs, int nsys)
 {
     __shared__ RhsLinks<PREC, RECON> lds;

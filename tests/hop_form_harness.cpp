@@ -20,7 +20,7 @@ int form_of(int prec, int recon, int full, const int* L, int n, int nrhs, int ra
     out[2] = h.tile;
     out[3] = h.lnt;
     out[4] = h.next;
-    out[5] = hop_built(prec, h.split, h.lnt, h.next);
+    out[5] = hop_built(prec, recon, h.split, h.lnt, h.next);
     return form;
 }
 

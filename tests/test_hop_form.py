@@ -45,6 +45,18 @@ def test_every_choice_is_built(lib, prec, recon):
         assert h["lnt"] == (nrhs == 1 and not full), case
 
 
+def test_every_kernel_is_chosen(lib):
+    """Kernels that are built are run: one wave per chunk, a pair and a pair with
+    right-hand sides next to each other, tiles with one wave and with two."""
+    seen = set()
+    for (prec, recon), L, full, nrhs in itertools.product(STORAGES, LATTICES + [(48, 48, 48, 24)], (0, 1), range(1, 17)):
+        _, h = choose(lib, prec, recon, full, [L], nrhs)
+        seen.add((prec, recon, h["split"], h["halves"], h["lnt"], h["next"]))
+    every = {(p, r, 2, 1, *k) for p, r in STORAGES for k in ((0, 0), (1, 0), (0, 1))} - {(32, 18, 2, 1, 0, 1)}
+    every |= {(p, r, 0, h, 0, 0) for p, r in STORAGES for h in (1, 2)} | {(64, 18, 1, 1, 1, 0)}
+    assert seen == every, seen ^ every
+
+
 def test_every_block_once(lib):
     """Blocks of every tile of right-hand sides, in either order of the tiles."""
     for slots, swizzle, adjacent in itertools.product((1, 2, 7, 8, 9, 64, 100), (0, 1), (0, 1)):
