@@ -164,7 +164,10 @@ def _stream(stream):
         # torch.cuda.current_stream() makes around it: 0.3 us instead of 2.8, in
         # calls that otherwise take 6 (16^3x8 FP64 hops back to back 8.8 -> 6.4)
         import torch
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # not of torch's public interface
+        if raw is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(torch.cuda.current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -429,3 +429,13 @@ def test_mixed_workspace(prec, recon, held, nrhs):
     extra = 2 * vec[64] + 6 * vec[held] + L.lqcd_field_bytes(g, L.FIELD_GAUGE, held, recon) - 8 * vec[64]
     mixed = L.lqcd_workspace_bytes(g, o, L.solve_params(nrhs=nrhs, inner_prec=prec, inner_recon=recon))
     assert abs(mixed - L.lqcd_workspace_bytes(g, o, L.solve_params(nrhs=nrhs)) - extra) <= 256 * 10  # each aligned
+
+
+def test_current_stream_without_the_raw_call(monkeypatch):
+    """The current stream comes from torch's public interface where the raw call is missing."""
+    import types
+    import torch
+    from paper_1411_5219_amd import lqcd as L
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+    assert L._stream(None) == 7
