@@ -191,3 +191,26 @@ def test_persistent_batch(mods, nrhs):
         for k in range(nrhs):
             tr = W.true_residual(U, got[k], b[k], L4, THETA, kappa, mu)
             assert tr <= tol and abs(tr - info[k]["true_resid"]) <= 1e-3 * tol, (L4, k)
+
+
+@pytest.mark.parametrize("L4,prec,recon,nrhs", [(A, 64, 18, 5), (A, 32, 12, 3), (A, 16, 12, 5)])
+def test_launch_fields_without_effect(mods, L4, prec, recon, nrhs):
+    """rhs_tile, rhs_group and rhs_lanes change no result, whichever form the hop
+    takes; the answer is the same bytes."""
+    torch, fields, lqcd = mods
+    print(f"\n[case] launch fields L={L4} prec={prec} nrhs={nrhs}", flush=True)
+    lat = fields.Lattice(L4, THETA)
+    Ud = lat.gauge(gauge_field(L4, "exp", eps=0.4, seed=69), prec, recon)
+    inp = lat.spinor(gaussian_spinor(L4, seed=79, nrhs=nrhs), prec)
+    op, saved = lqcd.op(0.16, 0.005, prec, recon), lqcd.lqcd_get_launch(lqcd.KERNEL_DSLASH_RHS, prec)
+    outs = []
+    try:
+        for tile, group, lanes in [(4, 4, 1), (1, 0, 1), (2, 2, 4), (4, 16, 16)]:
+            lqcd.lqcd_set_launch(lqcd.KERNEL_DSLASH_RHS, prec,
+                                 **dict(saved, rhs_tile=tile, rhs_group=group, rhs_lanes=lanes))
+            out = lat.zeros(lqcd.FIELD_SPINOR_FULL, prec, nrhs=nrhs)
+            lqcd.dslash_apply(lat.g, op, Ud, inp, out, nrhs=nrhs)
+            outs.append(out)
+    finally:
+        lqcd.lqcd_set_launch(lqcd.KERNEL_DSLASH_RHS, prec, **saved)
+    assert outs[0].any() and all(torch.equal(outs[0], o) for o in outs[1:])
