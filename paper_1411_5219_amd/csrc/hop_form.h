@@ -50,7 +50,9 @@ inline bool long_layers(const ChunkGrid& g) { return layered(g) && g.L[3] >= 10;
 // (hop_rhs.h).  Pairs while all of them run at once (two waves per SIMD in FP64,
 // three below: FP32/12 Schur complement 8^3x4 with four 9.8 us against 13.3,
 // 16^3x8 with four 15.0 against 16.8), one right-hand side after the other, which
-// is 0.1 to 0.2 us shorter.  Beyond that pairs with the right-hand sides of a
+// is 0.1 to 0.2 us shorter; the full matrix of FP64/12 on
+// small lattices up to five waves (12^3x8 n16 33.0 us, next to each other 36.4;
+// 16^3x8 n8 37.8 and 39.9; but 18^3x8 n6 47.5 and 46.7).  Beyond that pairs with the right-hand sides of a
 // chunk next to each other, so that all but one find its links in L2 (FP64/18
 // 24^3x8 n8 104 -> 66.4 us); us of one hop as such pairs and as tiles, n
 // right-hand sides:
@@ -89,7 +91,8 @@ inline int hop_form(int prec, int recon, bool full, const ChunkGrid* g, int n, i
         }
         return wave ? FORM_WAVE : FORM_PAIR;
     }
-    if (2 * chunks * nrhs <= (prec == 64 ? 2 : 3) * kSimds) return FORM_PAIR;
+    const int waves = prec != 64 ? 3 : recon == 12 && full && 4 * chunks <= kSimds ? 5 : 2;  // per SIMD
+    if (2 * chunks * nrhs <= waves * kSimds) return FORM_PAIR;
     for (int i = 0; i < n; ++i) {
         const int64_t own = (g[i].Vh + kChunk - 1) / kChunk;
         in_layers += layered(g[i]) ? own : 0;

@@ -59,7 +59,7 @@ P, T, N = 2, 3, 5       # FORM_PAIR, FORM_TILE, FORM_NEXT
 # three and four, with a last tile that is full and one that is not, and pairs
 # with their right-hand sides next to each other
 FORMS = [(A, 64, 18, 3, T, N), (A, 64, 18, 4, T, N), (A, 64, 18, 5, N, N), (A, 64, 12, 4, T, N), (A, 64, 12, 7, N, N),
-         (B, 64, 18, 5, T, N), (B, 64, 12, 7, T, N),
+         (B, 64, 18, 5, T, N), (B, 64, 12, 7, T, P),
          (A, 32, 18, 5, T, T), (A, 32, 18, 7, T, T), (A, 32, 12, 3, P, P), (A, 32, 12, 5, T, T), (A, 32, 12, 8, T, T),
          (C, 32, 12, 5, N, T), (A, 16, 12, 3, P, P), (A, 16, 12, 5, T, T), (A, 16, 12, 7, T, T), (C, 16, 12, 3, P, P),
          (D, 16, 12, 3, N, N), (D, 32, 12, 3, N, T)]

@@ -96,6 +96,7 @@ PAIR, TILE, NEXT = 2, 3, 5
     ((20, 20, 20, 8), 64, 18, 0, 3, 0, TILE), ((32, 32, 32, 8), 64, 18, 0, 12, 0, TILE), ((24, 24, 24, 8), 64, 18, 0, 8, 1, TILE),
     ((32, 32, 32, 8), 32, 12, 0, 12, 0, TILE), ((24, 24, 24, 8), 32, 12, 1, 8, 0, TILE), ((48, 48, 48, 24), 16, 12, 0, 2, 0, TILE),
     # and pairs one right-hand side after the other where all of them run at once
-    ((8, 8, 8, 4), 64, 18, 0, 16, 0, PAIR), ((16, 16, 16, 8), 32, 12, 0, 4, 0, PAIR)])
+    ((8, 8, 8, 4), 64, 18, 0, 16, 0, PAIR), ((16, 16, 16, 8), 32, 12, 0, 4, 0, PAIR),
+    ((12, 12, 12, 8), 64, 12, 1, 16, 0, PAIR), ((18, 18, 18, 8), 64, 12, 1, 6, 0, NEXT)])
 def test_choices(lib, L, prec, recon, full, nrhs, rare, form):
     assert choose(lib, prec, recon, full, [L], nrhs, rare)[0] == form
