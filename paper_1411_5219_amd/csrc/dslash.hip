@@ -1,5 +1,5 @@
-// Host side of the Dslash launches: block order and shape, right-hand-side
-// tile, grid, and the finalize step of fused reductions.  The kernels are
+// Host side of the Dslash launches: block order and shape, how right-hand sides
+// share them, grid, and the finalize step of fused reductions.  The kernels are
 // instantiated per storage precision in dslash64/32/16.hip.
 #include "lqcd.h"
 #include "lqcd_kernels.h"
@@ -101,7 +101,7 @@ hipError_t plan_dslash(int prec, int recon, bool dagger, int red, const DslashAr
     // half the group of blocks where a tile's spinors are twice as large or
     // both parities share the L2 (32^3x8, 4 right-hand sides: FP64 Schur 198 us
     // against 204, FP64 full 173 against 203, FP32/18 full 61 against 75; FP32
-    // Schur, 12 right-hand sides, is faster in groups of 4: 207 us against 213;
+    // Schur, 12 right-hand sides, is faster in groups of 4: 206 us against 211;
     // one right-hand side, FP64/18 full 32^3x8 54.8 -> 50.4, 48^3x12 326 -> 319,
     // but FP32/12 48^3x12 136 us with whole groups, 138 with halves)
     if (h.split == 0 ? prec == 64 || args.full : prec == 64 && args.full) c.block = cfg.block / 2;

@@ -12,7 +12,7 @@ namespace lqcd {
 constexpr int kSimds = 1024;  // 256 compute units of 4 SIMDs
 
 // Right-hand sides of a block (the kernel's bound).  Their spinors share the
-// XCD's L2: 32^3x8 FP32/12 Schur on 12 right-hand sides 207 us with 4 per
+// XCD's L2: 32^3x8 FP32/12 Schur on 12 right-hand sides 206 us with 4 per
 // block, 218 with 3, 245 with 2; 8 per block read more from beyond L2 (296).
 constexpr int kMaxTile = 4;
 

@@ -13,10 +13,11 @@
 // right-hand side per work-item with the links re-read through the caches
 // (and for FP16 two of them in registers): a link's third row is rebuilt once
 // for four right-hand sides and the link loads of a hop are one LDS read.
-// 32^3x8 Schur, 12 right-hand sides: FP32/12 241 -> 207 us, FP16/12 186 ->
-// 146, FP64/18 684 -> 565; 24^3x8 FP16/12 hop, 2: 15.2 -> 9.8.  Links are
-// loaded with the normal policy: the next tile finds them in the Infinity
-// Cache (streamed: 223 us instead of 207).
+// 32^3x8 Schur, 12 right-hand sides, calls back to back: FP32/12 241 -> 206 us
+// (a call by itself 260 -> 217), FP16/12 188 -> 139, FP64/18 683 -> 565.  Links
+// are loaded with the normal policy: the next tile finds them in the Infinity
+// Cache (streamed: FP32/12 219 us instead of 206, both parities of FP32/18 on
+// four 81 instead of 61; FP64/18 gains, 533 instead of 565).
 #pragma once
 
 #include "dslash_impl.h"

@@ -3,7 +3,7 @@
 // loads/stores in FP64, FP32 and FP16 storage, 12-real link reconstruction,
 // and the deterministic FP64 block reduction.
 //
-// Layouts (all per parity; Vh = V/2 sites, S = Vh rounded up to 256):
+// Layouts (all per parity; Vh = V/2 sites, S = Vh rounded up to an odd multiple of 16):
 //   spinor FP64 : 12 planes of double2, plane k = 3*spin + colour
 //   spinor FP32 :  6 planes of float4, plane k holds complex 2k and 2k+1
 //   spinor FP16 :  3 planes of 8 halves (complex 4k..4k+3, scaled) then one

@@ -18,7 +18,7 @@ struct Geom {
     int L[4];        // extents x, y, z, t (all even)
     int Lxh;         // L[0] / 2
     int Vh;          // sites per parity
-    int64_t S;       // plane stride in sites (Vh rounded up to 256)
+    int64_t S;       // plane stride in sites (Vh rounded up to an odd multiple of 16)
     double ph[4][2]; // exp(i theta_mu): applied on hops that cross the boundary
 };
 

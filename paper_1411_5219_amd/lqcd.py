@@ -434,7 +434,7 @@ def lqcd_autotune_stag(g, o, U, inp, out, reps=10, stream=None):
 
 
 def lqcd_autotune_dslash_rhs(g, o, U, inp, out, nrhs, reps=10, stream=None):
-    """Tunes the launch shape of hops on nrhs stacked fields (block request, tile, group) and installs it
+    """Tunes the launch shape of hops on nrhs stacked fields (the block request) and installs it
     as KERNEL_DSLASH_RHS; returns (launch, us per launch)."""
     best = Launch()
     us = ctypes.c_double()
